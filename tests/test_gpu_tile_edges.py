@@ -1,0 +1,79 @@
+"""The expert FFN calls at the sizes where a tile, a remainder or a dispatch rule can go wrong, against the oracle.
+
+Tolerances (largest difference over the largest reference value, per tensor and per expert): bf16 as in the other
+stage tests; fp32 2^-24 per rounded sum times the longest contraction here (2048 terms, worst case 1.2e-4) is covered
+by their 1e-4 because the errors of a sum partly cancel.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2602_11686_amd import binding as B
+from paper_2602_11686_amd import inputs as I
+from paper_2602_11686_amd.layer import MoeLayerBuffers
+from gpu_common import TOL, host
+from helpers import rel_max, rel_max_blocks, row_blocks
+
+pytestmark = pytest.mark.gpu
+
+
+def check_ffn(counts, d, f, dtype, seed, backward=True):
+    rng = np.random.default_rng(seed)
+    counts = np.array(counts, np.int32)
+    E, R = len(counts), int(counts.sum())
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    f32 = dtype == torch.float32
+
+    def values(*shape, std=1.0):
+        a = (rng.standard_normal(shape) * std).astype(np.float32)
+        if f32:
+            return torch.from_numpy(a).cuda(), a.astype(np.float64)
+        b = I.f32_to_bf16_bits(a)
+        return torch.from_numpy(b.view(np.int16)).cuda().view(torch.bfloat16), I.widen(b, np.float64)
+
+    (xp, xp_o), (dyp, dyp_o) = values(R, d), values(R, d)
+    (w1, w1_o), (w3, w3_o), (w2, w2_o) = values(E, d, f, std=0.05), values(E, d, f, std=0.05), values(E, f, d, std=0.05)
+    yp, A, Bm, H = O.ffn_fwd(xp_o, offsets, w1_o, w3_o, w2_o)
+    s = B.Shape(R, d, f, E, 1, dtype)     # T*k = R with k = 1: the shape only sizes the buffers of these calls
+    buf = MoeLayerBuffers(s, backward=True)
+    off = torch.from_numpy(offsets).cuda()
+    rows, tol = row_blocks(offsets), TOL[dtype]
+
+    def check(what, triples):
+        torch.cuda.synchronize()
+        for name, got, want, blocks in triples:
+            got = host(got)
+            assert np.isfinite(got).all(), (what, name)
+            assert rel_max(got, want) <= tol, (what, name)
+            err, e = rel_max_blocks(got, want, blocks)
+            assert err <= tol, (what, name, "expert", e, "rows", int(counts[e]), err)
+
+    for t in (buf.y_perm, buf.a_save, buf.b_save, buf.dx_perm, buf.dw1, buf.dw3, buf.dw2):
+        t.fill_(float("nan"))
+    B.moe_grouped_ffn_fwd(s, xp, off, w1, w3, w2, buf.y_perm, None, None, buf.ws)
+    check("inference", [("Yp", buf.y_perm, yp, rows)])
+    B.moe_grouped_ffn_fwd(s, xp, off, w1, w3, w2, buf.y_perm, buf.a_save, buf.b_save, buf.ws)
+    check("forward", [("Yp", buf.y_perm, yp, rows), ("A", buf.a_save, A, rows), ("B", buf.b_save, Bm, rows)])
+    if not backward:
+        return
+    ref = O.ffn_bwd(xp_o, offsets, w1_o, w3_o, w2_o, dyp_o)
+    grads = lambda: [("dXp", buf.dx_perm, ref[0], rows), ("dW1", buf.dw1, ref[1], range(E)),
+                     ("dW3", buf.dw3, ref[2], range(E)), ("dW2", buf.dw2, ref[3], range(E))]
+    for a, b in ((buf.a_save, buf.b_save), (None, None)):
+        B.moe_grouped_ffn_bwd(s, xp, off, w1, w3, w2, a, b, dyp, buf.dx_perm, buf.dw1, buf.dw3, buf.dw2, buf.ws)
+        check("backward", grads())
+    h = torch.full_like(buf.a_save, float("nan"))
+    B.moe_grouped_ffn_fwd_products(s, xp, off, w1, w3, w2, buf.y_perm, h, buf.a_save, buf.b_save)
+    B.moe_grouped_ffn_bwd_products(s, xp, off, w1, w3, w2, h, buf.a_save, buf.b_save, dyp, buf.dx_perm, buf.dw1,
+                                   buf.dw3, buf.dw2, buf.ws)
+    check("products", [("H", h, H, rows)] + grads())
+    for e in np.nonzero(counts == 0)[0]:
+        assert not buf.dw1[e].any() and not buf.dw3[e].any() and not buf.dw2[e].any()
+
+
+# fp32: 64x64 tiles (few tiles) and 128x128 tiles (the 2048-wide ones), remainders of rows, columns and k-stages
+@pytest.mark.parametrize("counts,d,f", [((1, 0, 63, 64, 65, 130), 68, 36), ((5, 17), 4, 132), ((0, 129, 300), 64, 16),
+                                        ((1200, 127, 0, 1), 2048, 260), ((700, 900), 260, 2048)])
+def test_ffn_f32(counts, d, f):
+    check_ffn(counts, d, f, torch.float32, 7 * d + f)
