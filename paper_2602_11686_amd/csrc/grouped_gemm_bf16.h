@@ -138,6 +138,9 @@ struct IntTag {
     static constexpr int value = N;
 };
 
+// what pieces past the end of a contraction are read from
+static __device__ __attribute__((aligned(512))) const uint32_t kZeroRow[128] = {};
+
 struct TileDesc {
     int e, m0, m_lim, n0, kbeg, kend, nk;  // nk = k-stages per K segment
     bool valid;
@@ -156,9 +159,12 @@ struct TileDesc {
 // finish times, while an XCD still works on one block of neighbouring tiles at a time.  The draw for the
 // next tile is made when a tile starts (one lane; its latency hides behind the main loop), reaches LDS
 // before the last barrier of the main loop and is read by all wavefronts after it.
-template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
+//
+// KREST (ragged M): K is no multiple of 64.  An instance of its own, because the test of the last stage in the
+// main loop's issue side costs 1.6 % where no stage is partial.
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool KREST = false>
 __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
-    static_assert(RAGK ? (AT == 1 && BT == 0) : (AT == 0), "operand forms");
+    static_assert(RAGK ? (AT == 1 && BT == 0 && !KREST) : (AT == 0), "operand forms");
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kTableOff);  // [E+1] rows of each expert
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
             }
         }
         t.n0 = nt * n_out;
-        t.nk = (t.kend - t.kbeg + TK - 1) / TK;  // exact when M is ragged (K % 64 == 0)
+        t.nk = (t.kend - t.kbeg + TK - 1) / TK;
         if (!RAGK && t.m0 >= t.m_lim) t.nk = 0;   // the lower half of a tile of at most 128 rows: nothing to do
         t.e = __builtin_amdgcn_readfirstlane(t.e);
         t.m0 = __builtin_amdgcn_readfirstlane(t.m0);
@@ -386,15 +392,35 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
         if constexpr (!RAGK) {
             const char* Ab = (sg ? sA[1] : sA[0]) + (int64_t)k0 * 2;
             const char* Bb = (sg ? sB[1] : sB[0]) + (BT == 1 ? (int64_t)k0 * 2 : (int64_t)k0 * ldb * 2);
+            if (!KREST || k0 + TK <= di.kend) {  // (wave-uniform) the whole stage lies inside the contraction
 #pragma unroll
-            for (int i = 0; i < CPW; ++i) {
-                if (i < lo || i >= hi) continue;
-                dma16_s(Ab, a_off[i], st + i * 1024);
-            }
+                for (int i = 0; i < CPW; ++i) {
+                    if (i < lo || i >= hi) continue;
+                    dma16_s(Ab, a_off[i], st + i * 1024);
+                }
 #pragma unroll
-            for (int i = 0; i < CPW; ++i) {
-                if (CPW + i < lo || CPW + i >= hi) continue;
-                dma16_s(Bb, b_off[i], st + kBOff + i * 1024);
+                for (int i = 0; i < CPW; ++i) {
+                    if (CPW + i < lo || CPW + i >= hi) continue;
+                    dma16_s(Bb, b_off[i], st + kBOff + i * 1024);
+                }
+            } else {
+                // last stage of a K that is no multiple of 64 (it is one of 8, so a 16-byte piece is inside or
+                // outside as a whole): what lies past the end reads zeros, on both sides
+                const int left = di.kend - k0;  // 8 .. TK-8
+                const char* zeros = reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16;
+#pragma unroll
+                for (int i = 0; i < CPW; ++i) {
+                    if (i < lo || i >= hi) continue;
+                    const int r = (wave * CPW + i) * 8 + (lane >> 3);
+                    dma16(((lane & 7) ^ swz_rows(r)) * 8 < left ? Ab + a_off[i] : zeros, st + i * 1024);
+                }
+#pragma unroll
+                for (int i = 0; i < CPW; ++i) {
+                    if (CPW + i < lo || CPW + i >= hi) continue;
+                    const int r = (wave * CPW + i) * 8 + (lane >> 3);
+                    const int k = BT == 1 ? ((lane & 7) ^ swz_rows(r)) * 8 : qb_row[i];
+                    dma16(k < left ? Bb + b_off[i] : zeros, st + kBOff + i * 1024);
+                }
             }
         } else {
             const char* Ab = reinterpret_cast<const char*>(sg ? iA[1] : iA[0]) + (int64_t)k0 * lda * 2;

@@ -77,3 +77,10 @@ def check_ffn(counts, d, f, dtype, seed, backward=True):
                                         ((1200, 127, 0, 1), 2048, 260), ((700, 900), 260, 2048)])
 def test_ffn_f32(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 7 * d + f)
+
+
+# bf16 contractions that end inside a 64-wide stage: one piece, one piece short of a stage, several stages and a rest
+@pytest.mark.parametrize("counts,d,f", [((3, 0, 130), 8, 8), ((257, 64, 1), 56, 72), ((128, 300, 2), 200, 328),
+                                        ((520, 31), 264, 1096)])
+def test_ffn_bf16_k_remainder(counts, d, f):
+    check_ffn(counts, d, f, torch.bfloat16, 11 * d + f)
