@@ -51,6 +51,10 @@ size_t gate_bwd_workspace_bytes(const moe_shape* s);
 void launch_gate_dwg_gemm(const void* x, const void* dl_hi, const void* dl_lo, const int32_t* chunk_offsets,
                           int nchunks, int d, int n_pad, float* partial, const void* zero_row, hipStream_t st);
 
+// the same in fp32: dl [T][n_pad], n_pad a multiple of four
+void launch_gate_dwg_gemm_f32(const void* x, const void* dl, const int32_t* chunk_offsets, int nchunks, int d, int n_pad,
+                              float* partial, hipStream_t st);
+
 // dx += (dl_hi + dl_lo) * wg_pad^T on the matrix cores (implemented next to the grouped GEMM):
 // dl_hi / dl_lo [T][n_pad] bf16, wg_pad [d][n_pad] bf16 (gate weight, columns past E zero), n_pad a multiple
 // of 64, whole = {0, T} in device memory, dx [T][d] bf16 read and written.

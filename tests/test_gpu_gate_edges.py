@@ -1,0 +1,80 @@
+"""The gate's calls at the edges of their kernels (expert tiles, token tiles, remainders of the hidden dimension),
+against 64-bit arithmetic.
+
+Logits: fp32 sums of d products of N(0,1) x N(0,0.02) values, each off by at most d * 2^-24 of the sum of the absolute
+products; 1e-5 of the logits' scale is what the stage tests allow as well.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_11686_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def gate_case(T, d, E, k, dtype, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.empty(T, d, dtype=dtype, device="cuda").normal_(generator=g)
+    wg = torch.empty(d, E, dtype=dtype, device="cuda").normal_(0.0, 0.02, generator=g)
+    bias = torch.empty(E, dtype=torch.float32, device="cuda").normal_(0.0, 0.1, generator=g)
+    s = B.Shape(T, d, 8, E, k, dtype)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    out = (torch.full((T, k), -7, dtype=torch.int32, device="cuda"), torch.empty(T, k, device="cuda"),
+           torch.full((T, E), float("nan"), device="cuda"))
+    return s, x, wg, bias, ws, out
+
+
+SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260, 17, 3, torch.float32),
+         (33, 132, 65, 4, torch.float32), (70, 1024, 130, 8, torch.float32), (40, 516, 256, 8, torch.float32),
+         (1, 8, 2, 2, torch.bfloat16), (31, 264, 33, 5, torch.bfloat16), (50, 1096, 200, 8, torch.bfloat16),
+         (1, 256, 8, 2, torch.bfloat16), (33, 512, 256, 8, torch.bfloat16), (64, 2048, 128, 8, torch.bfloat16)]
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", SIZES)
+def test_gate_topk_edges(T, d, E, k, dtype):
+    s, x, wg, bias, ws, (ids, w, logits) = gate_case(T, d, E, k, dtype, T + d + E)
+    B.moe_gate_topk(s, x, wg, bias, ids, w, logits, ws)
+    want = x.double() @ wg.double() + bias.double()
+    scale = max(1.0, float(want.abs().max()))
+    assert float((logits.double() - want).abs().max()) <= 1e-5 * scale
+    # the picks are the sorted top-k of the logits that the call returned, lower index first among equals
+    order = np.argsort(-logits.cpu().numpy(), axis=1, kind="stable")[:, :k]
+    np.testing.assert_array_equal(ids.cpu().numpy(), order)
+    ref_w = torch.softmax(want.gather(1, ids.long()), 1)
+    assert float((w.double() - ref_w).abs().max()) <= 1.2e-5
+
+
+@pytest.mark.parametrize("d,dtype", [(36, torch.float32), (264, torch.bfloat16), (256, torch.bfloat16)])
+def test_gate_topk_with_nan_and_equal_logits(d, dtype):
+    """Equal columns: lower expert first.  A token without a comparable logit still gets indices in range."""
+    s, x, wg, bias, ws, (ids, w, logits) = gate_case(20, d, 6, 3, dtype, 5)
+    wg[:] = wg[:, :1]
+    bias.zero_()
+    x[7] = float("nan")
+    B.moe_gate_topk(s, x, wg, bias, ids, w, logits, ws)
+    got = ids.cpu().numpy()
+    assert ((got >= 0) & (got < 6)).all()
+    for t in range(20):
+        if t != 7:
+            assert got[t].tolist() == [0, 1, 2]
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", [(1, 36, 5, 2, torch.float32), (33, 68, 65, 3, torch.float32),
+                                           (700, 128, 8, 2, torch.float32), (300, 1028, 256, 8, torch.float32)])
+def test_gate_bwd_edges(T, d, E, k, dtype):
+    s, x, wg, bias, ws, (ids, w, logits) = gate_case(T, d, E, k, dtype, 3 * T + E)
+    B.moe_gate_topk(s, x, wg, bias, ids, w, None, ws)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    dw = torch.empty(T, k, device="cuda").normal_(generator=g)
+    dx = torch.empty(T, d, dtype=dtype, device="cuda").normal_(generator=g)
+    dx0, dwg = dx.double(), torch.full((d, E), float("nan"), device="cuda")
+    B.moe_gate_topk_bwd(s, x, wg, ids, w, dw, dx, dwg, ws)
+    wd, dwd = w.double(), dw.double()
+    dl = torch.zeros(T, E, dtype=torch.float64, device="cuda").scatter_(
+        1, ids.long(), wd * (dwd - (wd * dwd).sum(1, keepdim=True)))
+    ref = x.double().t() @ dl
+    # fp32 sums of T products: 2^-24 each, partly cancelling; 1e-5 of the largest is 170 roundings of the whole sum
+    assert float((dwg.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+    ref = dx0 + dl @ wg.double().t()
+    assert float((dx.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
