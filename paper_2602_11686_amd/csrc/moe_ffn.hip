@@ -274,6 +274,114 @@ __global__ __launch_bounds__(256) void gg_bf16_kernel(const GArgs g) {
 #include "grouped_gemm_bf16.h"
 namespace moe {
 
+// Ragged M: the expert e whose tiles hold tile L of the launch, its rows [row0, row_end) and the tile's index among
+// the expert's.  False past the last tile.  Every wavefront looks it up by itself: lane l counts the tiles of
+// experts 4l .. 4l+3, then a scan over the lanes.
+template <int BM>
+__device__ __forceinline__ bool find_tile(const GArgs& g, int L, int n_tiles, int& e, int& row0, int& row_end, int& local) {
+    const int lane = threadIdx.x & 63;
+    int cnt[4], beg[4], end[4], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = lane * 4 + u;
+        beg[u] = x < g.E ? g.offsets[x] : 0;
+        end[u] = x < g.E ? g.offsets[x + 1] : 0;
+        cnt[u] = (end[u] - beg[u] + BM - 1) / BM * n_tiles;
+        sum += cnt[u];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int dlt = 1; dlt < 64; dlt <<= 1) {
+        const int o = __shfl_up(incl, dlt, 64);
+        if (lane >= dlt) incl += o;
+    }
+    int run = incl - sum, fe = 0, fl = 0, fb = 0, fn = 0;
+    bool mine = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (L >= run && L < run + cnt[u]) {
+            mine = true;
+            fe = lane * 4 + u;
+            fl = L - run;
+            fb = beg[u];
+            fn = end[u];
+        }
+        run += cnt[u];
+    }
+    const uint64_t who = __ballot(mine);
+    if (!who) return false;  // (the same in every wavefront)
+    const int src = __builtin_ctzll(who);
+    e = __builtin_amdgcn_readlane(fe, src);
+    local = __builtin_amdgcn_readlane(fl, src);
+    row0 = __builtin_amdgcn_readlane(fb, src);
+    row_end = __builtin_amdgcn_readlane(fn, src);
+    return true;
+}
+
+// four consecutive columns of one output row
+__device__ __forceinline__ void put4(float* p, const f32x4v v) { *reinterpret_cast<f32x4v*>(p) = v; }
+__device__ __forceinline__ void put4(bf16_t* p, const f32x4v v) {
+    *reinterpret_cast<u32x2*>(p) = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+__device__ __forceinline__ f32x4v get4(const float* p) { return *reinterpret_cast<const f32x4v*>(p); }
+__device__ __forceinline__ f32x4v get4(const bf16_t* p) {
+    const u32x2 u = *reinterpret_cast<const u32x2*>(p);
+    return (f32x4v){__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xFFFF0000u), __uint_as_float(u[1] << 16),
+                    __uint_as_float(u[1] & 0xFFFF0000u)};
+}
+template <class T, int EPI>
+__device__ __forceinline__ void epilogue_x4(const GArgs& g, int64_t idx, const f32x4v a, const f32x4v b) {
+    auto to = [&](const void* p) { return static_cast<T*>(const_cast<void*>(p)) + idx; };
+    if constexpr (EPI == EPI_STORE) {
+        put4(to(g.C0), a);
+    } else if constexpr (EPI == EPI_STORE2) {
+        put4(to(g.C0), a);
+        put4(to(g.C1), b);
+    } else if constexpr (EPI == EPI_SWIGLU) {
+        f32x4v h, p, q;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const float sA = silu_f(a[z]);
+            h[z] = sA * b[z];
+            p[z] = g.products ? b[z] * silu_grad_f(a[z]) : a[z];
+            q[z] = g.products ? sA : b[z];
+        }
+        put4(to(g.C0), h);
+        if (g.S0) {
+            put4(to(g.S0), p);
+            put4(to(g.S1), q);
+        }
+    } else if constexpr (EPI == EPI_DHP) {  // a = dH; saved P, Q
+        const f32x4v P = get4(to(g.S0)), Q = get4(to(g.S1));
+        f32x4v da, db;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            da[z] = a[z] * P[z];
+            db[z] = a[z] * Q[z];
+        }
+        put4(to(g.C1), da);
+        put4(to(g.C2), db);
+    } else {
+        static_assert(EPI == EPI_DH, "one of the epilogues above");  // a = dH
+        const f32x4v A = get4(to(g.S0)), B = get4(to(g.S1));
+        f32x4v h, da, db;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const float sA = silu_f(A[z]);
+            h[z] = sA * B[z];
+            da[z] = a[z] * B[z] * silu_grad_f(A[z]);
+            db[z] = a[z] * sA;
+        }
+        put4(to(g.C0), h);
+        put4(to(g.C1), da);
+        put4(to(g.C2), db);
+    }
+}
+
+}  // namespace moe
+#include "grouped_gemm_few_rows.h"
+namespace moe {
+
 // =============================== fp32 path ====================================
 // v_mfma_f32_16x16x4: fp32 operands, products and sums, at twice the rate of the scalar FMA units.  What bounds
 // these products is the matrix pipe (154 TFLOP/s measured for a large fp32 product of the library): a stage of
@@ -334,56 +442,6 @@ struct F32Tile {
     }
 };
 
-// four consecutive columns of one output row
-template <int EPI>
-__device__ __forceinline__ void epilogue_f32x4(const GArgs& g, int64_t idx, const f32x4v a, const f32x4v b) {
-    auto at = [&](const void* p) -> f32x4v& { return *reinterpret_cast<f32x4v*>(static_cast<float*>(const_cast<void*>(p)) + idx); };
-    if constexpr (EPI == EPI_STORE) {
-        at(g.C0) = a;
-    } else if constexpr (EPI == EPI_STORE2) {
-        at(g.C0) = a;
-        at(g.C1) = b;
-    } else if constexpr (EPI == EPI_SWIGLU) {
-        f32x4v h, p, q;
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            const float sA = silu_f(a[z]);
-            h[z] = sA * b[z];
-            p[z] = g.products ? b[z] * silu_grad_f(a[z]) : a[z];
-            q[z] = g.products ? sA : b[z];
-        }
-        at(g.C0) = h;
-        if (g.S0) {
-            at(g.S0) = p;
-            at(g.S1) = q;
-        }
-    } else if constexpr (EPI == EPI_DHP) {  // a = dH; saved P, Q
-        const f32x4v P = at(g.S0), Q = at(g.S1);
-        f32x4v da, db;
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            da[z] = a[z] * P[z];
-            db[z] = a[z] * Q[z];
-        }
-        at(g.C1) = da;
-        at(g.C2) = db;
-    } else {
-        static_assert(EPI == EPI_DH, "epilogues of the fp32 path");  // a = dH
-        const f32x4v A = at(g.S0), B = at(g.S1);
-        f32x4v h, da, db;
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            const float sA = silu_f(A[z]);
-            h[z] = sA * B[z];
-            da[z] = a[z] * B[z] * silu_grad_f(A[z]);
-            db[z] = a[z] * sA;
-        }
-        at(g.C0) = h;
-        at(g.C1) = da;
-        at(g.C2) = db;
-    }
-}
-
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK, int BM>
 __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
@@ -409,42 +467,9 @@ __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
         kbeg = g.offsets[e];
         kend = g.offsets[e + 1];
     } else {
-        // every wavefront by itself: lane l counts the tiles of experts 4l .. 4l+3, then a scan over the lanes
-        int cnt[4], beg[4], end[4], sum = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int x = lane * 4 + u;
-            beg[u] = x < g.E ? g.offsets[x] : 0;
-            end[u] = x < g.E ? g.offsets[x + 1] : 0;
-            cnt[u] = (end[u] - beg[u] + BM - 1) / BM * n_tiles;
-            sum += cnt[u];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int dlt = 1; dlt < 64; dlt <<= 1) {
-            const int o = __shfl_up(incl, dlt, 64);
-            if (lane >= dlt) incl += o;
-        }
-        int run = incl - sum, fe = 0, fl = 0, fb = 0, fn = 0;
-        bool mine = false;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (L >= run && L < run + cnt[u]) {
-                mine = true;
-                fe = lane * 4 + u;
-                fl = L - run;
-                fb = beg[u];
-                fn = end[u];
-            }
-            run += cnt[u];
-        }
-        const uint64_t who = __ballot(mine);
-        if (!who) return;  // past the last tile (the same in every wavefront)
-        const int src = __builtin_ctzll(who);
-        e = __builtin_amdgcn_readlane(fe, src);
-        const int b = __builtin_amdgcn_readlane(fb, src);
-        m_lim = __builtin_amdgcn_readlane(fn, src);
-        walk_tile(__builtin_amdgcn_readlane(fl, src), (m_lim - b + BM - 1) / BM, n_tiles, m, nt);
+        int local, b;
+        if (!find_tile<BM>(g, L, n_tiles, e, b, m_lim, local)) return;
+        walk_tile(local, (m_lim - b + BM - 1) / BM, n_tiles, m, nt);
         m0 = b + m * BM;
         kbeg = 0;
         kend = g.K;
@@ -509,11 +534,46 @@ __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
         for (int j = 0; j < NJ4; ++j) {
             const int row = m0 + wm + i * 16 + l16, col = n0 + b_row(j) + kg * 4;
             if (row < m_lim && col < g.N)
-                epilogue_f32x4<EPI>(g, cbase + (int64_t)row * g.ldc + col, acc[i][j], acc[i][DUAL ? j + NB / 2 : j]);
+                epilogue_x4<float, EPI>(g, cbase + (int64_t)row * g.ldc + col, acc[i][j], acc[i][DUAL ? j + NB / 2 : j]);
         }
 }
 
 // =============================== host dispatch ================================
+// Few rows per expert: the kernel of grouped_gemm_few_rows.h where it is the faster one.  The rows of each expert are
+// known on the device only, so the rule goes by their mean, and by whether gg256_kernel's tiles would leave half
+// of the chip idle.  Where the lines lie (us, gg256_kernel -> this; 64 experts of 2048 x 1408 and, with "half the chip
+// idle" in the products that end in d columns, 8 of 4096 x 7168; the products in the order forward 1, forward 2,
+// dgrad 1, dgrad 2):
+//   mean 16, 64 experts: 206 -> 142, 76 -> 69, 105 -> 90, 148 -> 115    8 experts: 264 -> 178, 155 -> 76, 106 -> 101, 298 -> 139
+//   mean 32, 64 experts: 208 -> 157, 79 -> 84 (not taken), 112 -> 98, 155 -> 135
+//   mean 64, 64 experts: 216 -> 179, 84 -> 106, 121 -> 124, 170 -> 189  8 experts: 262 -> 210, 154 -> 107, 107 -> 133, 304 -> 202
+//   mean 128, 64 experts: 229 -> 248, 117 -> 155, 145 -> 176, 237 -> 274 (none taken)
+template <int BT, bool DUAL, int EPI>
+static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
+    auto go = [&](auto kern, int bm, int n_out, int lds) {
+        const int64_t tiles = (g.N + n_out - 1) / n_out * (R / bm + (R < g.E ? R : g.E));  // (upper bound)
+        ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+        kern<<<(unsigned)((tiles + 63) / 64 * 64), kFewThreads, lds, st>>>(g);
+        return true;
+    };
+    const int64_t n256 = (g.N + (DUAL ? 127 : 255)) / (DUAL ? 128 : 256);
+    const bool half_idle = 2 * n256 * g.E <= 256;
+    if (R > 64 * (int64_t)g.E) return false;
+    const bool to32 = R <= 32 * (int64_t)g.E;
+    if constexpr (DUAL) {
+        if (to32) return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 2, 3>, 64, 64, few_rows_lds<64, 2, 3>());
+        return go(gg_few_rows_kernel<BT, DUAL, EPI, 128, 2, 2>, 128, 64, few_rows_lds<128, 2, 2>());
+    } else if constexpr (BT == 0) {
+        if (R <= 16 * (int64_t)g.E || (half_idle && to32))
+            return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 2, 3>, 64, 128, few_rows_lds<64, 2, 3>());
+        if (half_idle) return go(gg_few_rows_kernel<BT, DUAL, EPI, 128, 2, 3>, 128, 128, few_rows_lds<128, 2, 3>());
+    } else {
+        if (to32) return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 1, 3>, 64, 64, few_rows_lds<64, 1, 3>());
+        if (half_idle) return go(gg_few_rows_kernel<BT, DUAL, EPI, 128, 1, 3>, 128, 64, few_rows_lds<128, 1, 3>());
+    }
+    return false;
+}
+
 // A(m,k) layout AT, B(k,n) layout BT as in the bf16 kernel.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t st) {
@@ -524,6 +584,9 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             const bool ok = g.lda % 8 == 0 && g.ldb % 8 == 0 && g.N >= 8 && g.lda < (1 << 21) && g.ldb < (1 << 21) && g.ldc < (1 << 22) &&
                             (uint64_t)R * (uint64_t)g.lda < (1ull << 32) && (uint64_t)g.N * (uint64_t)g.ldb < (1ull << 32) &&
                             (!RAGK || g.M >= 8);
+            if constexpr (!RAGK) {
+                if (ok && launch_few_rows<BT, DUAL, EPI>(g, R, st)) return;
+            }
             if (ok) {
                 auto kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK>;
                 if constexpr (!RAGK)

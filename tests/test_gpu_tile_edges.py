@@ -84,3 +84,13 @@ def test_ffn_f32(counts, d, f):
                                         ((520, 31), 264, 1096)])
 def test_ffn_bf16_k_remainder(counts, d, f):
     check_ffn(counts, d, f, torch.bfloat16, 11 * d + f)
+
+
+# few rows per expert: 64-row tiles (mean at most 32) and 128-row ones (mean 33 .. 64, with and without enough column
+# tiles for the wide kernel), 16-row blocks, tails, an expert of several tiles, one to five k-stages and a remainder
+@pytest.mark.parametrize("counts,d,f", [((1, 0, 0, 2), 64, 64), ((15, 16, 17, 1, 0, 33, 64, 65), 128, 192),
+                                        ((0, 0, 0, 129), 200, 72), ((3,) * 7 + (0, 90), 320, 264),
+                                        ((128, 1, 63), 72, 136), ((40, 129, 0, 60), 264, 1096),
+                                        ((60,) * 40, 512, 1024), ((20,) * 30 + (300, 0), 1024, 520)])
+def test_ffn_few_rows(counts, d, f):
+    check_ffn(counts, d, f, torch.bfloat16, 13 * d + f)
