@@ -10,7 +10,31 @@
 
 namespace moe {
 
-size_t gate_workspace_bytes(const moe_shape* s) { return align_up((size_t)MOE_MAX_EXPERTS * s->d * 2, 256); }
+// What moe_gate_topk cannot do without (bf16 with d a multiple of 256: the packed gate weight).
+static inline size_t gate_needed_bytes(const moe_shape* s) { return align_up((size_t)MOE_MAX_EXPERTS * s->d * 2, 256); }
+
+// ---- short batches: the hidden dimension split over workgroups --------------------------------------------
+constexpr int kGateF32Tokens = 16, kGateF32Waves = 8;
+static inline int gate_tiles16(int E) { const int n = (E + 15) / 16; return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : n <= 8 ? 8 : 16; }
+// workgroups per token tile: enough for every compute unit, at least 16 values of the hidden dimension per wavefront
+static inline int gate_splits(const moe_shape* s) {
+    const int tiles = (s->T + kGateF32Tokens - 1) / kGateF32Tokens;
+    const int want = (256 + tiles - 1) / tiles, most = (s->d + 16 * kGateF32Waves - 1) / (16 * kGateF32Waves);
+    const int n = want < most ? want : most;
+    return n < 32 ? n : 32;
+}
+// Up to how many tokens: a token tile of the kernels that contract the whole hidden dimension takes its 10 to 70 us
+// however few tiles there are (bf16, 8 .. 1024 tokens of 2048 x 64 experts: 15-18 us with the packing of the weight,
+// 7-15 us split; of 4096 x 128: 59-64 and 12-45).  At 2048 tokens the packed bf16 kernel is the faster one again
+// (18 and 23; 64 and 87), the fp32 one is not (of 2048 x 128: 38 us whole, 26 split).
+static inline bool gate_packed(const moe_shape* s) { return s->dtype == MOE_BF16 && s->d % 256 == 0; }
+static inline size_t gate_split_bytes(const moe_shape* s) {
+    return s->T <= (gate_packed(s) ? 1024 : 2048) && gate_splits(s) > 1 ? (size_t)gate_splits(s) * s->T * gate_tiles16(s->E) * 16 * sizeof(float) : 0;
+}
+size_t gate_workspace_bytes(const moe_shape* s) {
+    const size_t a = gate_needed_bytes(s), b = align_up(gate_split_bytes(s), 256);
+    return a > b ? a : b;
+}
 
 // ---- bf16 forward on the matrix cores ------------------------------------------------------
 // One workgroup = 32 tokens, 4 wavefronts; wavefront w contracts the quarter
@@ -62,10 +86,10 @@ __device__ __forceinline__ float wave_max_f32(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-// What follows the contraction, in one workgroup of NW wavefronts: part [NW][MT][EP] holds the partial logits of MT
+// What follows the contraction, in one workgroup of NW wavefronts: part [NP][MT][EP] holds the partial logits of MT
 // tokens, added in a fixed order; then top-k and softmax.  A wavefront finishes MT/NW tokens.  part is reused for
 // the picked logits ([MT][MOE_MAX_EXPERTS]).
-template <int EP, int NW, int MT>
+template <int EP, int NP, int NW, int MT>
 __device__ __forceinline__ void gate_finish(float* part, const float* __restrict__ bias, int32_t* __restrict__ ids,
                                             float* __restrict__ wout, float* __restrict__ logits_out, int t0, int Tn,
                                             int E, int k) {
@@ -84,7 +108,7 @@ __device__ __forceinline__ void gate_finish(float* part, const float* __restrict
             if (e < E) {
                 v = part[row * EP + e];
 #pragma unroll
-                for (int q = 1; q < NW; ++q) v += part[(q * MT + row) * EP + e];  // fixed order
+                for (int q = 1; q < NP; ++q) v += part[(q * MT + row) * EP + e];  // fixed order
                 v += bias ? bias[e] : 0.f;
             }
             vals[i][j] = v;
@@ -201,7 +225,7 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* _
             mine[row * EP + j * 32 + l32] = acc[j][r];
         }
     __syncthreads();
-    gate_finish<NT * 32, NW, kGateMT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
+    gate_finish<NT * 32, NW, NW, kGateMT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
 }
 
 // ---- fp32, and bf16 with a hidden dimension that the kernel above does not split evenly ------------------
@@ -211,7 +235,10 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* _
 // wavefront requests U 16-wide pieces before it uses the first.  bf16 values are widened, which is exact.
 // Measured against one lane per expert and a serial walk of the hidden dimension (us): fp32, 2048 tokens x 1024, 8
 // experts 200 -> 7; fp32, 256 x 128, 8 experts 33 -> 4; bf16, 4099 x 1096, 24 experts 300 -> 26.
-constexpr int kGateF32Tokens = 16, kGateF32Waves = 8;
+template <int N>
+struct GateTag {
+    static constexpr int value = N;
+};
 
 __device__ __forceinline__ gf32x4 gate_load4(const float* p) { return *reinterpret_cast<const gf32x4*>(p); }
 __device__ __forceinline__ gf32x4 gate_load4(const bf16_t* p) {
@@ -220,10 +247,12 @@ __device__ __forceinline__ gf32x4 gate_load4(const bf16_t* p) {
                     __uint_as_float(u.y & 0xFFFF0000u)};
 }
 
-template <class T, int NT>  // NT expert tiles of 16
+// SPLIT: blockIdx.y picks a slice of the hidden dimension; the sums over the slice go to `slices`
+// ([gridDim.y][Tn][NT*16]) and gate_split_finish_kernel does the rest.
+template <class T, int NT, bool SPLIT>  // NT expert tiles of 16
 __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     const T* __restrict__ x, const T* __restrict__ wg, const float* __restrict__ bias, int32_t* __restrict__ ids,
-    float* __restrict__ wout, float* __restrict__ logits_out, int Tn, int d, int E, int k) {
+    float* __restrict__ wout, float* __restrict__ logits_out, float* __restrict__ slices, int Tn, int d, int E, int k) {
     extern __shared__ float part[];  // [waves][16][NT*16] partial logits, then the picked logits
     constexpr int NW = kGateF32Waves, MT = kGateF32Tokens, EP = NT * 16;
     constexpr int U = NT <= 2 ? 4 : NT <= 4 ? 2 : 1;
@@ -231,8 +260,9 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     const int l16 = lane & 15, kg = lane >> 4;
     const int t0 = blockIdx.x * MT;
     const int trow = min(t0 + l16, Tn - 1);
-    const int kq = (d + 16 * NW - 1) / (16 * NW) * 16;
-    const int kb = min(wave * kq, d), ke = min(kb + kq, d);
+    const int nw = NW * (SPLIT ? (int)gridDim.y : 1), w = SPLIT ? (int)blockIdx.y * NW + wave : wave;
+    const int kq = (d + 16 * nw - 1) / (16 * nw) * 16;
+    const int kb = min(w * kq, d), ke = min(kb + kq, d);
     gf32x4 acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = (gf32x4){0.f, 0.f, 0.f, 0.f};
@@ -267,25 +297,61 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) mine[(kg * 4 + r) * EP + j * 16 + l16] = acc[j][r];
     __syncthreads();
-    gate_finish<EP, NW, MT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
+    if constexpr (SPLIT) {
+        for (int i = threadIdx.x; i < MT * EP; i += NW * 64) {
+            float v = part[i];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) v += part[q * MT * EP + i];  // fixed order
+            if (t0 + i / EP < Tn) slices[((size_t)blockIdx.y * Tn + t0) * EP + i] = v;
+        }
+    } else {
+        gate_finish<EP, NW, NW, MT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
+    }
+}
+
+// the slices' sums of four tokens, added in slice order, then top-k and softmax (one wavefront per token)
+template <int NT>
+__global__ __launch_bounds__(256) void gate_split_finish_kernel(const float* __restrict__ slices, int nslices,
+                                                                const float* __restrict__ bias, int32_t* __restrict__ ids,
+                                                                float* __restrict__ wout, float* __restrict__ logits_out,
+                                                                int Tn, int E, int k) {
+    constexpr int EP = NT * 16, MT = 4;
+    __shared__ float part[MT * MOE_MAX_EXPERTS];
+    const int t0 = blockIdx.x * MT;
+    for (int i = threadIdx.x; i < MT * EP; i += 256) {
+        const int t = min(t0 + i / EP, Tn - 1);
+        float v = 0.f;
+#pragma unroll 8
+        for (int q = 0; q < nslices; ++q) v += slices[((size_t)q * Tn + t) * EP + i % EP];
+        part[i] = v;
+    }
+    __syncthreads();
+    gate_finish<EP, 1, 4, MT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
 }
 
 template <class T>
 static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, const float* bias, int32_t* ids, float* w,
-                                 float* logits, hipStream_t st) {
-    auto go = [&](auto kern, int nt) {
-        size_t lds = (size_t)kGateF32Waves * kGateF32Tokens * nt * 16 * sizeof(float);
+                                 float* logits, float* slices, hipStream_t st) {
+    auto go = [&](auto nt_tag) {
+        constexpr int NT = decltype(nt_tag)::value;
+        size_t lds = (size_t)kGateF32Waves * kGateF32Tokens * NT * 16 * sizeof(float);
         if (lds < (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float);
+        const dim3 grid((s->T + kGateF32Tokens - 1) / kGateF32Tokens, slices ? gate_splits(s) : 1);
+        auto kern = slices ? gate_topk_f32_kernel<T, NT, true> : gate_topk_f32_kernel<T, NT, false>;
         ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGateF32Waves * kGateF32Tokens * MOE_MAX_EXPERTS * 4);
-        kern<<<(s->T + kGateF32Tokens - 1) / kGateF32Tokens, kGateF32Waves * 64, lds, st>>>(x, wg, bias, ids, w, logits, s->T,
-                                                                                           s->d, s->E, s->k);
+        kern<<<grid, kGateF32Waves * 64, lds, st>>>(x, wg, bias, ids, w, logits, slices, s->T, s->d, s->E, s->k);
+        if (slices)
+            gate_split_finish_kernel<NT><<<(s->T + 3) / 4, 256, 0, st>>>(slices, (int)grid.y, bias, ids, w, logits, s->T, s->E, s->k);
     };
-    if (s->E <= 16) go(gate_topk_f32_kernel<T, 1>, 1);
-    else if (s->E <= 32) go(gate_topk_f32_kernel<T, 2>, 2);
-    else if (s->E <= 64) go(gate_topk_f32_kernel<T, 4>, 4);
-    else if (s->E <= 128) go(gate_topk_f32_kernel<T, 8>, 8);
-    else go(gate_topk_f32_kernel<T, 16>, 16);
+    switch (gate_tiles16(s->E)) {
+        case 1: go(GateTag<1>{}); break;
+        case 2: go(GateTag<2>{}); break;
+        case 4: go(GateTag<4>{}); break;
+        case 8: go(GateTag<8>{}); break;
+        default: go(GateTag<16>{}); break;
+    }
 }
+
 // ---- backward -----------------------------------------------------------------------
 
 // wgT[e][c] = w_gate[c][e] as fp32 (makes the dx update a contiguous read)
@@ -474,12 +540,18 @@ extern "C" moe_status moe_gate_topk(const moe_shape* s, const void* x, const voi
     MOE_RETURN_IF(check_ptr(topk_w, "topk_w", who));
     MOE_RETURN_IF(check_ptr(logits_out, "logits_out", who, true));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (s->dtype == MOE_BF16 && s->d % 256 == 0) {
+    const bool packed = gate_packed(s);
+    if (packed) {
         MOE_RETURN_IF(check_ptr(ws, "ws", who));
-        if (ws_bytes < gate_workspace_bytes(s)) {
-            set_error("%s: workspace %zu < %zu bytes", who, ws_bytes, gate_workspace_bytes(s));
+        if (ws_bytes < gate_needed_bytes(s)) {
+            set_error("%s: workspace %zu < %zu bytes", who, ws_bytes, gate_needed_bytes(s));
             return MOE_ERR_WORKSPACE_TOO_SMALL;
         }
+    }
+    // (a caller may bring less workspace than moe_workspace_bytes says, or none where it is not needed)
+    const size_t split = gate_split_bytes(s);
+    float* slices = split && ws && aligned16(ws) && ws_bytes >= split ? static_cast<float*>(ws) : nullptr;
+    if (packed && !slices) {
         const int nt = (s->E + 31) / 32;
         const int NT = nt <= 1 ? 1 : nt <= 2 ? 2 : nt <= 4 ? 4 : 8;
         bf16_t* wgT = static_cast<bf16_t*>(ws);
@@ -506,10 +578,10 @@ extern "C" moe_status moe_gate_topk(const moe_shape* s, const void* x, const voi
     }
     if (s->dtype == MOE_BF16)
         launch_gate_topk_f32(s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w_gate), bias, topk_ids, topk_w,
-                             logits_out, st);
+                             logits_out, slices, st);
     else
         launch_gate_topk_f32(s, static_cast<const float*>(x), static_cast<const float*>(w_gate), bias, topk_ids, topk_w,
-                             logits_out, st);
+                             logits_out, slices, st);
     return launch_status(who);
 }
 

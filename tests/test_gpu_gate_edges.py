@@ -28,12 +28,18 @@ def gate_case(T, d, E, k, dtype, seed):
 SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260, 17, 3, torch.float32),
          (33, 132, 65, 4, torch.float32), (70, 1024, 130, 8, torch.float32), (40, 516, 256, 8, torch.float32),
          (1, 8, 2, 2, torch.bfloat16), (31, 264, 33, 5, torch.bfloat16), (50, 1096, 200, 8, torch.bfloat16),
-         (1, 256, 8, 2, torch.bfloat16), (33, 512, 256, 8, torch.bfloat16), (64, 2048, 128, 8, torch.bfloat16)]
+         (1, 256, 8, 2, torch.bfloat16), (33, 512, 256, 8, torch.bfloat16), (64, 2048, 128, 8, torch.bfloat16),
+         # the ends of the range in which the hidden dimension is split over workgroups, and past them
+         (1024, 256, 20, 4, torch.bfloat16), (1025, 256, 20, 4, torch.bfloat16), (2048, 132, 9, 2, torch.float32),
+         (2049, 132, 9, 2, torch.float32), (2050, 264, 33, 2, torch.bfloat16)]
 
 
+@pytest.mark.parametrize("least_ws", [False, True])  # with the least workspace the dimension is never split
 @pytest.mark.parametrize("T,d,E,k,dtype", SIZES)
-def test_gate_topk_edges(T, d, E, k, dtype):
+def test_gate_topk_edges(T, d, E, k, dtype, least_ws):
     s, x, wg, bias, ws, (ids, w, logits) = gate_case(T, d, E, k, dtype, T + d + E)
+    if least_ws:
+        ws = ws[:512 * d] if dtype == torch.bfloat16 and d % 256 == 0 else ws[:0]
     B.moe_gate_topk(s, x, wg, bias, ids, w, logits, ws)
     want = x.double() @ wg.double() + bias.double()
     scale = max(1.0, float(want.abs().max()))
