@@ -31,6 +31,8 @@ CASES = [  # N, E, C, psi, dtype, empty slots
     (8, 5, 3, 8 * 4 * 77, torch.float32, 1),
     (32, 16, 2, 32 * 8 * 64, torch.bfloat16, 3),
     (1, 4, 4, 8 * 9, torch.bfloat16, 0),
+    (2, 70, 70, 2 * 8 * 1025, torch.bfloat16, 5),      # more slots than a wavefront, one piece past a unit
+    (2, 40, 30, 2 * 4 * 40961, torch.float32, 3),      # units of four passes
 ]
 
 
