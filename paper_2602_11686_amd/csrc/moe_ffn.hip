@@ -395,33 +395,39 @@ namespace moe {
 // lane groups start 16 banks apart (4*(BM + 4) mod 64 == 16).
 //
 // Measured on 4096 rows x 1024 x 2816 over 8 skewed experts, against 64x64 tiles on the scalar FMA units with the
-// same operands (us): forward 1 1155 -> 522, forward 2 773 -> 302, dgrad 1 618 -> 336, dgrad 2 1604 -> 598,
-// wgrad 2 658 -> 238, wgrad 1 1041 -> 429 (70 to 110 TFLOP/s).
+// same operands (us): forward 1 1155 -> 525, forward 2 773 -> 303, dgrad 1 618 -> 337, dgrad 2 1604 -> 604,
+// wgrad 2 658 -> 235, wgrad 1 1041 -> 441 (70 to 110 TFLOP/s; addresses formed anew for every piece of every stage
+// cost 3 to 5 % of that).
 template <int BM, int FORM>  // FORM 0: [row][k], k contiguous in memory; 1: [k][row]
 struct F32Tile {
     static constexpr int kK = 16;                               // contraction indices per stage
     static constexpr int kLd = FORM == 0 ? kK + 4 : BM + 4;
     static constexpr int kFloats = FORM == 0 ? BM * kLd : kK * kLd;
     static constexpr int kPieces = BM * kK / 4 / 256;           // 16-byte pieces per thread and stage
-    // rows [r0, r_lim) of the operand; `split`: tile rows from BM/2 on come from base2 (same r0, r_lim)
-    static __device__ __forceinline__ void load(f32x4v (&v)[kPieces], const float* __restrict__ base,
-                                                const float* __restrict__ base2, bool split, int64_t ld, int r0, int r_lim,
-                                                int k0, int k_lim) {
+    // This thread's pieces of a stage: addresses at k = k0 of the operand's rows r0 .. (rows past r_lim: any valid one,
+    // masked at the store) and the k inside the stage.  `split`: tile rows from BM/2 on come from base2.
+    const float* at[kPieces];
+    int kk[kPieces];
+    int64_t step;  // floats from one stage to the next
+    __device__ __forceinline__ void set(const float* base, const float* base2, bool split, int64_t ld, int r0, int r_lim, int k0) {
+        step = FORM == 0 ? kK : kK * ld;
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             const int p = threadIdx.x + i * 256;
             int r = FORM == 0 ? p / (kK / 4) : (p % (BM / 4)) * 4;
-            const int k = k0 + (FORM == 0 ? (p % (kK / 4)) * 4 : p / (BM / 4));
-            const float* b = base;
-            if (split && r >= BM / 2) {
-                r -= BM / 2;
-                b = base2;
-            }
-            r += r0;
-            v[i] = (f32x4v){0.f, 0.f, 0.f, 0.f};
-            // (leading dimensions and extents are multiples of four: a piece is inside or outside as a whole)
-            if (r < r_lim && k < k_lim)
-                v[i] = *reinterpret_cast<const f32x4v*>(b + (FORM == 0 ? (int64_t)r * ld + k : (int64_t)k * ld + r));
+            kk[i] = FORM == 0 ? (p % (kK / 4)) * 4 : p / (BM / 4);
+            const bool second = split && r >= BM / 2;
+            r = min(r0 + r - (second ? BM / 2 : 0), FORM == 0 ? r_lim - 1 : r_lim - 4);
+            at[i] = (second ? base2 : base) + (FORM == 0 ? (int64_t)r * ld + k0 + kk[i] : (int64_t)(k0 + kk[i]) * ld + r);
+        }
+    }
+    // the next stage, of which `left` contraction indices exist; the others read zeros (leading dimensions and extents
+    // are multiples of four: a piece is inside or outside as a whole)
+    __device__ __forceinline__ void load(f32x4v (&v)[kPieces], int left) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            v[i] = *reinterpret_cast<const f32x4v*>(kk[i] < left ? at[i] : reinterpret_cast<const float*>(kZeroRow));
+            at[i] += step;
         }
     }
     static __device__ __forceinline__ void store(float* s, const f32x4v (&v)[kPieces]) {
@@ -489,13 +495,21 @@ __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
 
     const int nk = (kend - kbeg + kK - 1) / kK, total = nk * g.nseg;
     f32x4v ra[TA::kPieces], rb[TB::kPieces];
-    auto gload = [&](int it) {
-        const int sg = it >= nk ? 1 : 0, k0 = kbeg + (it - sg * nk) * kK;
-        const int64_t eoff = RAGK ? 0 : (int64_t)weight_index(g, e) * g.strideB;
-        TA::load(ra, static_cast<const float*>(g.seg[sg].A), nullptr, false, g.lda, m0, m_lim, k0, kend);
-        TB::load(rb, static_cast<const float*>(g.seg[sg].B) + eoff,
-                 DUAL ? static_cast<const float*>(g.seg[sg].B2) + eoff : nullptr, DUAL, g.ldb, n0, g.N, k0, kend);
+    const int64_t eoff = RAGK ? 0 : (int64_t)weight_index(g, e) * g.strideB;
+    TA ta;
+    TB tb;
+    auto segment = [&](int sg) {
+        ta.set(static_cast<const float*>(g.seg[sg].A), nullptr, false, g.lda, m0, m_lim, kbeg);
+        tb.set(static_cast<const float*>(g.seg[sg].B) + eoff, DUAL ? static_cast<const float*>(g.seg[sg].B2) + eoff : nullptr,
+               DUAL, g.ldb, n0, g.N, kbeg);
     };
+    auto gload = [&](int it) {
+        if (it == nk) segment(1);
+        const int left = kend - kbeg - (it >= nk ? it - nk : it) * kK;
+        ta.load(ra, left);
+        tb.load(rb, left);
+    };
+    segment(0);
     if (total > 0) {
         gload(0);
         TA::store(sA[0], ra);
