@@ -465,6 +465,107 @@ __global__ __launch_bounds__(256) void permute_scatter_rows_kernel(const u32x4* 
     }
 }
 
+// ---- 1 to 4 in one launch, for few pairs -----------------------------------------------------
+// Up to kSmallPairs pairs every workgroup sorts all of them by itself in LDS (16 wavefronts, one chunk of 256 pairs
+// each; about what one of the launches above waits for) and then copies its share of the rows; the first one
+// also writes the tables.  What bounds three launches at these sizes is that each waits for the one before, and the
+// host's time to make them (us in a graph, and launched one by one): 64 tokens, top-8 of 128 experts, 2048 wide: 7.6 -> 6.4,
+// 17 -> 11; 512 tokens, top-4 of 64: 9.1 -> 6.5, 17 -> 11.  Past 2^20 pieces of x the copy is what counts and its own
+// kernel the better one (4096 tokens, top-1, 4096 wide: 17.8, 18.4 here).
+constexpr uint32_t kSmallPieces = 1u << 20;
+constexpr int kSmallWaves = 16, kSmallChunk = 256, kSmallPairs = kSmallWaves * kSmallChunk;
+__global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(
+    const int32_t* __restrict__ ids, int R, int E, int k, const u32x4* __restrict__ x, int vecs_per_row, uint32_t pieces,
+    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ row_of_pair,
+    int32_t* __restrict__ pair_of_row, u32x4* __restrict__ x_perm) {
+    __shared__ int32_t next[kSmallWaves * MOE_MAX_EXPERTS];  // [wave][expert]: histogram, then the next row
+    __shared__ int32_t total[MOE_MAX_EXPERTS], off[MOE_MAX_EXPERTS + 1];
+    __shared__ int32_t rows[kSmallPairs];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int e[kSmallChunk / 64];
+#pragma unroll
+    for (int i = 0; i < kSmallChunk / 64; ++i) {
+        const int p = wave * kSmallChunk + i * 64 + lane;
+        e[i] = p < R ? ids[p] : -1;
+    }
+    for (int i = tid; i < kSmallWaves * E; i += kSmallWaves * 64) next[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSmallChunk / 64; ++i)
+        if (e[i] >= 0) atomicAdd(&next[wave * E + e[i]], 1);
+    __syncthreads();
+    if (tid < E) {  // rows of the expert in earlier chunks
+        int32_t run = 0;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) {
+            const int32_t c = next[w * E + tid];
+            next[w * E + tid] = run;
+            run += c;
+        }
+        total[tid] = run;
+    }
+    __syncthreads();
+    if (wave == 0) {  // exclusive scan of the totals: 4 experts per lane, then across the lanes
+        int32_t c[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x4 = lane * 4 + u;
+            c[u] = x4 < E ? total[x4] : 0;
+            sum += c[u];
+        }
+        int32_t incl = sum;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const int32_t o = __shfl_up(incl, dlt, 64);
+            if (lane >= dlt) incl += o;
+        }
+        int32_t run = incl - sum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (lane * 4 + u < E) off[lane * 4 + u] = run;
+            run += c[u];
+        }
+        if (lane == 63) off[E] = run;
+    }
+    __syncthreads();
+    const bool first = blockIdx.x == 0;
+    if (first && tid <= E) {
+        offsets[tid] = off[tid];
+        if (tid < E) counts[tid] = total[tid];
+    }
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int i = 0; i < kSmallChunk / 64; ++i) {
+        const int p = wave * kSmallChunk + i * 64 + lane;
+        const bool live = e[i] >= 0;
+        uint64_t same = __ballot(live);
+        if (!live) same = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint64_t bal = __ballot((e[i] >> b) & 1);
+            same &= ((e[i] >> b) & 1) ? bal : ~bal;
+        }
+        int32_t* mine = next + wave * E + (live ? e[i] : 0);
+        if (live) {
+            const int row = off[e[i]] + *mine + __popcll(same & lt_mask);
+            rows[p] = row;
+            if (first) {
+                row_of_pair[p] = row;
+                pair_of_row[row] = p;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (live && (same >> lane) == 1ull) *mine += __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * blockDim.x + tid; i < pieces; i += gridDim.x * blockDim.x) {
+        const uint32_t t = i / (uint32_t)vecs_per_row, v = i - t * (uint32_t)vecs_per_row;
+        const u32x4 val = __builtin_nontemporal_load(&x[i]);
+        for (int s = 0; s < k; ++s) __builtin_nontemporal_store(val, &x_perm[(size_t)rows[t * k + s] * vecs_per_row + v]);
+    }
+}
+
 // ---- combine: y[t] = sum_s w[t,s] * y_perm[row_of_pair[t*k+s]] ------------------------
 template <class T, int VEC>
 struct VecIO;
@@ -659,6 +760,13 @@ static moe_status permute_launch(const char* who, const moe_shape* s, const void
                                  int32_t* counts, int32_t* offsets, int32_t* row_of_pair, int32_t* pair_of_row,
                                  void* x_perm, int32_t* chunk_hist, hipStream_t st) {
     const int R = s->T * s->k, E = s->E;
+    const int64_t pieces = x_perm ? (int64_t)s->T * (int64_t)((size_t)s->d * el_size(s) / 16) : 0;
+    if (R <= kSmallPairs && pieces <= kSmallPieces) {
+        permute_small_kernel<<<grid_for(pieces, kSmallWaves * 64, 256), kSmallWaves * 64, 0, st>>>(
+            topk_ids, R, E, s->k, static_cast<const u32x4*>(x), (int)((size_t)s->d * el_size(s) / 16), (uint32_t)pieces, counts,
+            offsets, row_of_pair, pair_of_row, static_cast<u32x4*>(x_perm));
+        return launch_status(who);
+    }
     const int nchunks = num_chunks(R);
     const int nblocks = (nchunks + kWavesPerBlock - 1) / kWavesPerBlock;
     const size_t lds = (size_t)kWavesPerBlock * E * sizeof(int32_t);
