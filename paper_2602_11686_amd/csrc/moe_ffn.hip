@@ -558,10 +558,10 @@ __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
 // of the chip idle.  Where the lines lie (us, gg256_kernel -> this; 64 experts of 2048 x 1408 and, with "half the chip
 // idle" in the products that end in d columns, 8 of 4096 x 7168; the products in the order forward 1, forward 2,
 // dgrad 1, dgrad 2):
-//   mean 16, 64 experts: 206 -> 142, 76 -> 69, 105 -> 90, 148 -> 115    8 experts: 264 -> 178, 155 -> 76, 106 -> 101, 298 -> 139
-//   mean 32, 64 experts: 208 -> 157, 79 -> 84 (not taken), 112 -> 98, 155 -> 135
-//   mean 64, 64 experts: 216 -> 179, 84 -> 106, 121 -> 124, 170 -> 189  8 experts: 262 -> 210, 154 -> 107, 107 -> 133, 304 -> 202
-//   mean 128, 64 experts: 229 -> 248, 117 -> 155, 145 -> 176, 237 -> 274 (none taken)
+//   mean 16, 64 experts: 163 -> 133, 77 -> 67, 107 -> 87, 151 -> 125    8 experts: 220 -> 173, 153 -> 75, 107 -> 104, 299 -> 147
+//   mean 32, 64 experts: 166 -> 150, 78 -> 79 (not taken), 113 -> 82, 155 -> 148
+//   mean 64, 64 experts: 181 -> 153, 84 -> 108, 126 -> 124, 173 -> 195  8 experts: 222 -> 209, 153 -> 107, 107 -> 129, 306 -> 205
+//   mean 128, 64 experts: 201 -> 226, 116 -> 164, 146 -> 174, 240 -> 279 (none taken)
 template <int BT, bool DUAL, int EPI>
 static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
     auto go = [&](auto kern, int bm, int n_out, int lds) {
