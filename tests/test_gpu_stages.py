@@ -289,8 +289,8 @@ def test_run_to_run_determinism(case):
 EDGE_COUNTS = [1, 7, 31, 33, 255, 257, 0, 128, 129, 64, 2, 513]
 
 
-# (256, 384): the MFMA-tile kernel; (192, 136): f is no multiple of 64, so the GEMMs with K = f take the plain tiled
-# kernel; (64, 64): one k-stage per tile; (128, 192): two and three k-stages (the pipelined loop runs once at most);
+# (256, 384): the MFMA-tile kernel; (192, 136): f is no multiple of 64, so the GEMMs with K = f end in a partial
+# stage; (64, 64): one k-stage per tile; (128, 192): two and three k-stages (the pipelined loop runs once at most);
 # (320, 264): five k-stages and a last column tile 8 wide
 @pytest.mark.parametrize("d,f", [(256, 384), (192, 136), (64, 64), (128, 192), (320, 264)])
 def test_grouped_ffn_at_tile_edges(d, f):
