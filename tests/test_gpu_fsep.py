@@ -32,7 +32,13 @@ CASES = [  # N, E, C, psi, dtype, empty slots
     (32, 16, 2, 32 * 8 * 64, torch.bfloat16, 3),
     (1, 4, 4, 8 * 9, torch.bfloat16, 0),
     (2, 70, 70, 2 * 8 * 1025, torch.bfloat16, 5),      # more slots than a wavefront, one piece past a unit
-    (2, 40, 30, 2 * 4 * 40961, torch.float32, 3),      # units of four passes
+    (2, 40, 30, 2 * 4 * 40961, torch.float32, 3),      # a chunk's last piece opens a unit
+    (8, 300, 130, 8 * 8 * 3, torch.bfloat16, 9),       # slots listed in five steps, chunks much shorter than a unit
+    # restored expert after expert (at least 2^20 pieces, half as many slots again as experts):
+    (4, 8, 6, 4 * 8 * 10925, torch.bfloat16, 2),       # slots in one mask, chunks longer than a unit
+    (2, 2, 40, 2 * 4 * 8197, torch.float32, 7),        # one piece per thread, listed slots, many copies of an expert
+    (32, 32, 8, 32 * 8 * 131, torch.bfloat16, 5),      # one piece per thread, chunks shorter than a unit
+    (32, 80, 4, 32 * 8 * 257, torch.bfloat16, 1),      # four pieces per thread, chunks shorter than a unit
 ]
 
 
