@@ -470,9 +470,10 @@ __global__ __launch_bounds__(256) void permute_scatter_rows_kernel(const u32x4* 
 // each; about what one of the launches above waits for) and then copies its share of the rows; the first one
 // also writes the tables.  What bounds three launches at these sizes is that each waits for the one before, and the
 // host's time to make them (us in a graph, and launched one by one): 64 tokens, top-8 of 128 experts, 2048 wide: 7.6 -> 6.4,
-// 17 -> 11; 512 tokens, top-4 of 64: 9.1 -> 6.5, 17 -> 11.  Past 2^20 pieces of x the copy is what counts and its own
-// kernel the better one (4096 tokens, top-1, 4096 wide: 17.8, 18.4 here).
-constexpr uint32_t kSmallPieces = 1u << 20;
+// 17 -> 11; 512 tokens, top-4 of 64: 9.1 -> 6.5, 17 -> 11.  Past 2^19 pieces of x the copy is what counts and its own kernel
+// the better one (us, three launches and one; 1024 tokens, top-4 of 16, 4096 wide, just within: 14.4, 13.5; 1000 of 5120:
+// 15.7, 16.3; 1000 of 8192: 21.2, 22.8; 4096 tokens, top-1 of 4, 1536 wide: 10.9, 11.6; of 64 experts 12.0, 10.8).
+constexpr uint32_t kSmallPieces = 1u << 19;
 constexpr int kSmallWaves = 16, kSmallChunk = 256, kSmallPairs = kSmallWaves * kSmallChunk;
 __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(
     const int32_t* __restrict__ ids, int R, int E, int k, const u32x4* __restrict__ x, int vecs_per_row, uint32_t pieces,

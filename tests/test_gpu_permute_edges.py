@@ -1,4 +1,5 @@
-"""moe_permute around the number of pairs up to which one launch does all of it (4096): whole numbers, exact."""
+"""moe_permute around the numbers of pairs (4096) and of 16-byte pieces of x (2^19) up to which one launch does all of it:
+whole numbers, exact."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,9 @@ pytestmark = pytest.mark.gpu
                                            (64, 2048, 128, 8, torch.bfloat16), (255, 136, 3, 1, torch.bfloat16),
                                            (1365, 20, 7, 3, torch.float32), (1366, 20, 7, 3, torch.float32),
                                            (4096, 64, 256, 1, torch.bfloat16), (4097, 64, 256, 1, torch.bfloat16),
-                                           (819, 4, 65, 5, torch.float32), (512, 256, 16, 8, torch.bfloat16)])
+                                           (819, 4, 65, 5, torch.float32), (512, 256, 16, 8, torch.bfloat16),
+                                           (512, 8192, 6, 3, torch.bfloat16), (513, 8192, 6, 3, torch.bfloat16),
+                                           (300, 8192, 70, 2, torch.float32)])
 def test_permute(T, d, E, k, dtype):
     rng = np.random.default_rng(T + E)
     # skewed: low experts are picked more often, some not at all
