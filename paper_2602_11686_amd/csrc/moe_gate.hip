@@ -16,10 +16,17 @@ static inline size_t gate_needed_bytes(const moe_shape* s) { return align_up((si
 // ---- short batches: the hidden dimension split over workgroups --------------------------------------------
 constexpr int kGateF32Tokens = 16, kGateF32Waves = 8;
 static inline int gate_tiles16(int E) { const int n = (E + 15) / 16; return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : n <= 8 ? 8 : 16; }
-// workgroups per token tile: enough for every compute unit, at least 16 values of the hidden dimension per wavefront
+static inline bool gate_packed(const moe_shape* s) { return s->dtype == MOE_BF16 && s->d % 256 == 0; }
+// Workgroups per token tile: enough for every compute unit, at least 16 values of the hidden dimension per wavefront.  With
+// more than 128 experts a workgroup's partial sums (128 KB) leave no room for a second one on its unit, and the few past
+// 256 would make a second round (us, whole, rounded up, down; 900 tokens of 4096 x 256: 108, 139, 101; 700 of 8192 x 256:
+// 202, 259, 168).  From 33 experts on that costs more than it gives too, where the slices come out even (960 of
+// 4096 x 64: 27, 28, 24), but not where they do not (900 of 2056 x 128: 27 and 30, 666 whole; 2000 of 4104 x 8: 20 and 26).
 static inline int gate_splits(const moe_shape* s) {
     const int tiles = (s->T + kGateF32Tokens - 1) / kGateF32Tokens;
-    const int want = (256 + tiles - 1) / tiles, most = (s->d + 16 * kGateF32Waves - 1) / (16 * kGateF32Waves);
+    const bool one_round = s->E > 128 || (s->E > 32 && gate_packed(s));
+    const int want = one_round ? (tiles < 256 ? 256 / tiles : 1) : (256 + tiles - 1) / tiles;
+    const int most = (s->d + 16 * kGateF32Waves - 1) / (16 * kGateF32Waves);
     const int n = want < most ? want : most;
     return n < 32 ? n : 32;
 }
@@ -27,7 +34,6 @@ static inline int gate_splits(const moe_shape* s) {
 // however few tiles there are (bf16, 8 .. 1024 tokens of 2048 x 64 experts: 15-18 us with the packing of the weight,
 // 7-15 us split; of 4096 x 128: 59-64 and 12-45).  At 2048 tokens the packed bf16 kernel is the faster one again
 // (18 and 23; 64 and 87), the fp32 one is not (of 2048 x 128: 38 us whole, 26 split).
-static inline bool gate_packed(const moe_shape* s) { return s->dtype == MOE_BF16 && s->d % 256 == 0; }
 static inline size_t gate_split_bytes(const moe_shape* s) {
     return s->T <= (gate_packed(s) ? 1024 : 2048) && gate_splits(s) > 1 ? (size_t)gate_splits(s) * s->T * gate_tiles16(s->E) * 16 * sizeof(float) : 0;
 }

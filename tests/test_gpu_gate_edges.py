@@ -31,7 +31,8 @@ SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260,
          (1, 256, 8, 2, torch.bfloat16), (33, 512, 256, 8, torch.bfloat16), (64, 2048, 128, 8, torch.bfloat16),
          # the ends of the range in which the hidden dimension is split over workgroups, and past them
          (1024, 256, 20, 4, torch.bfloat16), (1025, 256, 20, 4, torch.bfloat16), (2048, 132, 9, 2, torch.float32),
-         (2049, 132, 9, 2, torch.float32), (2050, 264, 33, 2, torch.bfloat16)]
+         (2049, 132, 9, 2, torch.float32), (2050, 264, 33, 2, torch.bfloat16),
+         (905, 768, 200, 8, torch.bfloat16), (2000, 264, 129, 2, torch.float32)]  # 57 and 125 token tiles: no even split of 256
 
 
 @pytest.mark.parametrize("least_ws", [False, True])  # with the least workspace the dimension is never split
