@@ -453,14 +453,22 @@ static inline int mma_chunks(int Tn) { const int c = mma_chunk_tokens(Tn); retur
 static inline int pad64(int v) { return (v + 63) / 64 * 64; }  // the dense dL is a K operand: whole 64-wide k-stages
 
 // one wavefront per token: dl[t,s] (fp32, for the dx update) and the dense rows, dl[t,s] = w_s (dw_s - sum_j w_j dw_j);
-// D = bf16_t: hi and lo, D = float: hi is the value itself
+// D = bf16_t: hi and lo, D = float: hi is the value itself.  It also writes the constants of the products after it: the
+// chunks' token ranges, a row of zeros, and the token range as a single group (in a launch of their own 1.4 us of the 11
+// that one fp32 token takes).
 template <class D>
 __global__ __launch_bounds__(256) void gate_dl_dense_kernel(const int32_t* __restrict__ ids, const float* __restrict__ w,
                                                             const float* __restrict__ dw, float* __restrict__ dl,
                                                             D* __restrict__ hi, D* __restrict__ lo, int Tn,
-                                                            int k, int n_pad) {
+                                                            int k, int n_pad, int32_t* __restrict__ chunk_off, int nchunks,
+                                                            int chunk_tokens, uint32_t* __restrict__ zero_row,
+                                                            int32_t* __restrict__ whole) {
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int i = blockIdx.x * 256 + threadIdx.x;  // (at least 256 threads, and 64 for every chunk)
+    if (i < 128) zero_row[i] = 0u;
+    if (i < 2) whole[i] = i * Tn;
+    if (i <= nchunks) chunk_off[i] = (int)min((int64_t)i * chunk_tokens, (int64_t)Tn);
     if (t >= Tn) return;
     float dot = 0.f;
     for (int s = 0; s < k; ++s) dot += w[(size_t)t * k + s] * dw[(size_t)t * k + s];
@@ -477,17 +485,6 @@ __global__ __launch_bounds__(256) void gate_dl_dense_kernel(const int32_t* __res
             hi[(size_t)t * n_pad + e] = v;
         }
     }
-}
-
-__global__ void gate_chunk_offsets_kernel(int32_t* __restrict__ off, int nchunks, int chunk_tokens, int Tn,
-                                          uint32_t* __restrict__ zero_row, int32_t* __restrict__ whole) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 128) zero_row[i] = 0u;
-    if (i == 0) {  // the token range as a single group
-        whole[0] = 0;
-        whole[1] = Tn;
-    }
-    if (i <= nchunks) off[i] = (int)min((int64_t)i * chunk_tokens, (int64_t)Tn);
 }
 
 // wg_pad[c][j] = w_gate[c][j] for j < E, zero up to n_pad: the gate weight as a [N][K] operand with whole k-stages
@@ -605,9 +602,8 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     int32_t* coff = static_cast<int32_t*>(cv.take((size_t)(nch + 1) * 4));
     uint32_t* zero_row = static_cast<uint32_t*>(cv.take(512));
     int32_t* whole = static_cast<int32_t*>(cv.take(256));
-    gate_dl_dense_kernel<T><<<(s->T + 3) / 4, 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad);
-    gate_chunk_offsets_kernel<<<(nch + 256) / 256, 256, 0, st>>>(coff, nch, f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s->T),
-                                                                 s->T, zero_row, whole);
+    gate_dl_dense_kernel<T><<<(s->T + 3) / 4, 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch,
+                                                            f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s->T), zero_row, whole);
     if (dx && !f32 && s->k >= 4) {
         // dx += dL * W_g^T as a GEMM over the dense (hi + lo) dL: reads and writes dx once; the gate
         // weight stays in bf16 (padded to whole k-stages in the space of the fp32 transpose).  The

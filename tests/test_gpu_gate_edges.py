@@ -68,7 +68,8 @@ def test_gate_topk_with_nan_and_equal_logits(d, dtype):
 
 
 @pytest.mark.parametrize("T,d,E,k,dtype", [(1, 36, 5, 2, torch.float32), (33, 68, 65, 3, torch.float32),
-                                           (700, 128, 8, 2, torch.float32), (300, 1028, 256, 8, torch.float32)])
+                                           (700, 128, 8, 2, torch.float32), (300, 1028, 256, 8, torch.float32),
+                                           (9000, 68, 3, 2, torch.float32)])  # more chunks of tokens than a workgroup has threads
 def test_gate_bwd_edges(T, d, E, k, dtype):
     s, x, wg, bias, ws, (ids, w, logits) = gate_case(T, d, E, k, dtype, 3 * T + E)
     B.moe_gate_topk(s, x, wg, bias, ids, w, None, ws)
