@@ -162,9 +162,12 @@ struct TileDesc {
 //
 // KREST (ragged M): K is no multiple of 64.  An instance of its own, because the test of the last stage in the
 // main loop's issue side costs 1.6 % where no stage is partial.
-template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool KREST = false>
+//
+// STREAM (ragged K): C is stored non-temporally.  (An instance of its own too: of two stores behind a test at run time
+// the compiler makes one plain store.)
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool KREST = false, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
-    static_assert(RAGK ? (AT == 1 && BT == 0 && !KREST) : (AT == 0), "operand forms");
+    static_assert(RAGK ? (AT == 1 && BT == 0 && !KREST) : (AT == 0 && !STREAM), "operand forms");
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kTableOff);  // [E+1] rows of each expert
@@ -576,8 +579,9 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                         float* d = static_cast<float*>(g.C0) + cbase + (int64_t)row * g.ldc + t.n0 + col;
                         for (int z = 0; z < 8; ++z) d[z] = 0.f;
                     } else {
-                        __builtin_nontemporal_store((u32x4){0, 0, 0, 0},
-                                                    reinterpret_cast<u32x4*>(dst + cbase + (int64_t)row * g.ldc + t.n0 + col));
+                        u32x4* to = reinterpret_cast<u32x4*>(dst + cbase + (int64_t)row * g.ldc + t.n0 + col);
+                        if constexpr (STREAM) __builtin_nontemporal_store((u32x4){0, 0, 0, 0}, to);
+                        else *to = (u32x4){0, 0, 0, 0};
                     }
                 }
             }
@@ -798,11 +802,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                     const uint32_t off = (uint32_t)trow * ldc_u + (uint32_t)col;
                     if (t.m0 + trow < t.m_lim && t.n0 + col < g.N) {
                         u32x4* to = reinterpret_cast<u32x4*>(dst + tile_base + off);
-                        // Weight gradients are large and nothing reads them soon: plain stores leave the memory-side
-                        // cache full of dirty lines, which the kernels after this one pay for.  64 experts of
-                        // 2048 x 1408, mean 16 rows: both gradients 263 -> 226 us; mean 64: 313 -> 294 us and the
-                        // next pass' forward products 299 -> 234 us.
-                        if constexpr (RAGK) __builtin_nontemporal_store(v[u], to);
+                        if constexpr (STREAM) __builtin_nontemporal_store(v[u], to);
                         else *to = v[u];
                     }
                 }

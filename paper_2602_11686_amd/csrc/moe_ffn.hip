@@ -588,6 +588,18 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
     return false;
 }
 
+// Whether the weight gradients are stored non-temporally.  Plain stores leave the memory-side cache full of their dirty
+// lines, which the kernels after them pay for, and where the products are bound by their output (few rows per
+// group) they pay for it themselves.  us, plain and non-temporal, both gradients alone, with the exchange that reads them
+// next (reshard of one device's experts), and with the next forward products:
+//   64 groups of 2048 x 1408, mean 128 rows: 732, 679; 1106, 1056; 990, 938     mean 512: 1338, 1334; 1722, 1707; 1944, 1898
+//   16 of 4096 x 2048, mean 1024: 1572, 1532; 1840, 1813; 2319, 2257            32 of 1024 x 512, 256: 120, 113; 148, 148; 174, 160
+//   16 of 1024 x 1408, mean 512 (138 MB, within the cache): 229, 219; 264, 267; 340, 328
+// (the backward call as a whole).  With many rows the matrix cores are the bound and the stores make no difference there (8
+// groups of 4096 x 14336, mean 4096: 18939, 18920), but after non-temporal ones the update of dx by moe_gate_topk_bwd
+// takes 67 us, after plain ones 46.
+static bool stream_gradients(int64_t R, int groups) { return R <= 2048 * (int64_t)groups; }
+
 // A(m,k) layout AT, B(k,n) layout BT as in the bf16 kernel.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t st) {
@@ -605,6 +617,8 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
                 auto kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK>;
                 if constexpr (!RAGK)
                     if (g.K % TK) kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK, true>;
+                if constexpr (RAGK)
+                    if (stream_gradients(R, g.E)) kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK, false, true>;
                 ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGemmLds);
                 kern<<<dim3(256), kThreads, kGemmLds, st>>>(g);  // persistent: one workgroup per CU
                 return;

@@ -94,3 +94,9 @@ def test_ffn_bf16_k_remainder(counts, d, f):
                                         ((60,) * 40, 512, 1024), ((20,) * 30 + (300, 0), 1024, 520)])
 def test_ffn_few_rows(counts, d, f):
     check_ffn(counts, d, f, torch.bfloat16, 13 * d + f)
+
+
+# more than 2048 rows per expert on average: the weight gradients go through the instances with plain stores
+@pytest.mark.parametrize("counts,d,f", [((6200, 0, 1), 136, 72), ((4100, 300), 264, 520)])
+def test_ffn_many_rows(counts, d, f):
+    check_ffn(counts, d, f, torch.bfloat16, 17 * d + f)

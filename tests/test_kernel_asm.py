@@ -79,7 +79,8 @@ def test_look_ahead_draw_is_first_read_behind_a_full_wait(ffn_asm):
     asynchronously.  The only reader of the destination register must be the LDS store that publishes it, and
     that store must follow an s_waitcnt vmcnt(0) in its own straight-line code."""
     found = 0
-    for m in re.finditer(r"^(_ZN3moe12gg256_kernel\w+Lb1EEEvNS_5GArgsE):(.*?)\n\s*s_endpgm", ffn_asm, re.S | re.M):
+    # (template arguments AT, BT, DUAL, EPI, RAGK, ...: the ones with ragged K)
+    for m in re.finditer(r"^(_ZN3moe12gg256_kernelILi\dELi\dELb[01]ELi\dELb1E\w+):(.*?)\n\s*s_endpgm", ffn_asm, re.S | re.M):
         lines = [l.strip() for l in m.group(2).split("\n")]
         lines = [l for l in lines if l and not l.startswith(";") and (not l.startswith(".") or l.startswith(".LBB"))]
         for n, l in enumerate(lines):
@@ -106,7 +107,7 @@ def test_look_ahead_draw_is_first_read_behind_a_full_wait(ffn_asm):
                 # the wait may sit in the block in front of the predicated store: look through one label
                 window = straight if any("vmcnt(0)" in y for y in straight) else back
                 assert any(y.startswith("s_waitcnt") and "vmcnt(0)" in y for y in window), (m.group(1), x)
-    assert found >= 2   # the two weight-gradient kernels draw their tiles
+    assert found >= 4   # the two weight-gradient products draw their tiles, with plain and with non-temporal stores
 
 
 def test_kernels_do_not_spill(ffn_asm):
