@@ -1,6 +1,6 @@
-"""Host-side check of the generated code of the persistent grouped-GEMM kernel (no GPU needed).
+"""Host-side check of the generated code of the grouped-GEMM kernels fed by LDS DMA (no GPU needed).
 
-The kernel orders its LDS DMA loads with hand-placed ``s_waitcnt vmcnt(N)`` in inline assembly, which the
+The kernels order their LDS DMA loads with hand-placed ``s_waitcnt vmcnt(N)`` in inline assembly, which the
 compiler does not see.  If the compiler believes that an ordinary global load is still pending when the
 main loop starts (an epilogue load that some path leaves unconsumed, say), it adds waits of its own inside
 the loop; they wait for the DMA loads too and cost 15-20 % of the kernel, silently.  So: compile the
@@ -28,11 +28,11 @@ def ffn_asm(tmp_path_factory):
     return out.read_text()
 
 
-def kernels(asm):
-    """{mangled kernel name: [(block label, [instructions])]} for the gg256 kernels."""
+def kernels(asm, which):
+    """{mangled kernel name: [(block label, [instructions])]} for the instances of a kernel."""
     out, kern, label, cur = {}, None, None, []
     for line in asm.split("\n"):
-        m = re.match(r"^(_ZN3moe12gg256_kernel\w+):", line)
+        m = re.match(r"^(_ZN3moe\d+%s\w+):" % which, line)
         if m:
             kern, label, cur = m.group(1), "entry", []
             out[kern] = [(label, cur)]
@@ -54,7 +54,7 @@ def kernels(asm):
 
 
 def test_main_loops_hold_only_the_hand_placed_vmcnt_waits(ffn_asm):
-    ks = kernels(ffn_asm)
+    ks = kernels(ffn_asm, "gg256_kernel")
     assert len(ks) >= 6, sorted(ks)
     seen_loops = 0
     for name, blocks in ks.items():
@@ -72,6 +72,33 @@ def test_main_loops_hold_only_the_hand_placed_vmcnt_waits(ffn_asm):
             between = [i for i in ins[waits[0][0] + 1:bar] if i.startswith(("ds_read", "global_load", "buffer_load"))]
             assert 0 < bar - waits[0][0] and not between, f"{name} {label}: the wait is not the one in front of the barrier"
     assert seen_loops >= len(ks)
+
+
+def test_few_rows_pipeline_holds_only_the_hand_placed_vmcnt_waits(ffn_asm):
+    """gg_few_rows_kernel keeps S-2 stages of DMA in flight behind ``vmcnt((S-2)*(CA+CB))``: between its first DMA load
+    and its last MFMA the compiler adds no vmcnt wait, the written ones are that and 0, and each stands in front of a
+    barrier that holds the kernel's only DMA requests back."""
+    found = 0
+    for m in re.finditer(r"^_ZN3moe18gg_few_rows_kernelILi[01]ELb[01]ELi\dELi(\d+)ELi(\d)ELi(\d)E\w+:(.*?)\n\s*s_endpgm",
+                         ffn_asm, re.S | re.M):
+        bm, nb, stages = (int(m.group(i)) for i in (1, 2, 3))
+        lines = [l.strip() for l in m.group(4).split("\n")]
+        dma = [n for n, l in enumerate(lines) if l.startswith("global_load_lds")]
+        mfma = [n for n, l in enumerate(lines) if l.startswith("v_mfma")]
+        assert dma and mfma, m.group(0)[:80]
+        by_hand, waits = False, []
+        for n in range(dma[0], mfma[-1]):
+            if lines[n].startswith(";;#ASM"):
+                by_hand = lines[n].startswith(";;#ASMSTART")
+            elif lines[n].startswith("s_waitcnt") and "vmcnt" in lines[n]:
+                assert by_hand, (m.group(0)[:80], n, lines[n])
+                waits.append((n, int(re.search(r"vmcnt\((\d+)\)", lines[n]).group(1))))
+        assert sorted({w for _, w in waits}) == sorted({0, (stages - 2) * (bm // 32 + 2 * nb)}), (m.group(0)[:80], waits)
+        bar = next(n for n, l in enumerate(lines) if l.startswith("s_barrier"))
+        assert max(n for n, _ in waits) < bar < mfma[0], (m.group(0)[:80], waits, bar)
+        assert not any(waits[0][0] < n < bar for n in dma), m.group(0)[:80]
+        found += 1
+    assert found >= 8   # the instances that are launched: 2 forward 1, 2 forward 2, 2 of each of three dgrad epilogues
 
 
 def test_look_ahead_draw_is_first_read_behind_a_full_wait(ffn_asm):
@@ -111,7 +138,7 @@ def test_look_ahead_draw_is_first_read_behind_a_full_wait(ffn_asm):
 
 
 def test_kernels_do_not_spill(ffn_asm):
-    for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe12gg256_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
+    for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe\d+gg(?:256|_few_rows)_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
         body = m.group(2)
         scratch = re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", body)
         assert scratch and int(scratch.group(1)) == 0, (m.group(1), scratch and scratch.group(1))
