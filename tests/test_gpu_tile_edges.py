@@ -1,8 +1,8 @@
 """The expert FFN calls at the sizes where a tile, a remainder or a dispatch rule can go wrong, against the oracle.
 
 Tolerances (largest difference over the largest reference value, per tensor and per expert): bf16 as in the other
-stage tests; fp32 2^-24 per rounded sum times the longest contraction here (2048 terms, worst case 1.2e-4) is covered
-by their 1e-4 because the errors of a sum partly cancel.
+stage tests; fp32 2^-24 per rounded sum times the longest contraction here (4096 terms: dX sums two segments of 2048;
+worst case 2.4e-4) is covered by their 1e-4 because the errors of a sum partly cancel.
 """
 import numpy as np
 import pytest
@@ -18,7 +18,7 @@ from helpers import rel_max, rel_max_blocks, row_blocks
 pytestmark = pytest.mark.gpu
 
 
-def check_ffn(counts, d, f, dtype, seed, backward=True):
+def check_ffn(counts, d, f, dtype, seed, backward=True, wstd=0.05):
     rng = np.random.default_rng(seed)
     counts = np.array(counts, np.int32)
     E, R = len(counts), int(counts.sum())
@@ -33,7 +33,7 @@ def check_ffn(counts, d, f, dtype, seed, backward=True):
         return torch.from_numpy(b.view(np.int16)).cuda().view(torch.bfloat16), I.widen(b, np.float64)
 
     (xp, xp_o), (dyp, dyp_o) = values(R, d), values(R, d)
-    (w1, w1_o), (w3, w3_o), (w2, w2_o) = values(E, d, f, std=0.05), values(E, d, f, std=0.05), values(E, f, d, std=0.05)
+    (w1, w1_o), (w3, w3_o), (w2, w2_o) = (values(*n, std=wstd) for n in ((E, d, f), (E, d, f), (E, f, d)))
     yp, A, Bm, H = O.ffn_fwd(xp_o, offsets, w1_o, w3_o, w2_o)
     s = B.Shape(R, d, f, E, 1, dtype)     # T*k = R with k = 1: the shape only sizes the buffers of these calls
     buf = MoeLayerBuffers(s, backward=True)
@@ -72,11 +72,27 @@ def check_ffn(counts, d, f, dtype, seed, backward=True):
         assert not buf.dw1[e].any() and not buf.dw3[e].any() and not buf.dw2[e].any()
 
 
-# fp32: 64x64 tiles (few tiles) and 128x128 tiles (the 2048-wide ones), remainders of rows, columns and k-stages
+# fp32, 64x64 tiles (fewer than 512 of 128x128 in every product): remainders of rows, columns and k-stages
 @pytest.mark.parametrize("counts,d,f", [((1, 0, 63, 64, 65, 130), 68, 36), ((5, 17), 4, 132), ((0, 129, 300), 64, 16),
                                         ((1200, 127, 0, 1), 2048, 260), ((700, 900), 260, 2048)])
 def test_ffn_f32(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 7 * d + f)
+
+
+# fp32, 128x128 tiles: at least 512 of them in every product (an upper bound with ragged rows, as the dispatch counts them)
+def test_ffn_f32_large_tiles():
+    counts, d, f = (0, 1, 127, 128, 129, 300, 17, 64) * 25, 260, 264
+    up = lambda n, m: -(-n // m)
+    rows = sum(counts) // 128 + len(counts)
+    tiles = [up(f, 64) * rows, up(d, 128) * rows, up(f, 128) * rows, up(d, 128) * up(f, 128) * len(counts)]
+    assert min(tiles) >= 512
+    check_ffn(counts, d, f, torch.float32, 3)
+
+
+# bf16 leading dimensions beyond the 32-bit offsets of the tile kernels: the plain 128x128x64 kernel
+@pytest.mark.parametrize("counts,d,f,wstd", [((3, 2), 1 << 21, 8, 7e-4), ((5,), 8, 1 << 21, 0.05)])
+def test_ffn_bf16_huge_leading_dimension(counts, d, f, wstd):
+    check_ffn(counts, d, f, torch.bfloat16, 23, wstd=wstd)
 
 
 # bf16 contractions that end inside a 64-wide stage: one piece, one piece short of a stage, several stages and a rest

@@ -1,8 +1,9 @@
 """moe_permute_static (the entry point that allocates nothing) against moe_permute, through the C ABI.
 
 Two calls in a row on one GPU, the second with a smaller input: the static scratch array keeps the first
-call's contents, so the second call must not depend on them.  Integer outputs and copied rows are compared
-bit for bit with moe_permute (which the other GPU tests compare with the oracle) and with the oracle itself.
+call's contents, so the second call must not depend on them.  (Up to 4096 pairs the call needs no scratch.)
+Integer outputs and copied rows are compared bit for bit with moe_permute (which the other GPU tests compare with
+the oracle) and with the oracle itself.
 """
 import numpy as np
 import pytest
@@ -62,9 +63,11 @@ def run_both(T, d, E, k, dtype, seed):
 def test_two_calls_in_a_row_the_second_smaller():
     print("[no-alloc] call 1: T=4096 k=4 E=64 bf16", flush=True)
     run_both(4096, 256, 64, 4, torch.bfloat16, seed=11)
-    print("[no-alloc] call 2: T=333 k=2 E=6 f32", flush=True)
+    print("[no-alloc] call 2: T=2777 k=2 E=6 f32", flush=True)
+    run_both(2777, 64, 6, 2, torch.float32, seed=14)
+    print("[no-alloc] call 3: T=333 k=2 E=6 f32", flush=True)
     run_both(333, 64, 6, 2, torch.float32, seed=12)
-    print("[no-alloc] call 3: T=1 k=1 E=2", flush=True)
+    print("[no-alloc] call 4: T=1 k=1 E=2", flush=True)
     run_both(1, 8, 2, 1, torch.float32, seed=13)
 
 
