@@ -4,10 +4,15 @@
 //
 // What bounds it is how fast the weights arrive from HBM, so the tile is chosen for loads in flight: a workgroup
 // of four wavefronts owns BM rows x 64 columns (per B matrix, or two column blocks of 64: NB = 2) and streams its B
-// columns in 64-wide k-stages through a ring of S LDS buffers, filled by DMA S-1 stages ahead.  Two or three
-// workgroups share a compute unit, which keeps 50 to 100 KB of weights in flight per unit (gg256_kernel:
-// one stage of 32 KB), and the number of tiles is several times the number of units where gg256_kernel has too few
-// 256-wide ones.  Every B request takes whole 128-byte lines.
+// columns in 64-wide k-stages through a ring of S LDS buffers, filled by DMA S-1 stages ahead, and the number of tiles is
+// several times the number of units where gg256_kernel has too few 256-wide ones.  Every B request takes whole 128-byte
+// lines.  Workgroups per unit and weights in flight on it (gg256_kernel: one stage of 32 KB), by instance <BM, NB, S>:
+//   <64,2,3> 2, 64 KB    <64,1,3> 3, 48 KB    <128,2,2> 2, 32 KB    <128,1,3> 2, 32 KB    <128,2,3> 1, 32 KB
+// Weights are requested non-temporally where one row tile uses them.  An expert's second row tile runs beside the first
+// on the same XCD, but finds such lines in its L2 only in part (bytes fetched past L2 over the weights' own: 96 rows in
+// tiles of 64 1.6, 200 rows in tiles of 128 2.0): with several row tiles the requests are plain (us, W1|W3 and both dgrads;
+// 2048 rows over 64 experts of 2048 x 1408, Zipf-skewed: 165 -> 150, 240 -> 218; 4096 rows on 16 of 128 experts of
+// 2048 x 768: 80 -> 67, 148 -> 115).  Two loops, because the test inside one costs 64 tokens of 128 experts 1 %.
 //
 // LDS: row form (K contiguous; A, and B in the dgrad products) as [64 or BM rows][128 B], read with ds_read_b128;
 // k-row form (N contiguous; B forward) as [64 k-rows][128 B], read with the transposing ds_read_b64_tr_b16.  The
@@ -48,7 +53,7 @@ __global__ __launch_bounds__(kFewThreads) void gg_few_rows_kernel(const GArgs g)
     const int n_out = DUAL ? 64 : 64 * NB;
     const int n_tiles = (g.N + n_out - 1) / n_out;
     // chunks of eight consecutive tiles go to the XCDs in turn (the grid is a multiple of 64); the row tiles of
-    // one column tile are consecutive, so an expert's second row tile finds the weights in the XCD's L2
+    // one column tile are consecutive
     const int L = (((int)(blockIdx.x >> 6) * 8 + (int)(blockIdx.x & 7)) << 3) + (int)((blockIdx.x >> 3) & 7);
     int e, m0, m_lim, local;
     if (!find_tile<BM>(g, L, n_tiles, e, m0, m_lim, local)) return;
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(kFewThreads) void gg_few_rows_kernel(const GArgs g)
         }
     }
     const int b_mat = DUAL ? wave >> 1 : 0;  // (CB = 4 chunks per wavefront: half h = wave/2)
-    auto issue = [&](int stage, int buf) {
+    auto issue = [&](auto stream, int stage, int buf) {
         const int sg = stage >= nk ? 1 : 0, k0 = (stage - sg * nk) * 64, left = g.K - k0;
         const uint32_t st = lds_base + buf * kStage;
         const char* Ab = static_cast<const char*>(g.seg[sg].A) + (int64_t)k0 * 2;
@@ -92,8 +97,11 @@ __global__ __launch_bounds__(kFewThreads) void gg_few_rows_kernel(const GArgs g)
         for (int i = 0; i < CA; ++i)
             dma16(a_k[i] < left ? Ab + a_off[i] : zeros, st + (wave * CA + i) * 1024);
 #pragma unroll
-        for (int i = 0; i < CB; ++i)
-            dma16_stream(b_k[i] < left ? Bb + b_off[i] : zeros, st + kABytes + (wave * CB + i) * 1024);
+        for (int i = 0; i < CB; ++i) {
+            const void* from = b_k[i] < left ? Bb + b_off[i] : zeros;
+            if constexpr (decltype(stream)::value) dma16_stream(from, st + kABytes + (wave * CB + i) * 1024);
+            else dma16(from, st + kABytes + (wave * CB + i) * 1024);
+        }
     };
 
     // ---- compute side ----
@@ -134,19 +142,23 @@ __global__ __launch_bounds__(kFewThreads) void gg_few_rows_kernel(const GArgs g)
             }
         }
     };
-    for (int s = 0; s < S - 1 && s < total; ++s) issue(s, s);
-    int cur = 0, fill = S - 1;  // ring positions of the stage computed and of the one requested next
-    for (int it = 0; it < total; ++it) {
-        // stage `it` has landed (behind it up to S-2 stages are in flight) and this wavefront's LDS reads of the buffer
-        // that is refilled below have returned; the barrier says so for all wavefronts
-        if (it + S - 1 <= total) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * (CA + CB)) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (it + S - 1 < total) issue(it + S - 1, fill);
-        compute(cur);
-        cur = cur + 1 == S ? 0 : cur + 1;
-        fill = fill + 1 == S ? 0 : fill + 1;
-    }
+    auto run = [&](auto stream) {
+        for (int s = 0; s < S - 1 && s < total; ++s) issue(stream, s, s);
+        int cur = 0, fill = S - 1;  // ring positions of the stage computed and of the one requested next
+        for (int it = 0; it < total; ++it) {
+            // stage `it` has landed (behind it up to S-2 stages are in flight) and this wavefront's LDS reads of the buffer
+            // that is refilled below have returned; the barrier says so for all wavefronts
+            if (it + S - 1 <= total) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * (CA + CB)) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (it + S - 1 < total) issue(stream, it + S - 1, fill);
+            compute(cur);
+            cur = cur + 1 == S ? 0 : cur + 1;
+            fill = fill + 1 == S ? 0 : fill + 1;
+        }
+    };
+    if (m_tiles == 1) run(IntTag<1>{});
+    else run(IntTag<0>{});
 
     // ---- epilogue: four consecutive columns of one row per lane, stored directly ----
 #pragma unroll
