@@ -461,7 +461,9 @@ __global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
     const int n_tiles = (g.N + n_out - 1) / n_out;
 
     // ---- which tile: chunks of eight neighbouring tiles go to the XCDs in turn (the grid is a multiple of 64) ----
-    const int L = (((int)(blockIdx.x >> 6) * 8 + (int)(blockIdx.x & 7)) << 3) + (int)((blockIdx.x >> 3) & 7);
+    // (a second grid dimension where one cannot hold the tiles: f32_grid)
+    const int b0 = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int L = (((b0 >> 6) * 8 + (b0 & 7)) << 3) + ((b0 >> 3) & 7);
     int e, m0, m_lim, kbeg, kend, m, nt;
     if constexpr (RAGK) {
         const int m_tiles = (g.M + BM - 1) / BM, per = m_tiles * n_tiles;
@@ -605,6 +607,13 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
 // takes 67 us, after plain ones 46.
 static bool stream_gradients(int64_t R, int groups) { return R <= 2048 * (int64_t)groups; }
 
+// workgroups of 256 threads for that many tiles, a multiple of 64 of them; a dimension holds fewer than 2^32 threads
+static dim3 f32_grid(int64_t tiles) {
+    constexpr int64_t kMost = 1 << 23;
+    const int64_t blocks = (tiles + 63) / 64 * 64;
+    return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
+}
+
 // A(m,k) layout AT, B(k,n) layout BT as in the bf16 kernel.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t st) {
@@ -641,7 +650,7 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             return n * (RAGK ? (g.M + bm - 1) / bm * g.E : (R + bm - 1) / bm + g.E);  // (upper bound with ragged M)
         };
         const bool small = tiles(128) < 512;
-        const unsigned grid = (unsigned)((tiles(small ? 64 : 128) + 63) / 64 * 64);
+        const dim3 grid = f32_grid(tiles(small ? 64 : 128));
         if (small) gg_f32_kernel<AT, BT, DUAL, EPI, RAGK, 64><<<grid, 256, 0, st>>>(g);
         else gg_f32_kernel<AT, BT, DUAL, EPI, RAGK, 128><<<grid, 256, 0, st>>>(g);
     }

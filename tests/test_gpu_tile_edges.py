@@ -116,3 +116,21 @@ def test_ffn_few_rows(counts, d, f):
 @pytest.mark.parametrize("counts,d,f", [((6200, 0, 1), 136, 72), ((4100, 300), 264, 520)])
 def test_ffn_many_rows(counts, d, f):
     check_ffn(counts, d, f, torch.bfloat16, 17 * d + f)
+
+
+def test_ffn_f32_more_tiles_than_a_grid_dimension():
+    """256 experts of 4 x 2^22: 16.8 million tiles in the first product.  w1, w3 and w2 share 17 GB.  fp32 sums of 2^22
+    terms: 2^-24 of the sum of absolute values per addition, which partly cancel; 1e-4 of it is 1678 of them."""
+    E, d, f, experts = 256, 4, 1 << 22, (3, 137, 255)
+    w = torch.empty(E, d, f, device="cuda").normal_(0.0, 0.5, generator=torch.Generator(device="cuda").manual_seed(1))
+    x = torch.tensor([[0.5, -1.0, 2.0, 0.25], [1.5, 0.75, -0.5, 1.0], [-0.25, 1.0, 1.0, -2.0]], device="cuda")
+    offsets = torch.tensor([sum(e < i for e in experts) for i in range(E + 1)], dtype=torch.int32, device="cuda")
+    s = B.Shape(3, d, f, E, 1, torch.float32)
+    y = torch.full((3, d), float("nan"), device="cuda")
+    ws = torch.full((3 * f,), float("nan"), device="cuda").view(torch.uint8)
+    B.moe_grouped_ffn_fwd(s, x, offsets, w, w, w.view(E, f, d), y, None, None, ws)
+    for r, e in enumerate(experts):
+        a = x[r].double() @ w[e].double()
+        h = torch.nn.functional.silu(a) * a
+        w2 = w.view(E, f, d)[e].double()
+        assert float(((y[r].double() - h @ w2).abs() / (h.abs() @ w2.abs())).max()) <= 1e-4, e
