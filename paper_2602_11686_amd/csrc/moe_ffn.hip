@@ -677,8 +677,8 @@ void launch_gate_dwg_gemm_f32(const void* x, const void* dl, const int32_t* chun
     g.seg[0] = {x, dl, nullptr};
     g.lda = d; g.ldb = n_pad; g.strideC = (int64_t)d * n_pad;
     g.C0 = partial; g.ldc = n_pad;
-    const int tiles = (n_pad + 63) / 64 * ((d + 63) / 64) * nchunks;
-    gg_f32_kernel<1, 0, false, EPI_STORE, true, 64><<<(tiles + 63) / 64 * 64, 256, 0, st>>>(g);
+    const int64_t tiles = (int64_t)((n_pad + 63) / 64) * ((d + 63) / 64) * nchunks;
+    gg_f32_kernel<1, 0, false, EPI_STORE, true, 64><<<f32_grid(tiles), 256, 0, st>>>(g);
 }
 
 void launch_gate_dx_gemm(const void* dl_hi, const void* dl_lo, const void* wg_pad, const int32_t* whole, int d, int n_pad,

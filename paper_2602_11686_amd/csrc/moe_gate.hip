@@ -264,7 +264,10 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     constexpr int U = NT <= 2 ? 4 : NT <= 4 ? 2 : 1;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int l16 = lane & 15, kg = lane >> 4;
-    const int t0 = blockIdx.x * MT;
+    // (a third grid dimension where the first cannot hold the tokens)
+    const int64_t first = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * MT;
+    if (first >= Tn) return;
+    const int t0 = (int)first;
     const int trow = min(t0 + l16, Tn - 1);
     const int nw = NW * (SPLIT ? (int)gridDim.y : 1), w = SPLIT ? (int)blockIdx.y * NW + wave : wave;
     const int kq = (d + 16 * nw - 1) / (16 * nw) * 16;
@@ -342,7 +345,8 @@ static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, co
         constexpr int NT = decltype(nt_tag)::value;
         size_t lds = (size_t)kGateF32Waves * kGateF32Tokens * NT * 16 * sizeof(float);
         if (lds < (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float);
-        const dim3 grid((s->T + kGateF32Tokens - 1) / kGateF32Tokens, slices ? gate_splits(s) : 1);
+        const unsigned tiles = (unsigned)(((int64_t)s->T + kGateF32Tokens - 1) / kGateF32Tokens), most = 1 << 22;
+        const dim3 grid(tiles < most ? tiles : most, slices ? gate_splits(s) : 1, (tiles + most - 1) / most);
         auto kern = slices ? gate_topk_f32_kernel<T, NT, true> : gate_topk_f32_kernel<T, NT, false>;
         ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGateF32Waves * kGateF32Tokens * MOE_MAX_EXPERTS * 4);
         kern<<<grid, kGateF32Waves * 64, lds, st>>>(x, wg, bias, ids, w, logits, slices, s->T, s->d, s->E, s->k);
@@ -452,6 +456,12 @@ static inline int pad4(int v) { return (v + 3) / 4 * 4; }
 static inline int mma_chunks(int Tn) { const int c = mma_chunk_tokens(Tn); return (Tn + c - 1) / c; }
 static inline int pad64(int v) { return (v + 63) / 64 * 64; }  // the dense dL is a K operand: whole 64-wide k-stages
 
+// workgroups in a grid whose first dimension stays below 2^32 threads
+static dim3 token_grid(int64_t blocks) {
+    constexpr int64_t kMost = 1 << 22;
+    return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
+}
+
 // one wavefront per token: dl[t,s] (fp32, for the dx update) and the dense rows, dl[t,s] = w_s (dw_s - sum_j w_j dw_j);
 // D = bf16_t: hi and lo, D = float: hi is the value itself.  It also writes the constants of the products after it: the
 // chunks' token ranges, a row of zeros, and the token range as a single group (in a launch of their own 1.4 us of the 11
@@ -464,11 +474,12 @@ __global__ __launch_bounds__(256) void gate_dl_dense_kernel(const int32_t* __res
                                                             int chunk_tokens, uint32_t* __restrict__ zero_row,
                                                             int32_t* __restrict__ whole) {
     const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int i = blockIdx.x * 256 + threadIdx.x;  // (at least 256 threads, and 64 for every chunk)
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t t = block * 4 + (threadIdx.x >> 6);
+    const int64_t i = block * 256 + threadIdx.x;  // (at least 256 threads, and 64 for every chunk)
     if (i < 128) zero_row[i] = 0u;
-    if (i < 2) whole[i] = i * Tn;
-    if (i <= nchunks) chunk_off[i] = (int)min((int64_t)i * chunk_tokens, (int64_t)Tn);
+    if (i < 2) whole[i] = (int)i * Tn;
+    if (i <= nchunks) chunk_off[i] = (int)min(i * chunk_tokens, (int64_t)Tn);
     if (t >= Tn) return;
     float dot = 0.f;
     for (int s = 0; s < k; ++s) dot += w[(size_t)t * k + s] * dw[(size_t)t * k + s];
@@ -602,7 +613,7 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     int32_t* coff = static_cast<int32_t*>(cv.take((size_t)(nch + 1) * 4));
     uint32_t* zero_row = static_cast<uint32_t*>(cv.take(512));
     int32_t* whole = static_cast<int32_t*>(cv.take(256));
-    gate_dl_dense_kernel<T><<<(s->T + 3) / 4, 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch,
+    gate_dl_dense_kernel<T><<<token_grid(((int64_t)s->T + 3) / 4), 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch,
                                                             f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s->T), zero_row, whole);
     if (dx && !f32 && s->k >= 4) {
         // dx += dL * W_g^T as a GEMM over the dense (hi + lo) dL: reads and writes dx once; the gate

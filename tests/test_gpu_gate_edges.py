@@ -86,3 +86,40 @@ def test_gate_bwd_edges(T, d, E, k, dtype):
     assert float((dwg.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
     ref = dx0 + dl @ wg.double().t()
     assert float((dx.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+def test_gate_topk_more_tokens_than_a_grid_dimension():
+    """2^27 tokens are 2^23 workgroups of 512 threads.  Two experts, top-1; fp32 logits of four terms of magnitude <= 1 are
+    within 2^-22 of the exact ones."""
+    T, d, E = (1 << 27) + 33, 4, 2
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.empty(T, d, device="cuda").uniform_(-1.0, 1.0, generator=g)
+    wg = torch.tensor([[1.0, -0.5], [0.25, 1.0], [-1.0, 0.5], [0.75, -1.0]], device="cuda")
+    ids, w = torch.full((T, 1), -7, dtype=torch.int32, device="cuda"), torch.full((T, 1), float("nan"), device="cuda")
+    B.moe_gate_topk(B.Shape(T, d, 4, E, 1, torch.float32), x, wg, None, ids, w, None,
+                    torch.empty(0, dtype=torch.uint8, device="cuda"))
+    gap = x @ (wg[:, 0] - wg[:, 1])
+    clear = gap.abs() > 1e-5
+    assert torch.equal(ids[clear, 0], (gap[clear] < 0).to(torch.int32))
+    assert int(ids.min()) >= 0 and int(ids.max()) <= 1 and bool((w == 1.0).all())
+
+
+def test_gate_bwd_more_tokens_than_a_grid_dimension():
+    """2^26 tokens are 2^24 workgroups of 256 threads in the launch that expands dL."""
+    T, d, E, k = (1 << 26) + 1029, 4, 3, 2
+    g = torch.Generator(device="cuda").manual_seed(3)
+    s = B.Shape(T, d, 4, E, k, torch.float32)
+    x = torch.empty(T, d, device="cuda").normal_(generator=g)
+    wg = torch.empty(d, E, device="cuda").normal_(generator=g)
+    ids = torch.stack([torch.arange(T, device="cuda") % E, (torch.arange(T, device="cuda") + 1) % E], 1).to(torch.int32)
+    w = torch.empty(T, k, device="cuda").uniform_(0.1, 0.9, generator=g)
+    dw = torch.empty(T, k, device="cuda").normal_(generator=g)
+    dx, dwg = torch.zeros(T, d, device="cuda"), torch.full((d, E), float("nan"), device="cuda")
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    B.moe_gate_topk_bwd(s, x, wg, ids, w, dw, dx, dwg, ws)
+    dl = torch.zeros(T, E, device="cuda").scatter_(1, ids.long(), w * (dw - (w * dw).sum(1, keepdim=True)))
+    assert float((dx - dl @ wg.t()).abs().max()) <= 1e-5 * 32       # sums of three products of magnitude up to about 32
+    ref = sum(x[i:i + (1 << 22)].double().t() @ dl[i:i + (1 << 22)].double() for i in range(0, T, 1 << 22))
+    # fp32 partial sums of 2^18 chunks added one after the other: their roundings, 2^-24 of the running sum each, add up
+    # like a random walk to 2^9 * 2^-24 of it
+    assert float((dwg.double() - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
