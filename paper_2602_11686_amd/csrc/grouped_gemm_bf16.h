@@ -2,17 +2,16 @@
 // MFMA 32x32x16 bf16 with fp32 accumulators, operands streamed HBM -> LDS by the
 // DMA path of the global loads (no register staging) into two LDS stages of 64 KB.
 //
-// One template covers the six products of the expert FFN (paper section 3.1;
-// 6*H*H' FLOPs per routed token forward, backward twice that):
+// One template covers the products that contract over the rows of an expert (paper section 3.1; the ones over
+// ragged rows are in grouped_gemm_quad.h) and the gate's two in the backward pass:
 //
-//   RAGK == false: the ragged dimension is M (the rows of one expert)
-//       A  [rows][K]  K contiguous                 (Xp, H, dYp, dA, dB)
-//       B  BT == 0: [K][N]  N contiguous           (forward: W1, W3 [d][f], W2 [f][d])
-//          BT == 1: [N][K]  K contiguous           (dgrad:   W2 as [f][d], W1/W3 as [d][f])
 //   RAGK == true: the ragged dimension is the contraction (wgrad), AT == 1, BT == 0
-//       A  [rows][M]  M contiguous                 (Xp, H)
-//       B  [rows][N]  N contiguous                 (dA|dB, dYp)
+//       A  [rows][M]  M contiguous                 (Xp, H; the tokens)
+//       B  [rows][N]  N contiguous                 (dA|dB, dYp; the logits' gradients)
 //       C_e [M][N] = sum over the rows of expert e;  an expert without rows gets zeros.
+//   RAGK == false: the ragged dimension is M (dx += dl * W_g^T, one expert), AT == 0, BT == 1
+//       A  [rows][K]  K contiguous
+//       B  [N][K]     K contiguous
 //
 // A k-stage is 64 wide.  What the vector memory path charges for is the cache line it touches, not the
 // bytes it delivers (measured per CU for a 32 KB stage from L2: 1300 clocks when every request takes 64 bytes
@@ -28,10 +27,10 @@
 // conflict-free on the 64 banks.  A DMA load writes 64 lanes x 16 B to consecutive LDS addresses, so
 // the swizzle is applied on the global side: lane l fetches the piece that belongs in slot l.
 //
-// DUAL: two B matrices share the A tile (W1|W3 forward, dA|dB wgrad): the B tile holds 128 columns of the
-// first as 64 k-rows x 256 B, then the same 128 columns of the second (same swizzle inside the 16 pieces of
-// a k-row), so that one DMA instruction (4 k-rows x 256 B) reads from one matrix only.  Each wavefront
-// accumulates both products for the same outputs (forward: the epilogue writes silu(a)*b).
+// DUAL: two B matrices share the A tile (dA|dB): the B tile holds 128 columns of the first as 64 k-rows x 256 B,
+// then the same 128 columns of the second (same swizzle inside the 16 pieces of a k-row), so that one DMA
+// instruction (4 k-rows x 256 B) reads from one matrix only.  Each wavefront accumulates both products for the
+// same outputs.
 #pragma once
 
 namespace moe {
@@ -160,15 +159,12 @@ struct TileDesc {
 // next tile is made when a tile starts (one lane; its latency hides behind the main loop), reaches LDS
 // before the last barrier of the main loop and is read by all wavefronts after it.
 //
-// KREST (ragged M): K is no multiple of 64.  An instance of its own, because the test of the last stage in the
-// main loop's issue side costs 1.6 % where no stage is partial.
-//
-// STREAM (ragged K): C is stored non-temporally.  (An instance of its own too: of two stores behind a test at run time
+// STREAM (ragged K): C is stored non-temporally.  (An instance of its own: of two stores behind a test at run time
 // the compiler makes one plain store.)
-template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool KREST = false, bool STREAM = false>
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
-    static_assert(RAGK ? (AT == 1 && BT == 0 && !KREST) : (AT == 0 && !STREAM), "operand forms");
-    static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
+    static_assert(RAGK ? (AT == 1 && BT == 0) : (AT == 0 && BT == 1 && !DUAL && !STREAM), "operand forms");
+    static_assert(RAGK ? EPI == EPI_STORE || EPI == EPI_STORE2 || EPI == EPI_STORE_F32 : EPI == EPI_ADD, "epilogues");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kTableOff);  // [E+1] rows of each expert
     int32_t* t_pref = t_off + MOE_MAX_EXPERTS + 1;                              // [E+1] tiles before expert e
@@ -395,35 +391,15 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
         if constexpr (!RAGK) {
             const char* Ab = (sg ? sA[1] : sA[0]) + (int64_t)k0 * 2;
             const char* Bb = (sg ? sB[1] : sB[0]) + (BT == 1 ? (int64_t)k0 * 2 : (int64_t)k0 * ldb * 2);
-            if (!KREST || k0 + TK <= di.kend) {  // (wave-uniform) the whole stage lies inside the contraction
 #pragma unroll
-                for (int i = 0; i < CPW; ++i) {
-                    if (i < lo || i >= hi) continue;
-                    dma16_s(Ab, a_off[i], st + i * 1024);
-                }
+            for (int i = 0; i < CPW; ++i) {
+                if (i < lo || i >= hi) continue;
+                dma16_s(Ab, a_off[i], st + i * 1024);
+            }
 #pragma unroll
-                for (int i = 0; i < CPW; ++i) {
-                    if (CPW + i < lo || CPW + i >= hi) continue;
-                    dma16_s(Bb, b_off[i], st + kBOff + i * 1024);
-                }
-            } else {
-                // last stage of a K that is no multiple of 64 (it is one of 8, so a 16-byte piece is inside or
-                // outside as a whole): what lies past the end reads zeros, on both sides
-                const int left = di.kend - k0;  // 8 .. TK-8
-                const char* zeros = reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16;
-#pragma unroll
-                for (int i = 0; i < CPW; ++i) {
-                    if (i < lo || i >= hi) continue;
-                    const int r = (wave * CPW + i) * 8 + (lane >> 3);
-                    dma16(((lane & 7) ^ swz_rows(r)) * 8 < left ? Ab + a_off[i] : zeros, st + i * 1024);
-                }
-#pragma unroll
-                for (int i = 0; i < CPW; ++i) {
-                    if (CPW + i < lo || CPW + i >= hi) continue;
-                    const int r = (wave * CPW + i) * 8 + (lane >> 3);
-                    const int k = BT == 1 ? ((lane & 7) ^ swz_rows(r)) * 8 : qb_row[i];
-                    dma16(k < left ? Bb + b_off[i] : zeros, st + kBOff + i * 1024);
-                }
+            for (int i = 0; i < CPW; ++i) {
+                if (CPW + i < lo || CPW + i >= hi) continue;
+                dma16_s(Bb, b_off[i], st + kBOff + i * 1024);
             }
         } else {
             const char* Ab = reinterpret_cast<const char*>(sg ? iA[1] : iA[0]) + (int64_t)k0 * lda * 2;
@@ -616,30 +592,23 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                             if (col + z < g.N) d[z] = acc[i][j][4 * g4 + z];
                     }
             }
-        } else if constexpr (EPI == EPI_DH || EPI == EPI_DHP || EPI == EPI_ADD) {
-            // dH in fp32 through LDS, 64 rows x 128 columns at a time; then 8 columns per thread: read A, B,
-            // write H = silu(A)*B, dA = dH*B*silu'(A), dB = dH*silu(A).  Staging rows are 512 B; a lane writes
-            // 16-byte pieces of its row, and the piece index is XORed with row%32 so that the 32 rows of a
-            // write fall into different banks.
-            // EPI_DHP is the same epilogue for activations saved as products (P = B*silu'(A), Q = silu(A); H is
-            // saved too and not rewritten): dA = dH*P, dB = dH*Q, two multiplications per element.
-            // The arithmetic bounds this epilogue (about 20 VALU issue slots per element, the exponential and
-            // the reciprocal at a quarter of the rate), so nothing else may add to it: the global operands of
-            // pass q+1 (saved A and B, or the old C) are requested at the top of pass q into a second set of
-            // registers and have a whole pass to arrive.  Every lane loads (dead items from a clamped address)
-            // and every lane consumes what it loaded; only the stores are predicated.  The wait for the
-            // operands of pass q leaves the loads of pass q+1 outstanding: vmcnt(loads per pass); loads return in
-            // order, so whatever the stores of pass q-1 do, the older loads have landed when at most the
-            // younger ones are pending.
-            constexpr int IPT = 64 * 16 / kThreads;                  // 8-column items per thread and pass
-            constexpr int NLD = (EPI == EPI_ADD ? 1 : 2) * IPT;      // loads per thread and pass
-            static_assert(NLD == 2 || NLD == 4, "the waits below are written for these counts");
+        } else if constexpr (EPI == EPI_ADD) {
+            // C += tile: the tile in fp32 through LDS, 64 rows x 128 columns at a time; then 8 columns per thread: the bf16
+            // values plus the tile, one rounding.  Staging rows are 512 B; a lane writes 16-byte pieces of its row, and the
+            // piece index is XORed with row%32 so that the 32 rows of a write fall into different banks.
+            // The old C of pass q+1 is requested at the top of pass q into a second set of registers and has a whole
+            // pass to arrive.  Every lane loads (dead items from a clamped address) and every lane consumes what it
+            // loaded; only the stores are predicated.  The wait for the operands of pass q leaves the loads of pass q+1
+            // outstanding: vmcnt(loads per pass); loads return in order, so whatever the stores of pass q-1 do, the
+            // older loads have landed when at most the younger ones are pending.
+            constexpr int IPT = 64 * 16 / kThreads;                  // 8-column items, and loads, per thread and pass
+            static_assert(IPT == 2, "the waits below are written for this count");
             const int64_t tile_base = cbase + (int64_t)t.m0 * g.ldc + t.n0;
             uint32_t ldc_u = (uint32_t)g.ldc;  // (opaque per tile, as in the bf16 path)
             asm volatile("" : "+s"(ldc_u));
             const int last_row = t.m_lim - 1 - t.m0, last_col = g.N - 8 - t.n0;
-            u32x4 pre0[2][IPT], pre1[2][IPT];
-            auto load_pass = [&](int q, u32x4 (&p0)[IPT], u32x4 (&p1)[IPT]) {
+            u32x4 pre[2][IPT];
+            auto load_pass = [&](int q, u32x4 (&p0)[IPT]) {
 #pragma unroll
                 for (int u = 0; u < IPT; ++u) {
                     const int item = tid + u * kThreads;
@@ -647,26 +616,20 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                     const int trow = (sr >> 5) * wrows + (q >> 1) * 32 + (sr & 31), tcol = (q & 1) * 128 + cg * 8;
                     const int lrow = trow < last_row ? trow : last_row, lcol = tcol < last_col ? tcol : last_col;
                     const uint32_t off = (uint32_t)lrow * ldc_u + (uint32_t)lcol;
-                    if constexpr (EPI == EPI_ADD) {
-                        p0[u] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(g.C0) + tile_base + off);
-                        p1[u] = (u32x4){0, 0, 0, 0};
-                    } else {
-                        p0[u] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(g.S0) + tile_base + off);
-                        p1[u] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(g.S1) + tile_base + off);
-                    }
+                    p0[u] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(g.C0) + tile_base + off);
                 }
             };
             // (the number of passes is a compile-time constant of each instance, so that the compiler's
             // bookkeeping of pending loads is exact and it adds no waits of its own in the next tile's loop)
             auto run_passes = [&](auto np_tag) {
             constexpr int NP = decltype(np_tag)::value;
-            load_pass(0, pre0[0], pre1[0]);
+            load_pass(0, pre[0]);
             __builtin_amdgcn_sched_barrier(0);  // the loads of pass 0 stay in front of those of pass 1
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
                 const int i = q >> 1, p = q & 1;
                 const bool more = q + 1 < NP;
-                if (more) load_pass(q + 1, pre0[(q + 1) & 1], pre1[(q + 1) & 1]);
+                if (more) load_pass(q + 1, pre[(q + 1) & 1]);
                 {
                     const int sr = wm * 32 + l32;
 #pragma unroll
@@ -682,8 +645,8 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                 }
                 __syncthreads();
                 // (builtins, so that the compiler's own bookkeeping of pending loads agrees)
-                if (more) __builtin_amdgcn_s_waitcnt(NLD == 4 ? 0x0F74 : 0x0F72);  // vmcnt(NLD)
-                else __builtin_amdgcn_s_waitcnt(0x0F70);                           // vmcnt(0)
+                if (more) __builtin_amdgcn_s_waitcnt(0x0F72);  // vmcnt(IPT)
+                else __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
 #pragma unroll
                 for (int u = 0; u < IPT; ++u) {
                     const int item = tid + u * kThreads;
@@ -695,57 +658,15 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                     const f32x4v d0 = *reinterpret_cast<const f32x4v*>(stg + sr * 512 + ((2 * cg) ^ sw) * 16);
                     const f32x4v d1 = *reinterpret_cast<const f32x4v*>(stg + sr * 512 + ((2 * cg + 1) ^ sw) * 16);
                     const float dh[8] = {d0[0], d0[1], d0[2], d0[3], d1[0], d1[1], d1[2], d1[3]};
-                    if constexpr (EPI == EPI_ADD) {  // C += tile: the bf16 values plus the tile in fp32, one rounding
-                        const u32x4 old = pre0[q & 1][u];
-                        u32x4 o;
+                    const u32x4 old = pre[q & 1][u];
+                    u32x4 o;
 #pragma unroll
-                        for (int z = 0; z < 4; ++z) {
-                            const float lo = __uint_as_float(old[z] << 16) + dh[2 * z];
-                            const float hi = __uint_as_float(old[z] & 0xFFFF0000u) + dh[2 * z + 1];
-                            o[z] = pack_bf16x2(lo, hi);
-                        }
-                        if (live) *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + tile_base + off) = o;
-                    } else {
-                        const u32x4 av = pre0[q & 1][u], bv = pre1[q & 1][u];
-                        u32x4 oh, oa, ob;
-                        if constexpr (EPI == EPI_DHP) {
-#pragma unroll
-                            for (int z4 = 0; z4 < 4; ++z4) {
-                                const float p_lo = __uint_as_float(av[z4] << 16), p_hi = __uint_as_float(av[z4] & 0xFFFF0000u);
-                                const float q_lo = __uint_as_float(bv[z4] << 16), q_hi = __uint_as_float(bv[z4] & 0xFFFF0000u);
-                                oa[z4] = pack_bf16x2(dh[2 * z4] * p_lo, dh[2 * z4 + 1] * p_hi);
-                                ob[z4] = pack_bf16x2(dh[2 * z4] * q_lo, dh[2 * z4 + 1] * q_hi);
-                            }
-                            if (live) {
-                                *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + tile_base + off) = oa;
-                                *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C2) + tile_base + off) = ob;
-                            }
-                            continue;
-                        }
-#pragma unroll
-                        for (int z4 = 0; z4 < 4; ++z4) {
-                            float hh[2], da[2], db[2];
-#pragma unroll
-                            for (int z = 0; z < 2; ++z) {
-                                const float A = __uint_as_float(z ? (av[z4] & 0xFFFF0000u) : (av[z4] << 16));
-                                const float B = __uint_as_float(z ? (bv[z4] & 0xFFFF0000u) : (bv[z4] << 16));
-                                const float sg = sigmoid_f(A);             // one exp and one reciprocal per element
-                                const float sA = A * sg;                   // silu(A)
-                                const float gr = sg + sA * (1.0f - sg);    // silu'(A) = s (1 + A (1 - s))
-                                hh[z] = sA * B;
-                                da[z] = dh[2 * z4 + z] * B * gr;
-                                db[z] = dh[2 * z4 + z] * sA;
-                            }
-                            oh[z4] = pack_bf16x2(hh[0], hh[1]);
-                            oa[z4] = pack_bf16x2(da[0], da[1]);
-                            ob[z4] = pack_bf16x2(db[0], db[1]);
-                        }
-                        if (live) {
-                            *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + tile_base + off) = oh;
-                            *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + tile_base + off) = oa;
-                            *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C2) + tile_base + off) = ob;
-                        }
+                    for (int z = 0; z < 4; ++z) {
+                        const float lo = __uint_as_float(old[z] << 16) + dh[2 * z];
+                        const float hi = __uint_as_float(old[z] & 0xFFFF0000u) + dh[2 * z + 1];
+                        o[z] = pack_bf16x2(lo, hi);
                     }
+                    if (live) *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + tile_base + off) = o;
                 }
                 __syncthreads();
             }
@@ -753,14 +674,13 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
             if (ni == 4) run_passes(IntTag<8>{});  // pass q: row block q/2, column half q%2
             else run_passes(IntTag<4>{});          // (a 128-row tile has two row blocks)
         } else {
-            // bf16 tiles: stage [RPP rows][ROWB bytes] with swizzled 16-byte pieces, then 16 bytes per lane along
-            // rows.  A pass fills one of two 16 KB areas: block i of both wavefront rows (64 rows of 256 B) or of
-            // one wavefront row (32 rows of 512 B).  The areas take the passes in turn, so one barrier per pass is
-            // enough: a wavefront that writes pass p+2 has passed the barrier of pass p+1, which every wavefront
+            // bf16 tiles: stage [32 rows][512 bytes] with swizzled 16-byte pieces, then 16 bytes per lane along
+            // rows.  A pass fills one of two 16 KB areas with block i of one wavefront row.  The areas take the passes in
+            // turn, so one barrier per pass is enough: a wavefront that writes pass p+2 has passed the barrier of pass p+1, which every wavefront
             // reaches only after it has read pass p.
-            constexpr int ROWB = (DUAL && EPI == EPI_SWIGLU) ? 256 : 512;
+            constexpr int ROWB = 512;
             constexpr int PPR = ROWB / 16;               // pieces per row
-            constexpr int RPP = kStagingBytes / 2 / ROWB;  // rows per pass: 64 or 32
+            constexpr int RPP = kStagingBytes / 2 / ROWB;  // rows per pass
             constexpr int ITEMS = RPP * PPR / kThreads;   // 16-byte pieces per thread and pass
             static_assert(ITEMS * kThreads == RPP * PPR, "a pass is a whole number of pieces per thread");
             // Four accumulators r = 4g .. 4g+3 of a lane are four consecutive columns of its row: one 8-byte
@@ -771,7 +691,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                 u32x2 o;
                 o[0] = pack_bf16x2(v0, v1);
                 o[1] = pack_bf16x2(v2, v3);
-                const int sr = (RPP == 64 ? wm * 32 : 0) + l32;
+                const int sr = l32;
                 const int col = colbase + g4 * 8 + kg * 4;
                 *reinterpret_cast<u32x2*>(sb + sr * ROWB + (((col >> 3) ^ stg_sw(sr)) << 4) + (col & 7) * 2) = o;
             };
@@ -780,7 +700,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
             // otherwise compute them once per kernel and keep them in scratch memory)
             uint32_t ldc_u = (uint32_t)g.ldc;
             asm volatile("" : "+s"(ldc_u));
-            // h: the wavefront row whose 32 rows the pass holds (RPP == 32)
+            // h: the wavefront row whose 32 rows the pass holds
             auto flush = [&](const char* sb, int i, int h, bf16_t* dst0, bf16_t* dst1, int cols0) {
                 __syncthreads();
                 u32x4 v[ITEMS];
@@ -794,7 +714,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                 for (int u = 0; u < ITEMS; ++u) {
                     const int item = tid + u * kThreads;
                     const int sr = item / PPR, pc = item % PPR;
-                    const int trow = (RPP == 64 ? (sr >> 5) : h) * wrows + i * 32 + (sr & 31);  // row inside the tile
+                    const int trow = h * wrows + i * 32 + sr;  // row inside the tile
                     int col = pc * 8;
                     bf16_t* dst = dst0;
                     if (dst1 && col >= cols0) { col -= cols0; dst = dst1; }
@@ -812,61 +732,33 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (i >= ni) break;
-                if constexpr (EPI == EPI_SWIGLU) {
-                    for (int pass = 0; pass < (g.S0 ? 3 : 1); ++pass) {
-                        char* sb = next_buf();
 #pragma unroll
-                        for (int j = 0; j < NJ / 2; ++j)
+                for (int h = 0; h < 2; ++h) {
+                    char* sb = next_buf();
+                    if (wm == h) {
+                        if constexpr (DUAL) {  // EPI_STORE2: first 128 columns -> C0, second 128 -> C1
 #pragma unroll
-                            for (int g4 = 0; g4 < 4; ++g4) {
-                                float v[4];
+                            for (int j = 0; j < NJ / 2; ++j)
 #pragma unroll
-                                for (int z = 0; z < 4; ++z) {
-                                    const float a = acc[i][j][4 * g4 + z], b = acc[i][j + NJ / 2][4 * g4 + z];
-                                    if (pass == 0) {
-                                        v[z] = silu_f(a) * b;
-                                    } else if (!g.products) {
-                                        v[z] = pass == 1 ? a : b;
-                                    } else {  // P = b * silu'(a), Q = silu(a)
-                                        const float sg = sigmoid_f(a), sA = a * sg;
-                                        v[z] = pass == 1 ? b * (sg + sA * (1.0f - sg)) : sA;
-                                    }
+                                for (int g4 = 0; g4 < 4; ++g4) {
+                                    const int r = 4 * g4;
+                                    put4(sb, g4, wn * (NJ / 2) * 32 + j * 32, acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2],
+                                         acc[i][j][r + 3]);
+                                    put4(sb, g4, 128 + wn * (NJ / 2) * 32 + j * 32, acc[i][j + NJ / 2][r], acc[i][j + NJ / 2][r + 1],
+                                         acc[i][j + NJ / 2][r + 2], acc[i][j + NJ / 2][r + 3]);
                                 }
-                                put4(sb, g4, wn * (NJ / 2) * 32 + j * 32, v[0], v[1], v[2], v[3]);
-                            }
-                        bf16_t* dst = pass == 0 ? static_cast<bf16_t*>(g.C0)
-                                                : const_cast<bf16_t*>(static_cast<const bf16_t*>(pass == 1 ? g.S0 : g.S1));
-                        flush(sb, i, 0, dst, nullptr, 0);
-                    }
-                } else {
+                        } else {  // EPI_STORE
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        char* sb = next_buf();
-                        if (wm == h) {
-                            if constexpr (DUAL) {  // EPI_STORE2: first 128 columns -> C0, second 128 -> C1
+                            for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                                for (int j = 0; j < NJ / 2; ++j)
-#pragma unroll
-                                    for (int g4 = 0; g4 < 4; ++g4) {
-                                        const int r = 4 * g4;
-                                        put4(sb, g4, wn * (NJ / 2) * 32 + j * 32, acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2],
-                                             acc[i][j][r + 3]);
-                                        put4(sb, g4, 128 + wn * (NJ / 2) * 32 + j * 32, acc[i][j + NJ / 2][r], acc[i][j + NJ / 2][r + 1],
-                                             acc[i][j + NJ / 2][r + 2], acc[i][j + NJ / 2][r + 3]);
-                                    }
-                            } else {  // EPI_STORE
-#pragma unroll
-                                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                                    for (int g4 = 0; g4 < 4; ++g4) {
-                                        const int r = 4 * g4;
-                                        put4(sb, g4, wn * NJ * 32 + j * 32, acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]);
-                                    }
-                            }
+                                for (int g4 = 0; g4 < 4; ++g4) {
+                                    const int r = 4 * g4;
+                                    put4(sb, g4, wn * NJ * 32 + j * 32, acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]);
+                                }
                         }
-                        if constexpr (DUAL) flush(sb, i, h, static_cast<bf16_t*>(g.C0), static_cast<bf16_t*>(g.C1), 128);
-                        else flush(sb, i, h, static_cast<bf16_t*>(g.C0), nullptr, 0);
                     }
+                    if constexpr (DUAL) flush(sb, i, h, static_cast<bf16_t*>(g.C0), static_cast<bf16_t*>(g.C1), 128);
+                    else flush(sb, i, h, static_cast<bf16_t*>(g.C0), nullptr, 0);
                 }
             }
             __syncthreads();  // the last two passes have been read: the chunks under the staging area may be requested

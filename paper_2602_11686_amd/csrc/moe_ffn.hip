@@ -15,12 +15,11 @@
 //   dgrad 2     dXp_e = dA_e * W1_e^T + dB_e * W3_e^T      (two K segments)
 //   wgrad       dW2_e = H_e^T * dYp_e,  [dW1_e|dW3_e] = Xp_e^T * [dA_e|dB_e]
 //
-// bf16 path: the persistent 256x256x64 kernel of grouped_gemm_bf16.h (8 wavefronts,
-// MFMA 32x32x16 bf16 with fp32 accumulators, operands brought into LDS by DMA in
-// memory order, transposing LDS reads where the contraction index is not the
-// contiguous one).  A K that is no multiple of 64 ends in a stage padded with zeros: 4099 tokens over 24 experts of
-// 1096 x 1352 took 1665 us in the five products with ragged rows on the plain 128x128x64 kernel below and take
-// 612 us here.  That kernel is left for leading dimensions and extents beyond the 32-bit offsets of this one.
+// bf16 path: persistent 256x256x64 kernels, 8 wavefronts, fp32 accumulators, operands brought into LDS by DMA in
+// memory order, transposing LDS reads where the contraction index is not the contiguous one: gg_quad_kernel
+// (grouped_gemm_quad.h) for the products over ragged rows, gg256_kernel (grouped_gemm_bf16.h) for those that contract
+// over them.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
+// left for leading dimensions and extents beyond the 32-bit offsets of these.
 // fp32 path: 128x128 or 64x64 tiles on the fp32 matrix instructions, same tile walk and epilogues.
 #include "moe_internal.h"
 
@@ -272,6 +271,7 @@ __global__ __launch_bounds__(256) void gg_bf16_kernel(const GArgs g) {
 
 }  // namespace moe
 #include "grouped_gemm_bf16.h"
+#include "grouped_gemm_quad.h"
 namespace moe {
 
 // Ragged M: the expert e whose tiles hold tile L of the launch, its rows [row0, row_end) and the tile's index among
@@ -627,14 +627,18 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             if constexpr (!RAGK) {
                 if (ok && launch_few_rows<BT, DUAL, EPI>(g, R, st)) return;
             }
-            if (ok) {
-                auto kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK>;
-                if constexpr (!RAGK)
-                    if (g.K % TK) kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK, true>;
-                if constexpr (RAGK)
-                    if (stream_gradients(R, g.E)) kern = gg256_kernel<AT, BT, DUAL, EPI, RAGK, false, true>;
+            if constexpr (!RAGK) {
+                if (ok) {
+                    auto kern = g.K % TK ? gg_quad_kernel<BT, DUAL, EPI, true> : gg_quad_kernel<BT, DUAL, EPI, false>;
+                    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kQuadLds);
+                    kern<<<dim3(256), kThreads, kQuadLds, st>>>(g);  // persistent: one workgroup per CU
+                    return;
+                }
+            } else if (ok) {
+                auto kern = stream_gradients(R, g.E) ? gg256_kernel<AT, BT, DUAL, EPI, RAGK, true>
+                                                     : gg256_kernel<AT, BT, DUAL, EPI, RAGK>;
                 ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGemmLds);
-                kern<<<dim3(256), kThreads, kGemmLds, st>>>(g);  // persistent: one workgroup per CU
+                kern<<<dim3(256), kThreads, kGemmLds, st>>>(g);
                 return;
             }
         }

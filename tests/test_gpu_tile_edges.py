@@ -102,6 +102,42 @@ def test_ffn_bf16_k_remainder(counts, d, f):
     check_ffn(counts, d, f, torch.bfloat16, 11 * d + f)
 
 
+# 256-row tiles computed in quadrants: one to six k-stages, tiles of at most 128 rows (with and without rows in the second
+# 64) among full ones, several tiles per workgroup, a last round cut in two, a remainder of K
+@pytest.mark.parametrize("counts,d,f", [((300, 1, 0, 128, 129), 64, 64), ((257, 200, 64), 128, 192), ((700, 0, 513), 320, 256),
+                                        ((65,) * 30 + (300,) * 10, 1024, 1408), ((2000, 130, 384), 2048, 1032)])
+def test_ffn_quadrants(counts, d, f):
+    check_ffn(counts, d, f, torch.bfloat16, 19 * d + f)
+
+
+def test_ffn_quadrants_long_tile_list():
+    """102400 tiles, 400 for each workgroup, which keeps a ring of 512.  Contractions of 8 and of 81920 terms; each output is
+    one rounding to bf16 (2^-9 of the value) plus fp32 sums of its terms (2^-24 of their absolute values each, partly
+    cancelling: 1e-5 of them covers 168)."""
+    E, d, f, big = 256, 320 * 256, 8, 65 * 256
+    g = torch.Generator(device="cuda").manual_seed(2)
+    counts = [1] * E
+    counts[100] = big
+    off = torch.tensor([0] + np.cumsum(counts).tolist(), dtype=torch.int32, device="cuda")
+    R = int(off[-1])
+    val = lambda *n, std=1.0: torch.empty(*n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, w1, w3, w2 = val(R, d), val(E, d, f, std=0.02), val(E, d, f, std=0.02), val(E, f, d)
+    s = B.Shape(R, d, f, E, 1, torch.bfloat16)
+    y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    h, p, q = (torch.full((R, f), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    B.moe_grouped_ffn_fwd_products(s, x, off, w1, w3, w2, y, h, p, q)
+    for e in (0, 99, 100, 101, 255):
+        for b in range(int(off[e]), int(off[e + 1]), 4096):
+            r = slice(b, min(b + 4096, int(off[e + 1])))
+            want, terms = h[r].float() @ w2[e].float(), h[r].float().abs() @ w2[e].float().abs()
+            assert bool(((y[r].float() - want).abs() <= want.abs() * 2.0**-8 + terms * 1e-5).all()), (e, b)
+        r = slice(int(off[e]), min(int(off[e + 1]), int(off[e]) + 300))
+        a, c = x[r].double() @ w1[e].double(), x[r].double() @ w3[e].double()
+        want = torch.nn.functional.silu(a) * c
+        assert float((h[r].double() - want).norm() / want.norm()) <= 4e-3, e   # (2^-9 and the sums of 81920 terms)
+    assert bool(torch.isfinite(y).all())
+
+
 # few rows per expert: 64-row tiles (mean at most 32) and 128-row ones (mean 33 .. 64, with and without enough column
 # tiles for the wide kernel), 16-row blocks, tails, an expert of several tiles, one to five k-stages and a remainder
 @pytest.mark.parametrize("counts,d,f", [((1, 0, 0, 2), 64, 64), ((15, 16, 17, 1, 0, 33, 64, 65), 128, 192),

@@ -145,3 +145,26 @@ def test_kernels_do_not_spill(ffn_asm):
         assert scratch and int(scratch.group(1)) == 0, (m.group(1), scratch and scratch.group(1))
         vgpr = re.search(r"\.amdhsa_next_free_vgpr (\d+)", body)
         assert vgpr and int(vgpr.group(1)) <= 256, (m.group(1), vgpr and vgpr.group(1))
+
+
+def test_quadrant_pipeline_holds_only_the_hand_placed_vmcnt_waits(ffn_asm):
+    """gg_quad_kernel counts its DMA loads across stages and tiles: in the blocks with MFMAs (one loop for tiles of more than
+    128 rows, one for the others) the compiler adds no vmcnt wait, the written ones are 8 and 6, 4 and 6, and nothing
+    is read or requested between each and its barrier; nothing spills."""
+    ks = kernels(ffn_asm, "gg_quad_kernel")
+    assert len(ks) == 10, sorted(ks)
+    for name, blocks in ks.items():
+        seen = []
+        for label, ins in blocks:
+            if not any(i.startswith("v_mfma") for i in ins):
+                continue
+            waits = [(k, int(re.search(r"vmcnt\((\d+)\)", i).group(1))) for k, i in enumerate(ins)
+                     if i.startswith("s_waitcnt") and "vmcnt" in i]
+            seen += [w for _, w in waits]
+            for k, _ in waits:
+                after = next((i for i in ins[k + 1:] if i.startswith(("s_barrier", "global_load", "ds_"))), "")
+                assert after.startswith("s_barrier"), (name, label, after)
+        # (with a K remainder the requests sit behind branches, the half loop's second wait in a block without MFMAs)
+        assert sorted(seen) == ([4, 6, 8] if name.endswith("Lb1EEEvNS_5GArgsE") else [4, 6, 6, 8]), (name, seen)
+    for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe\d+gg_quad_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
+        assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", m.group(2)), m.group(1)
