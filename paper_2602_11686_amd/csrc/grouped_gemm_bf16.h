@@ -2,8 +2,8 @@
 // MFMA 32x32x16 bf16 with fp32 accumulators, operands streamed HBM -> LDS by the
 // DMA path of the global loads (no register staging) into two LDS stages of 64 KB.
 //
-// One template covers the products that contract over the rows of an expert (paper section 3.1; the ones over
-// ragged rows are in grouped_gemm_quad.h) and the gate's two in the backward pass:
+// One template covers the products that contract over the rows of an expert, where these are few (the others, and the
+// ones over ragged rows, are in grouped_gemm_quad.h; paper section 3.1), and the gate's two in the backward pass:
 //
 //   RAGK == true: the ragged dimension is the contraction (wgrad), AT == 1, BT == 0
 //       A  [rows][M]  M contiguous                 (Xp, H; the tokens)

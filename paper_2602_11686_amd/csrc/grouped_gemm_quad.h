@@ -1,10 +1,16 @@
 // Grouped bf16 GEMM over ragged row counts, 256x256x64 tiles computed quadrant by quadrant.
 //
-// The products whose ragged dimension is M, the rows of one expert (6*H*H' FLOPs per routed token forward, twice that
-// backward with the two of grouped_gemm_bf16.h; paper section 3.1):
+// One template covers the six products of the expert FFN (6*H*H' FLOPs per routed token forward, twice that backward;
+// paper section 3.1):
+//
+//   RAGK == false: the ragged dimension is M (the rows of one expert)
 //       A  [rows][K]  K contiguous                 (Xp, H, dYp, dA, dB)
 //       B  BT == 0: [K][N]  N contiguous           (forward: W1, W3 [d][f], W2 [f][d])
 //          BT == 1: [N][K]  K contiguous           (dgrad:   W2 as [f][d], W1/W3 as [d][f])
+//   RAGK == true: the ragged dimension is the contraction (wgrad), BT == 0
+//       A  [rows][M]  M contiguous                 (Xp, H)
+//       B  [rows][N]  N contiguous                 (dA|dB, dYp)
+//       C_e [M][N] = sum over the rows of expert e;  an expert without rows gets zeros.
 //
 // What bounds a loop with one barrier per k-stage is that barrier: the 64 DMA instructions of a stage can only be
 // requested behind it, in a burst, and have to land before the next one.  Here a stage's tile is computed as four quadrants of
@@ -33,7 +39,8 @@
 // Measured, 32768 rows over 8 experts of 4096 x 14336 (us; one barrier per stage and 32x32x16 -> this): forward 1
 // 6500 -> 6070, forward 2 3210 -> 2930, dgrad 1 3620 -> 3220, dgrad 2 6500 -> 5990, 1270 to 1310 TFLOP/s without the epilogue
 // of dgrad 1.  The four phases alone, still in 32x32x16: 6590, 3210, 3580, 6500 (with zeros as operands 5510, 2190, 3190,
-// 4270 against 5940, 2680, 3470, 5380: 9 to 26 % fewer clocks, at a lower clock).
+// 4270 against 5940, 2680, 3470, 5380: 9 to 26 % fewer clocks, at a lower clock).  With the weight gradients here too a
+// training pass of these sizes takes 27580 us instead of 28200, 16 experts of 4096 x 2048 over 32 groups 2854 instead of 3001.
 //
 // LDS: row form halves [128 rows][128 B], the 16-byte piece p of row r in slot p ^ ((r >> 1) & 7); k-row form halves
 // [64 k-rows][256 B], swz_krow16 (DUAL: B0 is the first matrix, B1 the second).  The two stage buffers lie on both sides of
@@ -60,17 +67,23 @@ static_assert(kQuadLds <= kLdsBytes, "fits the unit's LDS");
 __device__ __forceinline__ int swz_krow16(int q) { return 2 * ((q & 3) | (((q >> 3) & 1) << 2)); }
 
 // KREST: K is no multiple of 64 (the last stage of a segment reads zeros past it); an instance of its own.
-template <int BT, bool DUAL, int EPI, bool KREST>
+//
+// RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).  STREAM (RAGK): C is stored non-temporally (an
+// instance of its own: of two stores behind a test at run time the compiler makes one plain store).
+template <int BT, bool DUAL, int EPI, bool KREST, bool RAGK = false, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
+    static_assert(RAGK ? BT == 0 && !KREST && (EPI == EPI_STORE || EPI == EPI_STORE2) : !STREAM && EPI != EPI_STORE2, "forms");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kQTableOff);  // [E+1] rows of each expert
     int32_t* t_pref = t_off + MOE_MAX_EXPERTS + 1;                   // [E+1] tiles before expert e
-    int4* list = reinterpret_cast<int4*>(smem + kQListOff);          // weights' index (-1: no more tiles), m0, m_lim, n0
+    // the workgroup's tiles: index of the weights (-1: no more tiles), m0, m_lim, n0; ragged K: expert, m0, its first row, n0
+    int4* list = reinterpret_cast<int4*>(smem + kQListOff);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave >> 2, wn = wave & 3;
     const int n_out = DUAL ? TN / 2 : TN;     // output columns per tile
     const int n_tiles = (g.N + n_out - 1) / n_out;
+    const int m_tiles_k = (g.M + TM - 1) / TM;  // ragged K
 
     // ---- rows of each expert and the number of tiles before it ----
     for (int i = threadIdx.x; i <= g.E; i += kThreads) t_off[i] = g.offsets[i];
@@ -80,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int e = lane * 4 + u;
-            c[u] = e < g.E ? ((t_off[e + 1] - t_off[e] + TM - 1) / TM) * n_tiles : 0;
+            c[u] = e < g.E ? (RAGK ? m_tiles_k : (t_off[e + 1] - t_off[e] + TM - 1) / TM) * n_tiles : 0;
             sum += c[u];
         }
         int incl = sum;
@@ -102,53 +115,95 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     // When the last round of tiles fills at most half of the workgroups, its tiles are cut into their upper and lower
     // 128 rows (tiles split_from + 2i and + 2i + 1), so that the round costs a 128-row tile's time.
     int total_tiles = t_pref[g.E], split_from = total_tiles;
-    {
+    if constexpr (!RAGK) {
         const int left = total_tiles % (int)gridDim.x;
         if (left > 0 && 2 * left <= (int)gridDim.x) {
             split_from = total_tiles - left;
             total_tiles += left;
         }
     }
-    // Tile `pos` of this workgroup -> its entry in the ring.  (The lower half of a cut tile of at most 128 rows is empty;
-    // it belongs to the last round, so it ends the workgroup's list.)
-    auto build_entry = [&](int pos) {
-        int L = logical_tile(blockIdx.x + pos * gridDim.x);
+    // Logical tile L -> entry `pos` of the ring.  (The lower half of a cut tile of at most 128 rows is empty; it belongs to
+    // the last round, so it ends the workgroup's list.)
+    auto build_entry = [&](int pos, int L) {
         int4 d = {-1, 0, 0, 0};
         if (L < total_tiles) {
-            int part = -1;
-            if (L >= split_from) {
-                part = (L - split_from) & 1;
-                L = split_from + ((L - split_from) >> 1);
-            }
-            int lo = 0, hi = g.E - 1;  // the expert whose tiles hold L: the last one with t_pref <= L
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (t_pref[mid] <= L) lo = mid;
-                else hi = mid - 1;
-            }
-            const int b = t_off[lo], en = t_off[lo + 1];
             int m, nt;
-            walk_tile(L - t_pref[lo], (en - b + TM - 1) / TM, n_tiles, m, nt);
-            d.y = b + m * TM;
-            d.z = en;
-            if (part >= 0) {
-                d.y += part * (TM / 2);
-                d.z = min(en, d.y + TM / 2);
+            if constexpr (RAGK) {
+                const int per = m_tiles_k * n_tiles, oi = L / per;
+                d.x = g.order[oi];  // heaviest experts first
+                walk_tile(L - oi * per, m_tiles_k, n_tiles, m, nt);
+                d.y = m * TM;
+                d.z = t_off[d.x];
+                d.w = nt * n_out;
+            } else {
+                int part = -1;
+                if (L >= split_from) {
+                    part = (L - split_from) & 1;
+                    L = split_from + ((L - split_from) >> 1);
+                }
+                int lo = 0, hi = g.E - 1;  // the expert whose tiles hold L: the last one with t_pref <= L
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (t_pref[mid] <= L) lo = mid;
+                    else hi = mid - 1;
+                }
+                const int b = t_off[lo], en = t_off[lo + 1];
+                walk_tile(L - t_pref[lo], (en - b + TM - 1) / TM, n_tiles, m, nt);
+                d.y = b + m * TM;
+                d.z = en;
+                if (part >= 0) {
+                    d.y += part * (TM / 2);
+                    d.z = min(en, d.y + TM / 2);
+                }
+                d.w = nt * n_out;
+                if (d.y < d.z) d.x = weight_index(g, lo);
             }
-            d.w = nt * n_out;
-            if (d.y < d.z) d.x = weight_index(g, lo);
         }
         list[pos & (kQList - 1)] = d;
     };
-    build_entry(threadIdx.x);
+    // Ragged M: the fixed order logical_tile(blockIdx.x + pos * gridDim.x).  Ragged K, where a tile costs as much as its
+    // expert has rows: the first two tiles in that order, the others drawn two tiles ahead from queues.  The logical
+    // order is cut into blocks of 32, block b belongs to XCD b % 8; entry c of queue x is tile ((c / 32) * 8 + x) * 32 + c % 32;
+    // a workgroup draws from its XCD's queue, then from the others.
+    if (!RAGK || threadIdx.x < 2) build_entry(threadIdx.x, logical_tile(blockIdx.x + threadIdx.x * gridDim.x));
     __syncthreads();
+    const int xcd = blockIdx.x & 7;
+    int qx = 0;  // (wavefront 0) queues found empty so far; the current one is that of XCD (xcd + qx) % 8
+    auto queue_counter = [&](int x) { return g.sched + ((xcd + x) & 7) * kSchedStride; };
+    auto tile_of_draw = [&](int x, int c) { return ((((c + 64) >> 5) * 8 + ((xcd + x) & 7)) << 5) + (c & 31); };
+    auto draw = [&]() -> int {
+        return qx < 8 && lane == 0 ? (int)__hip_atomic_fetch_add(queue_counter(qx), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    };
+    // (wavefront 0) draw `c` of the current queue, or of the next one that has any, becomes entry `pos`
+    auto place_draw = [&](int pos, int c) {
+        int L = total_tiles;
+        while (qx < 8) {
+            c = __builtin_amdgcn_readfirstlane(c);
+            L = tile_of_draw(qx, c);
+            if (L < total_tiles) break;
+            bool live = false;  // one look at all counters
+            if (lane > qx && lane < 8)
+                live = tile_of_draw(lane, (int)__hip_atomic_load(queue_counter(lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < total_tiles;
+            const uint64_t m = __ballot(live);
+            qx = m ? __builtin_ctzll(m) : 8;
+            c = draw();
+        }
+        if (lane == 0) build_entry(pos, qx < 8 ? L : total_tiles);
+    };
     struct Tile {
-        int w, m0, m_lim, n0;
+        int w, m0, m_lim, n0;  // w: index of the weights, or of the result
+        int row0, rows;        // ragged K: the expert's
     };
     auto tile_at = [&](int pos) -> Tile {
         const int4 d = list[pos & (kQList - 1)];
-        return {__builtin_amdgcn_readfirstlane(d.x), __builtin_amdgcn_readfirstlane(d.y), __builtin_amdgcn_readfirstlane(d.z),
-                __builtin_amdgcn_readfirstlane(d.w)};
+        Tile t{__builtin_amdgcn_readfirstlane(d.x), __builtin_amdgcn_readfirstlane(d.y), __builtin_amdgcn_readfirstlane(d.z),
+               __builtin_amdgcn_readfirstlane(d.w), 0, 0};
+        if constexpr (RAGK) {
+            t.row0 = t.m_lim;
+            t.rows = t.w < 0 ? 0 : __builtin_amdgcn_readfirstlane(t_off[t.w + 1]) - t.row0;
+            t.m_lim = g.M;
+        }
+        return t;
     };
 
     // ================= issue side: a cursor over the stages of the workgroup's tiles =================
@@ -156,18 +211,23 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     // slot lane%8.  k-row form: k-rows 4c .. 4c+3, lane -> k-row 4c + lane/16, slot lane%16.
     const int64_t lda = g.lda, ldb = g.ldb;
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(LDS_AS char*)smem + wave * 2048);
-    const int nk = (g.K + TK - 1) / TK, total = nk * g.nseg;  // k-stages per segment and per tile
+    const int nk = RAGK ? 0 : (g.K + TK - 1) / TK;  // k-stages per segment
+    // k-stages of a tile.  Ragged K: at least two, so that the cursor, two stages ahead, is never two tiles ahead (what lies
+    // past an expert's rows reads zeros, all of it where an expert has no rows)
+    auto stages_of = [&](const Tile& t) { return RAGK ? max(2, (t.rows + TK - 1) / TK) : nk * g.nseg; };
     uint32_t a_off[4], b_off[4];  // byte offsets of this lane's pieces (half, chunk) from the tile's bases at k = 0
     const char* sA[2];
     const char* sB[2];            // per segment; DUAL: per matrix
-    int ipos = 0, istage = 0, ibuf = 0;
+    int ipos = 0, istage = 0, ibuf = 0, itotal = 0, irows = 0;
     auto cursor_to = [&](const Tile& t) {
         if (t.w < 0) return;  // past the last tile: its first stages once more, which nobody reads
-        const int64_t eoff = (int64_t)t.w * g.strideB;
+        itotal = stages_of(t);
+        irows = t.rows;
+        const int64_t eoff = RAGK ? (int64_t)t.row0 * ldb : (int64_t)t.w * g.strideB;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int q = s < g.nseg ? s : 0;
-            sA[s] = reinterpret_cast<const char*>(static_cast<const bf16_t*>(g.seg[q].A) + (int64_t)t.m0 * lda);
+            sA[s] = reinterpret_cast<const char*>(static_cast<const bf16_t*>(g.seg[q].A) + (RAGK ? (int64_t)t.row0 * lda + t.m0 : (int64_t)t.m0 * lda));
             const bf16_t* b = static_cast<const bf16_t*>(DUAL && s ? g.seg[0].B2 : g.seg[q].B) + eoff;
             sB[s] = reinterpret_cast<const char*>(BT == 1 ? b + (int64_t)t.n0 * ldb : b + t.n0);
         }
@@ -178,7 +238,12 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const int c = wave * 2 + u;
-                {
+                if constexpr (RAGK) {
+                    const int q = c * 4 + (ln >> 4);
+                    int col = h * 128 + ((ln & 15) ^ swz_krow16(q)) * 8;
+                    col = t.m0 + col < g.M ? col : g.M - 8 - t.m0;
+                    a_off[2 * h + u] = ((uint32_t)q * (uint32_t)lda + (uint32_t)col) * 2;
+                } else {
                     const int r = h * 128 + c * 8 + (ln >> 3), last = t.m_lim - 1 - t.m0;
                     const int rl = r < last ? r : last;  // rows past the expert's end: any valid row (masked at the store)
                     a_off[2 * h + u] = ((uint32_t)rl * (uint32_t)lda + ((ln & 7) ^ swz_rows(r)) * 8) * 2;
@@ -196,7 +261,17 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
             }
     };
     // Half `h` of operand A / B at the cursor, chunk u of this wavefront's two.
+    auto k_row = [&](int u) { return (wave * 2 + u) * 4 + (lane >> 4); };  // k-row form: this lane's in the stage
+    auto zeros = [&]() { return reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16; };
     auto issue_a = [&](int h, int u) {
+        if constexpr (RAGK) {
+            const char* base = sA[0] + (int64_t)istage * TK * lda * 2;
+            const uint32_t to = lds_wave + (h ? (ibuf ? kQA1of1 : kQA1of0) : (ibuf ? kQBase1 : kQBase0) + kQA0) + u * 1024;
+            const int left = irows - istage * TK;
+            if (left >= TK) dma16_s(base, a_off[2 * h + u], to);
+            else dma16(k_row(u) < left ? base + a_off[2 * h + u] : zeros(), to);
+            return;
+        }
         const int sg = istage >= nk ? 1 : 0, k0 = (istage - sg * nk) * TK;
         const char* base = (sg ? sA[1] : sA[0]) + (int64_t)k0 * 2;
         const uint32_t to = lds_wave + (h ? (ibuf ? kQA1of1 : kQA1of0) : (ibuf ? kQBase1 : kQBase0) + kQA0) + u * 1024;
@@ -204,25 +279,32 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
             dma16_s(base, a_off[2 * h + u], to);
         } else {  // (K is a multiple of 8: a 16-byte piece is inside or outside as a whole)
             const int r = (wave * 2 + u) * 8 + (lane >> 3);
-            dma16(((lane & 7) ^ swz_rows(r)) * 8 < g.K - k0 ? base + a_off[2 * h + u]
-                                                          : reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16, to);
+            dma16(((lane & 7) ^ swz_rows(r)) * 8 < g.K - k0 ? base + a_off[2 * h + u] : zeros(), to);
         }
     };
     auto issue_b = [&](int h, int u) {
+        if constexpr (RAGK) {
+            const char* base = (DUAL ? sB[h] : sB[0]) + (int64_t)istage * TK * ldb * 2;
+            const uint32_t to = lds_wave + (ibuf ? kQBase1 : kQBase0) + (h ? kQB1 : kQB0) + u * 1024;
+            const int left = irows - istage * TK;
+            if (left >= TK) dma16_s(base, b_off[2 * h + u], to);
+            else dma16(k_row(u) < left ? base + b_off[2 * h + u] : zeros(), to);
+            return;
+        }
         const int sg = istage >= nk ? 1 : 0, k0 = (istage - sg * nk) * TK;
         const char* base = (DUAL ? sB[h] : sg ? sB[1] : sB[0]) + (BT == 1 ? (int64_t)k0 * 2 : (int64_t)k0 * ldb * 2);
         const uint32_t to = lds_wave + (ibuf ? kQBase1 : kQBase0) + (h ? kQB1 : kQB0) + u * 1024;
         if (!KREST || k0 + TK <= g.K) {
             dma16_s(base, b_off[2 * h + u], to);
         } else {
-            const int c = wave * 2 + u, r = c * 8 + (lane >> 3);
-            const int k = BT == 1 ? ((lane & 7) ^ swz_rows(r)) * 8 : c * 4 + (lane >> 4);
-            dma16(k < g.K - k0 ? base + b_off[2 * h + u] : reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16, to);
+            const int r = (wave * 2 + u) * 8 + (lane >> 3);
+            const int k = BT == 1 ? ((lane & 7) ^ swz_rows(r)) * 8 : k_row(u);
+            dma16(k < g.K - k0 ? base + b_off[2 * h + u] : zeros(), to);
         }
     };
     auto advance = [&]() {  // behind the request of A1, a stage's last
         ibuf ^= 1;
-        if (++istage == total) {
+        if (++istage == itotal) {
             istage = 0;
             cursor_to(tile_at(++ipos));
         }
@@ -231,28 +313,29 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     // ================= compute side =================
     const int l16 = lane & 15, kg = lane >> 4;
     const int tr_krow = kg * 8 + (l16 >> 2);          // + ks*32 + t*4: neither changes the swizzle
-    const int tr_col = wn * 32 + (l16 & 3) * 4;       // + j*16: bit 1 of the piece, not the swizzle's to move within a pair
     const int sw = swz_rows(l16);                     // (repeats every 16 rows)
     const int a_rd = (wm * 64 + l16) * 128 + ((kg ^ sw) << 4);  // + i*16 rows; ks flips bit 2 of the piece
-    const int b_rd = BT == 1 ? (wn * 32 + l16) * 128 + ((kg ^ sw) << 4) : tr_krow * 256 + (tr_col & 7) * 2;
+    const int b_rd = (wn * 32 + l16) * 128 + ((kg ^ sw) << 4);
+    auto read_tr = [&](const char* half, int col, int ks) -> bf16x8 {  // 16 columns from `col` on
+        const char* p = half + tr_krow * 256 + ((((col >> 3) + ((l16 & 3) >> 1)) ^ swz_krow16(tr_krow)) << 4) + (l16 & 1) * 8 + ks * 8192;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)p);
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + 1024));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
     auto read_a = [&](const char* half, int i, int ks) -> bf16x8 {
+        if constexpr (RAGK) return read_tr(half, wm * 64 + i * 16, ks);
         return *reinterpret_cast<const bf16x8*>(half + (a_rd ^ (ks << 6)) + i * 2048);
     };
     auto read_b = [&](const char* half, int j, int ks) -> bf16x8 {
-        if constexpr (BT == 1) {
-            return *reinterpret_cast<const bf16x8*>(half + (b_rd ^ (ks << 6)) + j * 2048);
-        } else {
-            const char* p = half + b_rd + ((((tr_col >> 3) + j * 2) ^ swz_krow16(tr_krow)) << 4) + ks * 8192;
-            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)p);
-            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + 1024));
-            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        if constexpr (BT == 1) return *reinterpret_cast<const bf16x8*>(half + (b_rd ^ (ks << 6)) + j * 2048);
+        else return read_tr(half, wn * 32 + j * 16, ks);
     };
     auto barrier = [&]() {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
     int buf = 0;  // the stage buffer of the tile's first stage
+    int pos = 0;  // the tile's entry
     // One tile, of at most 128 rows (HALF) or more.  (The accumulators live in here: shared by both forms they are copied.)
     auto run_tile = [&](auto half_tag, const Tile& t) {
         constexpr bool kHalf = decltype(half_tag)::value != 0;
@@ -342,7 +425,7 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
             asm volatile("" : "+v"(tid));
             const int lane = tid & 63, wave = tid >> 6;
             const int wm = wave >> 2, wn = wave & 3, l16 = lane & 15, kg = lane >> 4;
-            const int64_t tile_base = (int64_t)t.m0 * g.ldc + t.n0;
+            const int64_t tile_base = (RAGK ? (int64_t)t.w * g.strideC : 0) + (int64_t)t.m0 * g.ldc + t.n0;
             uint32_t ldc_u = (uint32_t)g.ldc;  // (opaque per tile, or the store offsets are computed once and kept in scratch)
             asm volatile("" : "+s"(ldc_u));
             auto tile_row = [&](int p, int sr) { return (p >> 1) * 128 + (sr >> 5) * 64 + (p & 1) * 32 + (sr & 31); };
@@ -463,7 +546,11 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                         const int trow = tile_row(i, item >> 4), tcol = col0 + (item & 15) * 8;
                         // (offsets inside a tile fit 32 bits: at most 256 rows of ldc < 2^22 elements)
                         if (t.m0 + trow < t.m_lim && t.n0 + tcol < g.N)
-                            *reinterpret_cast<u32x4*>(dst + tile_base + ((uint32_t)trow * ldc_u + (uint32_t)tcol)) = v[u];
+                        {
+                        u32x4* to = reinterpret_cast<u32x4*>(dst + tile_base + ((uint32_t)trow * ldc_u + (uint32_t)tcol));
+                        if constexpr (STREAM) __builtin_nontemporal_store(v[u], to);
+                        else *to = v[u];
+                    }
                     }
                 };
 #pragma unroll
@@ -494,7 +581,8 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                         }
                     } else {
                         pass(i, [&](int r, int j) { return acc[r][j]; }, static_cast<bf16_t*>(g.C0), 0);
-                        pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C0), 128);
+                        if constexpr (DUAL) pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C1), 0);
+                    else pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C0), 128);
                     }
                 }
                 __syncthreads();  // the staging area has been read: the A1 half under it may be requested
@@ -509,9 +597,16 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int i = 0; i < 4; ++i) read_next(smem + (buf ? kQBase1 : kQBase0), ks, i);
+        const int total = stages_of(t);
         for (int it = 0; it < total; ++it) stage();
+        int drawn = 0;
+        if constexpr (RAGK)
+            if (wave == 0) drawn = draw();  // (arrives under the epilogue)
         // (buf: the buffer of the next tile's first stage; the A1 half that is free is the other one's)
         epilogue(t, smem + (buf ? kQStaging0 : kQStaging1));
+        if constexpr (RAGK)
+            if (wave == 0) place_draw(pos + 2, drawn);
+        if constexpr (EPI != EPI_DH && EPI != EPI_DHP) __syncthreads();  // the staging area has been read: the A1 half under it may be requested
     };
 
     // ================= the tiles of this workgroup =================
@@ -530,12 +625,13 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     issue_first();
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // A0, B0, B1 of stage 0
     barrier();
-    for (int pos = 0;;) {
+    for (;;) {
         if (t.m_lim - t.m0 <= TM / 2) run_tile(IntTag<1>{}, t);
         else run_tile(IntTag<0>{}, t);
         ++pos;
-        if ((pos & 255) == 128 && pos > 256) {  // the half of the ring that no cursor is in
-            if (threadIdx.x < 256) build_entry((pos & ~255) + 256 + threadIdx.x);
+        if (!RAGK && (pos & 255) == 128 && pos > 256) {  // the half of the ring that no cursor is in
+            const int next = (pos & ~255) + 256 + threadIdx.x;
+            if (threadIdx.x < 256) build_entry(next, logical_tile(blockIdx.x + next * gridDim.x));
             __syncthreads();
         }
         t = tile_at(pos);

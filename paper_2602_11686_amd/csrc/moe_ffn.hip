@@ -17,8 +17,7 @@
 //
 // bf16 path: persistent 256x256x64 kernels, 8 wavefronts, fp32 accumulators, operands brought into LDS by DMA in
 // memory order, transposing LDS reads where the contraction index is not the contiguous one: gg_quad_kernel
-// (grouped_gemm_quad.h) for the products over ragged rows, gg256_kernel (grouped_gemm_bf16.h) for those that contract
-// over them.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
+// (grouped_gemm_quad.h), and gg256_kernel (grouped_gemm_bf16.h) for the gradients of few rows.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
 // left for leading dimensions and extents beyond the 32-bit offsets of these.
 // fp32 path: 128x128 or 64x64 tiles on the fp32 matrix instructions, same tile walk and epilogues.
 #include "moe_internal.h"
@@ -607,6 +606,13 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
 // takes 67 us, after plain ones 46.
 static bool stream_gradients(int64_t R, int groups) { return R <= 2048 * (int64_t)groups; }
 
+// Whether a weight gradient's tiles are too short for gg_quad_kernel, which runs at least two k-stages per tile and fills its
+// pipeline first.  A training pass with the gradients on gg256_kernel and on gg_quad_kernel (us; experts of 4096 x 7168 (8),
+// 2048 x 1408 (64), 512 x 768 (32)), by mean rows per expert:
+//   16: 822, 891; 713, 762    64: 1005, 1057; 885, 892; 190, 191    80: 1139, 1137; 953, 949    96: 1222, 1194; 1050, 1021; 199, 198
+//   128: 1278, 1222; 1135, 1102; 203, 204    256: 254, 253 (the smallest)    512: 2183, 2131 (64 experts)    4096: 28203, 27583 (8)
+static bool few_rows_per_tile(int64_t R, int groups) { return R < 80 * (int64_t)groups; }
+
 // workgroups of 256 threads for that many tiles, a multiple of 64 of them; a dimension holds fewer than 2^32 threads
 static dim3 f32_grid(int64_t tiles) {
     constexpr int64_t kMost = 1 << 23;
@@ -635,10 +641,15 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
                     return;
                 }
             } else if (ok) {
-                auto kern = stream_gradients(R, g.E) ? gg256_kernel<AT, BT, DUAL, EPI, RAGK, true>
-                                                     : gg256_kernel<AT, BT, DUAL, EPI, RAGK>;
-                ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGemmLds);
-                kern<<<dim3(256), kThreads, kGemmLds, st>>>(g);
+                auto go = [&](auto kern, int lds) {
+                    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+                    kern<<<dim3(256), kThreads, lds, st>>>(g);
+                };
+                const bool stream = stream_gradients(R, g.E);
+                if (few_rows_per_tile(R, g.E))
+                    go(stream ? gg256_kernel<AT, BT, DUAL, EPI, RAGK, true> : gg256_kernel<AT, BT, DUAL, EPI, RAGK>, kGemmLds);
+                else
+                    go(stream ? gg_quad_kernel<BT, DUAL, EPI, false, true, true> : gg_quad_kernel<BT, DUAL, EPI, false, true>, kQuadLds);
                 return;
             }
         }
