@@ -1,0 +1,218 @@
+// Grouped fp32 GEMM on v_mfma_f32_16x16x4: fp32 operands, products and sums, at twice the rate of the scalar FMA units.
+// Operand forms, tile walk and epilogues as in the bf16 kernels.
+//
+// What bounds it is the matrix pipe (154 TFLOP/s in a loop of these MFMAs alone, 139 at the 2.1 GHz that the power limit
+// leaves a whole kernel), and before that the last tiles: few experts of 64 to 1000 rows make few tiles.  So a workgroup of
+// four wavefronts owns a tile of 64 x 64 only, and a ring of three LDS stages of 32 contraction indices (48 KB, three
+// workgroups per unit), filled by DMA two stages ahead.  A wavefront computes 32 x 32 in 2 x 2 blocks; MFMA z of 16
+// contraction indices contracts z, 4+z, 8+z, 12+z.
+//
+// Measured, training passes (us; 128x128 or 64x64 tiles staged through registers, 16 indices per stage -> this): 2048 tokens, 8
+// experts of 1024 x 2816 2368 -> 2157; 4096 tokens, 4 of 2048 x 5632 8428 -> 7870; 512 tokens, 8 of 1024 x 2816 970 -> 816;
+// 2000 tokens, 24 of 516 x 1036 925 -> 798; forward of 64 tokens, 64 of 2048 x 1408 1230 -> 665, of 8 tokens, 8 of
+// 1024 x 2816 205 -> 142.  80 to 110 TFLOP/s.  Tried: 64 x 128 tiles (-4 to +1.5 %), 128 x 128 with two stages (0 to -18 %), two
+// or four stages (-2 to +1, -3 to -6 %), fragments of the next half stage read under the MFMAs of this one (0).
+//
+// LDS: an operand whose contraction index is contiguous in memory ("row form") lies as [64 rows][128 B], the 16-byte piece
+// p of row r in slot p ^ ((r >> 1) & 7); a lane reads its row's k = 4*(lane/16) .. +3 at once.  An operand whose other index is
+// contiguous ("k-row form") lies as [32 k-rows][256 B], piece p of k-row q in slot p ^ swz_f32(q); a lane reads W neighbouring
+// columns of a k-row at once, one for each of W blocks: block j of those holds columns W*n + j, n = 0 .. 15.
+#pragma once
+
+namespace moe {
+
+constexpr int kF32Tile = 64, kF32K = 32, kF32Stages = 3;
+constexpr int kF32Operand = kF32Tile * kF32K * 4;              // bytes of one operand's stage
+constexpr int kF32Lds = kF32Stages * 2 * kF32Operand;
+
+__device__ __forceinline__ int swz_f32(int q) { return 8 * ((q >> 2) & 1) + 4 * ((q >> 3) & 1); }
+
+// This wavefront's DMA chunks (1 KB) of one operand's stages.
+template <int FORM>  // 0: row form; 1: k-row form
+struct F32Issue {
+    static constexpr int kChunks = kF32Operand / 4096;  // per wavefront and stage
+    static constexpr int kRowPieces = FORM == 0 ? 8 : kF32Tile / 4;
+    const char* at[kChunks];  // this lane's pieces of the next stage
+    int kk[kChunks];          // their contraction index inside the stage
+    int64_t step;             // bytes from one stage to the next
+    // rows (or columns) r0 .. of `base`, those from r_lim on: any valid ones (masked at the store); `split`: from tile column
+    // 32 on they are those of base2
+    __device__ __forceinline__ void set(const float* base, const float* base2, bool split, int64_t ld, int r0, int r_lim, int k0) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        step = (FORM == 0 ? kF32K : kF32K * ld) * 4;
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+            const int p = (wave * kChunks + i) * 64 + lane, line = p / kRowPieces, slot = p % kRowPieces;
+            int r;
+            if constexpr (FORM == 0) {
+                r = line;
+                kk[i] = (slot ^ swz_rows(line)) * 4;
+            } else {
+                r = (slot ^ swz_f32(line)) * 4;
+                kk[i] = line;
+            }
+            const bool second = split && r >= kF32Tile / 2;
+            r = min(r0 + r - (second ? kF32Tile / 2 : 0), FORM == 0 ? r_lim - 1 : r_lim - 4);
+            const float* b = second ? base2 : base;
+            at[i] = reinterpret_cast<const char*>(b + (FORM == 0 ? (int64_t)r * ld + k0 + kk[i] : (int64_t)(k0 + kk[i]) * ld + r));
+        }
+    }
+    // the next stage, of which `left` contraction indices exist; the others read zeros (leading dimensions and extents are
+    // multiples of four: a piece is inside or outside as a whole)
+    __device__ __forceinline__ void issue(uint32_t lds_wave, int left) {
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+            dma16(kk[i] < left ? at[i] : reinterpret_cast<const char*>(kZeroRow) + (threadIdx.x & 31) * 16, lds_wave + i * 1024);
+            at[i] += step;
+        }
+    }
+};
+
+template <int W>
+__device__ __forceinline__ void lds_floats(const char* p, float (&v)[W]) {
+    if constexpr (W == 1) v[0] = *reinterpret_cast<const float*>(p);
+    else if constexpr (W == 2) { const f32x2v x = *reinterpret_cast<const f32x2v*>(p); v[0] = x[0]; v[1] = x[1]; }
+    else { const f32x4v x = *reinterpret_cast<const f32x4v*>(p); for (int j = 0; j < 4; ++j) v[j] = x[j]; }
+}
+
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
+__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GArgs g) {
+    static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
+    using TA = F32Issue<AT>;
+    using TB = F32Issue<BT == 0 ? 1 : 0>;
+    constexpr int BM = kF32Tile, S = kF32Stages;
+    constexpr int NB = BM / 32;              // 16x16 blocks per wavefront along each side
+    constexpr int WB = DUAL ? NB / 2 : NB;   // blocks that share a read of B in k-row form
+    constexpr int kOperand = kF32Operand, kStage = 2 * kOperand;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n_out = DUAL ? BM / 2 : BM;
+    const int n_tiles = (g.N + n_out - 1) / n_out;
+
+    // ---- which tile: chunks of eight neighbouring tiles go to the XCDs in turn (the grid is a multiple of 64) ----
+    // (a second grid dimension where one cannot hold the tiles: f32_grid)
+    const int b0 = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int L = (((b0 >> 6) * 8 + (b0 & 7)) << 3) + ((b0 >> 3) & 7);
+    int e, m0, m_lim, kbeg, kend, m, nt;
+    if constexpr (RAGK) {
+        const int m_tiles = (g.M + BM - 1) / BM, per = m_tiles * n_tiles;
+        if (L >= per * g.E) return;
+        e = g.order ? g.order[L / per] : L / per;  // heaviest experts first
+        walk_tile(L % per, m_tiles, n_tiles, m, nt);
+        m0 = m * BM;
+        m_lim = g.M;
+        kbeg = g.offsets[e];
+        kend = g.offsets[e + 1];
+    } else {
+        int local, b;
+        if (!find_tile<BM>(g, L, n_tiles, e, b, m_lim, local)) return;
+        walk_tile(local, (m_lim - b + BM - 1) / BM, n_tiles, m, nt);
+        m0 = b + m * BM;
+        kbeg = 0;
+        kend = g.K;
+    }
+    const int n0 = nt * n_out;
+
+    // ---- issue side ----
+    const int nk = (kend - kbeg + kF32K - 1) / kF32K, total = nk * g.nseg;
+    const int64_t eoff = RAGK ? 0 : (int64_t)weight_index(g, e) * g.strideB;
+    const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(LDS_AS char*)smem);
+    TA ta;
+    TB tb;
+    auto segment = [&](int sg) {
+        ta.set(static_cast<const float*>(g.seg[sg].A), nullptr, false, g.lda, m0, m_lim, kbeg);
+        tb.set(static_cast<const float*>(g.seg[sg].B) + eoff, DUAL ? static_cast<const float*>(g.seg[sg].B2) + eoff : nullptr,
+               DUAL, g.ldb, n0, g.N, kbeg);
+    };
+    auto issue = [&](int it, int buf) {
+        if (it == nk) segment(1);
+        const int left = kend - kbeg - (it >= nk ? it - nk : it) * kF32K;
+        const uint32_t st = lds_base + buf * kStage + wave * (TA::kChunks * 1024);
+        ta.issue(st, left);
+        tb.issue(st + kOperand, left);
+    };
+    segment(0);
+
+    // ---- compute side ----
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kg = lane >> 4;
+    f32x4v acc[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = (f32x4v){0.f, 0.f, 0.f, 0.f};
+    // v[j][z]: block j's value at k = 16*h + 4*kg + z
+    auto frags = [&](auto form, auto width, const char* s, int first, int h, float (&v)[NB][4]) {
+        constexpr int W = decltype(width)::value;
+        if constexpr (decltype(form)::value == 0) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int r = first + j * 16 + l16;
+                lds_floats<4>(s + r * 128 + (((h * 4 + kg) ^ swz_rows(l16)) << 4), v[j]);  // (swz_rows repeats every 16 rows)
+            }
+        } else {
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+#pragma unroll
+                for (int q = 0; q < NB / W; ++q) {  // (DUAL: q is the matrix)
+                    const int col = q * (BM / 2) + first + l16 * W, k = kg * 4 + z;
+                    float x[W];
+                    lds_floats<W>(s + (h * 16 + k) * (BM * 4) + (((col >> 2) ^ swz_f32(k)) << 4) + (col & 3) * 4, x);
+#pragma unroll
+                    for (int j = 0; j < W; ++j) v[q * W + j][z] = x[j];
+                }
+        }
+    };
+    auto compute = [&](int buf) {
+        const char* sa = smem + buf * kStage;
+        const char* sb = sa + kOperand;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float a[NB][4], b[NB][4];
+            frags(IntTag<AT>{}, IntTag<NB>{}, sa, wm * (BM / 2), h, a);
+            frags(IntTag<BT == 0 ? 1 : 0>{}, IntTag<WB>{}, sb, wn * 16 * WB, h, b);
+            // (B first: blocks are accumulated transposed)
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][z], a[i][z], acc[i][j], 0, 0, 0);
+        }
+    };
+    for (int s = 0; s < S - 1 && s < total; ++s) issue(s, s);
+    int cur = 0, fill = S - 1;  // ring positions of the stage computed and of the one requested next
+    for (int it = 0; it < total; ++it) {
+        // stage `it` has landed (behind it up to S-2 stages are in flight) and this wavefront's LDS reads of the buffer that is
+        // refilled below have returned; the barrier says so for all wavefronts
+        if (it + S - 1 <= total) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * 2 * TA::kChunks) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (it + S - 1 < total) issue(it + S - 1, fill);
+        compute(cur);
+        cur = cur + 1 == S ? 0 : cur + 1;
+        fill = fill + 1 == S ? 0 : fill + 1;
+    }
+
+    // ---- epilogue: a lane holds, of each of its rows, quads of four consecutive columns ----
+    const int64_t cbase = RAGK ? (int64_t)e * g.strideC : 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int row = m0 + wm * (BM / 2) + (AT == 0 ? i * 16 + l16 : l16 * NB + i);
+        auto quad = [&](int q, int t) {  // matrix q, quad t
+            if constexpr (BT == 1) return acc[i][t];
+            f32x4v v;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) v[z] = acc[i][q * WB + (4 * t + z) % WB][(4 * t + z) / WB];
+            return v;
+        };
+#pragma unroll
+        for (int t = 0; t < WB; ++t) {
+            const int col = n0 + wn * 16 * WB + (BT == 1 ? t * 16 + kg * 4 : kg * 4 * WB + t * 4);
+            if (row < m_lim && col < g.N)
+                epilogue_x4<float, EPI>(g, cbase + (int64_t)row * g.ldc + col, quad(0, t), quad(DUAL ? 1 : 0, t));
+        }
+    }
+}
+
+}  // namespace moe

@@ -19,7 +19,7 @@
 // memory order, transposing LDS reads where the contraction index is not the contiguous one: gg_quad_kernel
 // (grouped_gemm_quad.h), and gg256_kernel (grouped_gemm_bf16.h) for the gradients of few rows.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
 // left for leading dimensions and extents beyond the 32-bit offsets of these.
-// fp32 path: 128x128 or 64x64 tiles on the fp32 matrix instructions, same tile walk and epilogues.
+// fp32 path: 64x64 tiles on the fp32 matrix instructions (grouped_gemm_f32.h), same tile walk and epilogues.
 #include "moe_internal.h"
 
 namespace moe {
@@ -381,177 +381,9 @@ __device__ __forceinline__ void epilogue_x4(const GArgs& g, int64_t idx, const f
 #include "grouped_gemm_few_rows.h"
 namespace moe {
 
-// =============================== fp32 path ====================================
-// v_mfma_f32_16x16x4: fp32 operands, products and sums, at twice the rate of the scalar FMA units.  What bounds
-// these products is the matrix pipe (154 TFLOP/s measured for a large fp32 product of the library): a stage of
-// 16 contraction indices keeps a SIMD busy for 2048 clocks, so a plain register-staged double buffer in LDS
-// hides its loads.  BM x BM workgroup tiles, four wavefronts of BM/2 x BM/2, in 16x16 blocks.
-//
-// LDS: an operand whose contraction index is contiguous in memory is kept as [row][16 + 4 pad]; a lane reads its
-// row's four values k = 4*(lane/16) .. +3 with one ds_read_b128 (16 rows at a stride of 5 pieces: no conflict)
-// and the four MFMAs of a stage take one of them each, so MFMA i contracts k = i, 4+i, 8+i, 12+i.  An operand
-// whose other index is contiguous is kept as [k][BM + 4]; the same four values are four ds_read_b32, whose
-// lane groups start 16 banks apart (4*(BM + 4) mod 64 == 16).
-//
-// Measured on 4096 rows x 1024 x 2816 over 8 skewed experts, against 64x64 tiles on the scalar FMA units with the
-// same operands (us): forward 1 1155 -> 525, forward 2 773 -> 303, dgrad 1 618 -> 337, dgrad 2 1604 -> 604,
-// wgrad 2 658 -> 235, wgrad 1 1041 -> 441 (70 to 110 TFLOP/s; addresses formed anew for every piece of every stage
-// cost 3 to 5 % of that).
-template <int BM, int FORM>  // FORM 0: [row][k], k contiguous in memory; 1: [k][row]
-struct F32Tile {
-    static constexpr int kK = 16;                               // contraction indices per stage
-    static constexpr int kLd = FORM == 0 ? kK + 4 : BM + 4;
-    static constexpr int kFloats = FORM == 0 ? BM * kLd : kK * kLd;
-    static constexpr int kPieces = BM * kK / 4 / 256;           // 16-byte pieces per thread and stage
-    // This thread's pieces of a stage: addresses at k = k0 of the operand's rows r0 .. (rows past r_lim: any valid one,
-    // masked at the store) and the k inside the stage.  `split`: tile rows from BM/2 on come from base2.
-    const float* at[kPieces];
-    int kk[kPieces];
-    int64_t step;  // floats from one stage to the next
-    __device__ __forceinline__ void set(const float* base, const float* base2, bool split, int64_t ld, int r0, int r_lim, int k0) {
-        step = FORM == 0 ? kK : kK * ld;
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int p = threadIdx.x + i * 256;
-            int r = FORM == 0 ? p / (kK / 4) : (p % (BM / 4)) * 4;
-            kk[i] = FORM == 0 ? (p % (kK / 4)) * 4 : p / (BM / 4);
-            const bool second = split && r >= BM / 2;
-            r = min(r0 + r - (second ? BM / 2 : 0), FORM == 0 ? r_lim - 1 : r_lim - 4);
-            at[i] = (second ? base2 : base) + (FORM == 0 ? (int64_t)r * ld + k0 + kk[i] : (int64_t)(k0 + kk[i]) * ld + r);
-        }
-    }
-    // the next stage, of which `left` contraction indices exist; the others read zeros (leading dimensions and extents
-    // are multiples of four: a piece is inside or outside as a whole)
-    __device__ __forceinline__ void load(f32x4v (&v)[kPieces], int left) {
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            v[i] = *reinterpret_cast<const f32x4v*>(kk[i] < left ? at[i] : reinterpret_cast<const float*>(kZeroRow));
-            at[i] += step;
-        }
-    }
-    static __device__ __forceinline__ void store(float* s, const f32x4v (&v)[kPieces]) {
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int p = threadIdx.x + i * 256;
-            const int off = FORM == 0 ? p / (kK / 4) * kLd + p % (kK / 4) * 4 : p / (BM / 4) * kLd + p % (BM / 4) * 4;
-            *reinterpret_cast<f32x4v*>(s + off) = v[i];
-        }
-    }
-    // the values of tile row `row` (a lane's own) at k = 4*kg .. 4*kg+3
-    static __device__ __forceinline__ f32x4v frag(const float* s, int row, int kg) {
-        if constexpr (FORM == 0) return *reinterpret_cast<const f32x4v*>(s + row * kLd + kg * 4);
-        f32x4v v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = s[(kg * 4 + i) * kLd + row];
-        return v;
-    }
-};
-
-template <int AT, int BT, bool DUAL, int EPI, bool RAGK, int BM>
-__global__ __launch_bounds__(256) void gg_f32_kernel(const GArgs g) {
-    static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
-    using TA = F32Tile<BM, AT>;
-    using TB = F32Tile<BM, BT == 0 ? 1 : 0>;
-    constexpr int NB = BM / 32;          // 16x16 blocks per wavefront along each side
-    constexpr int kK = TA::kK;
-    __shared__ __attribute__((aligned(16))) float sA[2][TA::kFloats], sB[2][TB::kFloats];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n_out = DUAL ? BM / 2 : BM;
-    const int n_tiles = (g.N + n_out - 1) / n_out;
-
-    // ---- which tile: chunks of eight neighbouring tiles go to the XCDs in turn (the grid is a multiple of 64) ----
-    // (a second grid dimension where one cannot hold the tiles: f32_grid)
-    const int b0 = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int L = (((b0 >> 6) * 8 + (b0 & 7)) << 3) + ((b0 >> 3) & 7);
-    int e, m0, m_lim, kbeg, kend, m, nt;
-    if constexpr (RAGK) {
-        const int m_tiles = (g.M + BM - 1) / BM, per = m_tiles * n_tiles;
-        if (L >= per * g.E) return;
-        e = g.order ? g.order[L / per] : L / per;  // heaviest experts first
-        walk_tile(L % per, m_tiles, n_tiles, m, nt);
-        m0 = m * BM;
-        m_lim = g.M;
-        kbeg = g.offsets[e];
-        kend = g.offsets[e + 1];
-    } else {
-        int local, b;
-        if (!find_tile<BM>(g, L, n_tiles, e, b, m_lim, local)) return;
-        walk_tile(local, (m_lim - b + BM - 1) / BM, n_tiles, m, nt);
-        m0 = b + m * BM;
-        kbeg = 0;
-        kend = g.K;
-    }
-    const int n0 = nt * n_out;
-
-    const int wm = (wave >> 1) * (BM / 2), wn = wave & 1;
-    const int l16 = lane & 15, kg = lane >> 4;
-    auto b_row = [&](int j) {  // tile column of block j: with two matrices, blocks NB/2 .. are the second one's
-        return DUAL ? (j / (NB / 2)) * (BM / 2) + wn * (BM / 4) + (j % (NB / 2)) * 16 : wn * (BM / 2) + j * 16;
-    };
-    f32x4v acc[NB][NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = (f32x4v){0.f, 0.f, 0.f, 0.f};
-
-    const int nk = (kend - kbeg + kK - 1) / kK, total = nk * g.nseg;
-    f32x4v ra[TA::kPieces], rb[TB::kPieces];
-    const int64_t eoff = RAGK ? 0 : (int64_t)weight_index(g, e) * g.strideB;
-    TA ta;
-    TB tb;
-    auto segment = [&](int sg) {
-        ta.set(static_cast<const float*>(g.seg[sg].A), nullptr, false, g.lda, m0, m_lim, kbeg);
-        tb.set(static_cast<const float*>(g.seg[sg].B) + eoff, DUAL ? static_cast<const float*>(g.seg[sg].B2) + eoff : nullptr,
-               DUAL, g.ldb, n0, g.N, kbeg);
-    };
-    auto gload = [&](int it) {
-        if (it == nk) segment(1);
-        const int left = kend - kbeg - (it >= nk ? it - nk : it) * kK;
-        ta.load(ra, left);
-        tb.load(rb, left);
-    };
-    segment(0);
-    if (total > 0) {
-        gload(0);
-        TA::store(sA[0], ra);
-        TB::store(sB[0], rb);
-    }
-    __syncthreads();
-    for (int it = 0; it < total; ++it) {
-        const bool more = it + 1 < total;
-        if (more) gload(it + 1);
-        const float* a_s = sA[it & 1];
-        const float* b_s = sB[it & 1];
-        f32x4v a[NB], b[NB];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) a[i] = TA::frag(a_s, wm + i * 16 + l16, kg);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) b[j] = TB::frag(b_s, b_row(j) + l16, kg);
-        // (B first: blocks are accumulated transposed, a lane then holds four consecutive columns of one row)
-#pragma unroll
-        for (int z = 0; z < 4; ++z)
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][z], a[i][z], acc[i][j], 0, 0, 0);
-        if (more) {
-            TA::store(sA[(it + 1) & 1], ra);
-            TB::store(sB[(it + 1) & 1], rb);
-        }
-        __syncthreads();
-    }
-    const int64_t cbase = RAGK ? (int64_t)e * g.strideC : 0;
-    constexpr int NJ4 = DUAL ? NB / 2 : NB;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ4; ++j) {
-            const int row = m0 + wm + i * 16 + l16, col = n0 + b_row(j) + kg * 4;
-            if (row < m_lim && col < g.N)
-                epilogue_x4<float, EPI>(g, cbase + (int64_t)row * g.ldc + col, acc[i][j], acc[i][DUAL ? j + NB / 2 : j]);
-        }
-}
+}  // namespace moe
+#include "grouped_gemm_f32.h"
+namespace moe {
 
 // =============================== host dispatch ================================
 // Few rows per expert: the kernel of grouped_gemm_few_rows.h where it is the faster one.  The rows of each expert are
@@ -620,6 +452,13 @@ static dim3 f32_grid(int64_t tiles) {
     return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
 }
 
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
+static void launch_f32(const GArgs& g, int64_t tiles, hipStream_t st) {
+    auto kern = gg_f32_kernel<AT, BT, DUAL, EPI, RAGK>;
+    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kF32Lds);
+    kern<<<f32_grid(tiles), 256, kF32Lds, st>>>(g);
+}
+
 // A(m,k) layout AT, B(k,n) layout BT as in the bf16 kernel.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t st) {
@@ -658,16 +497,10 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
         else grid = dim3((g.N + BN - 1) / BN, (unsigned)((R + BM - 1) / BM + g.E), 1);
         gg_bf16_kernel<AT, BT, DUAL, EPI, RAGK><<<grid, 256, 0, st>>>(g);
     } else {
-        // 128x128 tiles unless they are too few to give every compute unit two, then 64x64 (the products of 512 rows
-        // x 128 x 256 over 8 experts: 27-81 us with scalar 64x64 tiles, 10-21 us with these)
-        auto tiles = [&](int64_t bm) {
-            const int64_t n = (g.N + (DUAL ? bm / 2 : bm) - 1) / (DUAL ? bm / 2 : bm);
-            return n * (RAGK ? (g.M + bm - 1) / bm * g.E : (R + bm - 1) / bm + g.E);  // (upper bound with ragged M)
-        };
-        const bool small = tiles(128) < 512;
-        const dim3 grid = f32_grid(tiles(small ? 64 : 128));
-        if (small) gg_f32_kernel<AT, BT, DUAL, EPI, RAGK, 64><<<grid, 256, 0, st>>>(g);
-        else gg_f32_kernel<AT, BT, DUAL, EPI, RAGK, 128><<<grid, 256, 0, st>>>(g);
+        const int64_t n_tiles = (g.N + (DUAL ? kF32Tile / 2 : kF32Tile) - 1) / (DUAL ? kF32Tile / 2 : kF32Tile);
+        const int64_t m_tiles = RAGK ? (int64_t)((g.M + kF32Tile - 1) / kF32Tile) * g.E
+                                     : (R + kF32Tile - 1) / kF32Tile + g.E;  // (upper bound with ragged M)
+        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, n_tiles * m_tiles, st);
     }
 }
 
@@ -693,7 +526,7 @@ void launch_gate_dwg_gemm_f32(const void* x, const void* dl, const int32_t* chun
     g.lda = d; g.ldb = n_pad; g.strideC = (int64_t)d * n_pad;
     g.C0 = partial; g.ldc = n_pad;
     const int64_t tiles = (int64_t)((n_pad + 63) / 64) * ((d + 63) / 64) * nchunks;
-    gg_f32_kernel<1, 0, false, EPI_STORE, true, 64><<<f32_grid(tiles), 256, 0, st>>>(g);
+    launch_f32<1, 0, false, EPI_STORE, true>(g, tiles, st);
 }
 
 void launch_gate_dx_gemm(const void* dl_hi, const void* dl_lo, const void* wg_pad, const int32_t* whole, int d, int n_pad,

@@ -79,6 +79,13 @@ def test_ffn_f32(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 7 * d + f)
 
 
+# fp32, a ring of three 32-wide k-stages: none to five of them in either contraction, with every kind of remainder
+@pytest.mark.parametrize("counts,d,f", [((28, 32, 36, 0), 32, 64), ((64, 68, 96, 1), 96, 28), ((4, 31, 33, 160), 100, 128),
+                                        ((130, 3), 36, 160)])
+def test_ffn_f32_stages(counts, d, f):
+    check_ffn(counts, d, f, torch.float32, 5 * d + f)
+
+
 # fp32, 128x128 tiles: at least 512 of them in every product (an upper bound with ragged rows, as the dispatch counts them)
 def test_ffn_f32_large_tiles():
     counts, d, f = (0, 1, 127, 128, 129, 300, 17, 64) * 25, 260, 264
