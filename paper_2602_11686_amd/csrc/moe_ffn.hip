@@ -518,6 +518,113 @@ void launch_gate_dwg_gemm(const void* x, const void* dl_hi, const void* dl_lo, c
     kern<<<dim3(256), kThreads, kGemmLds, st>>>(g);
 }
 
+// dW_g of bf16 layers: partial[c][m][n] as in launch_gate_dwg_gemm, n_out columns per row.
+//
+// What bounds it is reading the tokens, so they are read once (hi and lo meet the same fragments), in tiles of 128 columns of
+// x by 64 experts, and there are as many chunks of tokens as it takes to fill the chip.  Four wavefronts of 32 columns each;
+// 64-token stages in a ring of two, 32 KB each: x as [64 tokens][256 B] (swz_krow16), hi and lo as [64 tokens][128 B]
+// (swz_few_krow), all read transposed.
+//
+// Measured (us, on 256x256 tiles of gg256_kernel with x read for hi and again for lo, 512 tokens a chunk -> this): 16384 tokens
+// of 4096 over 8 experts 85 -> 37 (3.7 TB/s), of 2048 over 128 57 -> 35, 4099 of 1096 over 24 38 -> 9, 4096 of 512 over 32
+// 33 -> 5.
+constexpr int kDwgM = 128, kDwgN = 64, kDwgStage = 64 * kDwgM * 2 + 2 * 64 * kDwgN * 2, kDwgStages = 2;
+constexpr int kDwgLds = kDwgStages * kDwgStage;
+__global__ __launch_bounds__(256) void gate_dwg_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ hi,
+                                                       const bf16_t* __restrict__ lo, const int32_t* __restrict__ chunk_offsets,
+                                                       int d, int n_pad, int n_out, float* __restrict__ partial) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int m0 = blockIdx.x * kDwgM, n0 = blockIdx.y * kDwgN, c = blockIdx.z;
+    const int t0 = chunk_offsets[c], tokens = chunk_offsets[c + 1] - t0, total = (tokens + 63) / 64;
+    const int nb = min(kDwgN, n_out - n0) / 16;  // blocks of 16 experts
+    const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(LDS_AS char*)smem);
+    const char* zeros = reinterpret_cast<const char*>(kZeroRow) + (lane & 31) * 16;
+    // this wavefront's DMA chunks: 4 of x (4 tokens each), 2 of hi and 2 of lo (8 tokens each)
+    const char *xa[4], *ha[2], *la[2];
+    int xq[4], hq[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        xq[i] = (wave * 4 + i) * 4 + (lane >> 4);
+        const int col = min(m0 + ((lane & 15) ^ swz_krow16(xq[i])) * 8, d - 8);  // (columns past the end: any; not stored)
+        xa[i] = reinterpret_cast<const char*>(x + (int64_t)(t0 + xq[i]) * d + col);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        hq[i] = (wave * 2 + i) * 8 + (lane >> 3);
+        const int64_t off = (int64_t)(t0 + hq[i]) * n_pad + n0 + ((lane & 7) ^ swz_few_krow(hq[i])) * 8;
+        ha[i] = reinterpret_cast<const char*>(hi + off);
+        la[i] = reinterpret_cast<const char*>(lo + off);
+    }
+    auto issue = [&](int it) {
+        const uint32_t st = lds_base + (it & 1) * kDwgStage;
+        const int left = tokens - it * 64;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dma16(xq[i] < left ? xa[i] : zeros, st + (wave * 4 + i) * 1024);
+            xa[i] += (int64_t)64 * d * 2;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            dma16(hq[i] < left ? ha[i] : zeros, st + 16384 + (wave * 2 + i) * 1024);
+            dma16(hq[i] < left ? la[i] : zeros, st + 24576 + (wave * 2 + i) * 1024);
+            ha[i] += (int64_t)64 * n_pad * 2;
+            la[i] += (int64_t)64 * n_pad * 2;
+        }
+    };
+    const int l16 = lane & 15, kg = lane >> 4, q = kg * 8 + (l16 >> 2), half = (l16 & 3) >> 1;
+    auto pair = [](const char* p, int step) -> bf16x8 {
+        const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)p);
+        const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + step));
+        return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    f32x4v acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = (f32x4v){0.f, 0.f, 0.f, 0.f};
+    if (total > 0) issue(0);
+    for (int it = 0; it < total; ++it) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (it + 1 < total) issue(it + 1);
+        const char* s = smem + (it & 1) * kDwgStage;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                a[i] = pair(s + (ks * 32 + q) * 256 + (((wave * 4 + i * 2 + half) ^ swz_krow16(q)) << 4) + (l16 & 1) * 8, 1024);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j >= nb) break;
+                const char* p = s + 16384 + (ks * 32 + q) * 128 + (((j * 2 + half) ^ swz_few_krow(q)) << 4) + (l16 & 1) * 8;
+                const bf16x8 h = pair(p, 512), l = pair(p + 8192, 512);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h, a[i], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, a[i], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = m0 + wave * 32 + i * 16 + l16;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j < nb && m < d) *reinterpret_cast<f32x4v*>(partial + ((int64_t)c * d + m) * n_out + n0 + j * 16 + kg * 4) = acc[i][j];
+    }
+}
+
+void launch_gate_dwg(const void* x, const void* dl_hi, const void* dl_lo, const int32_t* chunk_offsets, int nchunks, int d,
+                     int n_pad, int n_out, float* partial, hipStream_t st) {
+    ensure_dynamic_lds(reinterpret_cast<const void*>(&gate_dwg_kernel), kDwgLds);
+    gate_dwg_kernel<<<dim3((d + kDwgM - 1) / kDwgM, (n_out + kDwgN - 1) / kDwgN, nchunks), 256, kDwgLds, st>>>(
+        static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(dl_hi), static_cast<const bf16_t*>(dl_lo), chunk_offsets, d,
+        n_pad, n_out, partial);
+}
+
 void launch_gate_dwg_gemm_f32(const void* x, const void* dl, const int32_t* chunk_offsets, int nchunks, int d, int n_pad,
                               float* partial, hipStream_t st) {
     GArgs g{};

@@ -437,12 +437,20 @@ static void launch_gate_bwd_dx(T* dx, const float* wgT, const int32_t* ids, cons
 
 // ---- dW_g through the grouped GEMM -----------------------------------------------------------
 // dL is written out densely (bf16 layers: as two bf16 matrices hi + lo, the pair carries 16 mantissa bits
-// of the fp32 value), tokens are cut into chunks, each chunk's X^T * dL is one
-// ragged-K GEMM group, and the chunk partials are added in chunk order.
-// (512 tokens, or more for very long batches: the GEMM's group table holds MOE_MAX_EXPERTS groups)
-static inline int mma_chunk_tokens(int Tn) {
-    const int need = (Tn + MOE_MAX_EXPERTS - 1) / MOE_MAX_EXPERTS;
-    return need <= 512 ? 512 : (need + 31) / 32 * 32;
+// of the fp32 value), tokens are cut into chunks, each chunk's X^T * dL is a product of its own,
+// and the chunk partials are added in chunk order.
+// The product runs on gate_dwg_kernel, but for many experts and many tokens on the grouped GEMM, whose 256-wide tiles they
+// fill.  Training passes on either (us, grouped GEMM -> gate_dwg_kernel): 160 experts, 512, 4096 and 16384 tokens 441 -> 400,
+// 1374 -> 1339, 2722 -> 2659; 256 experts, 1000 and 8192 tokens 801 -> 757, 2783 -> 2771 (within the spread).
+static inline bool dwg_tokens_once(const moe_shape* s) { return s->E <= 192 || s->T <= 4096; }
+// 512 tokens (or more for very long batches: the GEMM's group table holds MOE_MAX_EXPERTS groups); gate_dwg_kernel: halved
+// while its 128 x 64 tiles of all chunks are too few to give every compute unit two
+static inline int mma_chunk_tokens(const moe_shape* s) {
+    const int need = (s->T + MOE_MAX_EXPERTS - 1) / MOE_MAX_EXPERTS;
+    int c = need <= 512 ? 512 : (need + 63) / 64 * 64;
+    const int64_t tiles = (int64_t)((s->d + 127) / 128) * ((s->E + 63) / 64);
+    while (dwg_tokens_once(s) && c > 64 && c % 128 == 0 && (s->T + c - 1) / c * tiles < 512) c /= 2;
+    return c;
 }
 // fp32: 256 tokens, halved while the 64x64 tiles of all chunks are too few to give every compute unit two
 static inline int f32_chunk_tokens(const moe_shape* s) {
@@ -453,7 +461,8 @@ static inline int f32_chunk_tokens(const moe_shape* s) {
 }
 static inline int f32_chunks(const moe_shape* s) { const int c = f32_chunk_tokens(s); return (s->T + c - 1) / c; }
 static inline int pad4(int v) { return (v + 3) / 4 * 4; }
-static inline int mma_chunks(int Tn) { const int c = mma_chunk_tokens(Tn); return (Tn + c - 1) / c; }
+static inline int mma_chunks(const moe_shape* s) { const int c = mma_chunk_tokens(s); return (s->T + c - 1) / c; }
+static inline int pad16(int v) { return (v + 15) / 16 * 16; }
 static inline int pad64(int v) { return (v + 63) / 64 * 64; }  // the dense dL is a K operand: whole 64-wide k-stages
 
 // workgroups in a grid whose first dimension stays below 2^32 threads
@@ -531,7 +540,7 @@ size_t gate_bwd_workspace_bytes(const moe_shape* s) {
     size_t b = align_up((size_t)pad64(s->E) * s->d * 4, 256);          // wgT (fp32), or the padded bf16 gate weight
     b += align_up((size_t)s->T * s->k * 4, 256);                       // dl
     const bool f32 = s->dtype == MOE_F32;
-    const int nch = f32 ? f32_chunks(s) : mma_chunks(s->T);
+    const int nch = f32 ? f32_chunks(s) : mma_chunks(s);
     b += align_up((size_t)nch * s->d * (f32 ? pad4(s->E) : pad64(s->E)) * 4, 256);  // partial sums
     b += 2 * align_up((size_t)s->T * pad64(s->E) * 2, 256);             // dense dL, hi and lo (or fp32)
     b += align_up((size_t)(nch + 1) * 4, 256) + 512 + 256;  // token chunk offsets, a row of zeros, {0, T}
@@ -606,7 +615,8 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     float* wgT = static_cast<float*>(cv.take((size_t)pad64(s->E) * s->d * 4));  // fp32 transpose, or the padded bf16 copy
     float* dl = static_cast<float*>(cv.take((size_t)s->T * s->k * 4));
     const bool f32 = sizeof(T) == 4;
-    const int n_pad = f32 ? pad4(s->E) : pad64(s->E), nch = f32 ? f32_chunks(s) : mma_chunks(s->T);
+    const int n_pad = f32 ? pad4(s->E) : pad64(s->E), nch = f32 ? f32_chunks(s) : mma_chunks(s);
+    const int n_out = !f32 && dwg_tokens_once(s) ? pad16(s->E) : n_pad;  // columns of the partial sums
     float* partial = static_cast<float*>(cv.take((size_t)nch * s->d * n_pad * 4));
     T* hi = static_cast<T*>(cv.take((size_t)s->T * n_pad * sizeof(T)));
     T* lo = f32 ? nullptr : static_cast<T*>(cv.take((size_t)s->T * n_pad * sizeof(T)));
@@ -614,7 +624,7 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     uint32_t* zero_row = static_cast<uint32_t*>(cv.take(512));
     int32_t* whole = static_cast<int32_t*>(cv.take(256));
     gate_dl_dense_kernel<T><<<token_grid(((int64_t)s->T + 3) / 4), 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch,
-                                                            f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s->T), zero_row, whole);
+                                                            f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s), zero_row, whole);
     if (dx && !f32 && s->k >= 4) {
         // dx += dL * W_g^T as a GEMM over the dense (hi + lo) dL: reads and writes dx once; the gate
         // weight stays in bf16 (padded to whole k-stages in the space of the fp32 transpose).  The
@@ -630,8 +640,9 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     // (fp32, 256 tokens x 128: 112 us with one thread per column and a serial walk of the tokens, 4 us here;
     // 2048 tokens x 1024: 134 us and 7 us)
     if (f32) launch_gate_dwg_gemm_f32(x, hi, coff, nch, s->d, n_pad, partial, st);
+    else if (dwg_tokens_once(s)) launch_gate_dwg(x, hi, lo, coff, nch, s->d, n_pad, n_out, partial, st);
     else launch_gate_dwg_gemm(x, hi, lo, coff, nch, s->d, n_pad, partial, zero_row, st);
-    gate_bwd_dwg_reduce_kernel<<<256, 256, 0, st>>>(partial, dwg, nch, s->d, s->E, n_pad);
+    gate_bwd_dwg_reduce_kernel<<<256, 256, 0, st>>>(partial, dwg, nch, s->d, s->E, n_out);
     return launch_status("moe_gate_topk_bwd");
 }
 

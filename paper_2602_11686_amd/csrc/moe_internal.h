@@ -51,6 +51,10 @@ size_t gate_bwd_workspace_bytes(const moe_shape* s);
 void launch_gate_dwg_gemm(const void* x, const void* dl_hi, const void* dl_lo, const int32_t* chunk_offsets,
                           int nchunks, int d, int n_pad, float* partial, const void* zero_row, hipStream_t st);
 
+// the same with the tokens read once: n_out columns per row of the partial sums (a multiple of 16, at most n_pad)
+void launch_gate_dwg(const void* x, const void* dl_hi, const void* dl_lo, const int32_t* chunk_offsets, int nchunks, int d,
+                     int n_pad, int n_out, float* partial, hipStream_t st);
+
 // the same in fp32: dl [T][n_pad], n_pad a multiple of four
 void launch_gate_dwg_gemm_f32(const void* x, const void* dl, const int32_t* chunk_offsets, int nchunks, int d, int n_pad,
                               float* partial, hipStream_t st);

@@ -129,3 +129,25 @@ def test_gate_bwd_more_tokens_than_a_grid_dimension():
     # fp32 partial sums of 2^18 chunks added one after the other: their roundings, 2^-24 of the running sum each, add up
     # like a random walk to 2^9 * 2^-24 of it
     assert float((dwg.double() - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
+
+
+# the gate weight's gradient: token chunks of 64 to 512 (one token, a stage, its neighbours, several chunks with a rest), tiles of
+# 128 columns and their remainders, 16-expert blocks and 64-expert tiles, and the grouped GEMM (many experts and tokens)
+@pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (63, 120, 15, 2), (64, 128, 16, 3), (65, 136, 17, 4), (129, 264, 64, 1),
+                                     (700, 1096, 65, 6), (300, 520, 130, 8), (2049, 640, 100, 2), (4097, 136, 200, 4),
+                                     (20000, 4096, 8, 2)])
+def test_gate_weight_gradient_edges(T, d, E, k):
+    """Against 64 bits.  The gradient of a logit enters as a pair of bf16 values (2^-17 of it is lost), sums are in fp32:
+    1e-5 of the result's 2-norm."""
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    s = B.Shape(T, d, 8, E, k, torch.bfloat16)
+    x = torch.empty(T, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    wg = torch.empty(d, E, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
+    ids = torch.rand(T, E, device="cuda", generator=g).topk(k, 1).indices.int().contiguous()
+    w, dw = torch.softmax(torch.randn(T, k, device="cuda", generator=g), 1), torch.randn(T, k, device="cuda", generator=g)
+    dwg = torch.full((d, E), float("nan"), device="cuda")
+    ws = torch.full((B.moe_workspace_bytes(s),), 255, dtype=torch.uint8, device="cuda")   # (NaNs in whatever is not written)
+    B.moe_gate_topk_bwd(s, x, wg, ids, w, dw, None, dwg, ws)
+    dl = w.double() * (dw.double() - (w.double() * dw.double()).sum(1, keepdim=True))
+    want = x.double().T @ torch.zeros(T, E, dtype=torch.float64, device="cuda").scatter_(1, ids.long(), dl)
+    assert float((dwg.double() - want).norm()) <= 1e-5 * float(want.norm()) + 1e-30
