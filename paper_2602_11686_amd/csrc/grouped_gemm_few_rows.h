@@ -1,12 +1,12 @@
 // Grouped bf16 GEMM for experts with few rows (decode steps, short batches): the weights are the work.
 //
-//   C[m,n] = sum_k A(m,k) * B(k,n) per expert, ragged M, the operand forms and epilogues of gg256_kernel
+//   C[m,n] = sum_k A(m,k) * B(k,n) per expert, ragged M, the operand forms and epilogues of gg_quad_kernel
 //
 // What bounds it is how fast the weights arrive from HBM, so the tile is chosen for loads in flight: a workgroup
 // of four wavefronts owns BM rows x 64 columns (per B matrix, or two column blocks of 64: NB = 2) and streams its B
 // columns in 64-wide k-stages through a ring of S LDS buffers, filled by DMA S-1 stages ahead, and the number of tiles is
-// several times the number of units where gg256_kernel has too few 256-wide ones.  Every B request takes whole 128-byte
-// lines.  Workgroups per unit and weights in flight on it (gg256_kernel: one stage of 32 KB), by instance <BM, NB, S>:
+// several times the number of units where gg_quad_kernel has too few 256-wide ones.  Every B request takes whole 128-byte
+// lines.  Workgroups per unit and weights in flight on it (gg_quad_kernel: two stages of 32 KB), by instance <BM, NB, S>:
 //   <64,2,3> 2, 64 KB    <64,1,3> 3, 48 KB    <128,2,2> 2, 32 KB    <128,1,3> 2, 32 KB    <128,2,3> 1, 32 KB
 // Weights are requested non-temporally where one row tile uses them.  An expert's second row tile runs beside the first
 // on the same XCD, but finds such lines in its L2 only in part (bytes fetched past L2 over the weights' own: 96 rows in

@@ -66,18 +66,26 @@ static_assert(kQuadLds <= kLdsBytes, "fits the unit's LDS");
 // q+3 and q+8 .. q+11, which this spreads over all 64 banks
 __device__ __forceinline__ int swz_krow16(int q) { return 2 * ((q & 3) | (((q >> 3) & 1) << 2)); }
 
+// dma16_s for what is read once: non-temporal
+__device__ __forceinline__ void dma16_s_stream(const void* sbase, uint32_t voff, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(voff), "s"(sbase)
+                 : "memory", "m0");
+}
+
 // KREST: K is no multiple of 64 (the last stage of a segment reads zeros past it); an instance of its own.
 //
-// RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).  STREAM (RAGK): C is stored non-temporally (an
-// instance of its own: of two stores behind a test at run time the compiler makes one plain store).
+// RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).  STREAM, RAGK: C is stored non-temporally (an
+// instance of its own: of two stores behind a test at run time the compiler makes one plain store).  STREAM, ragged M: the
+// weights of experts with a single row tile, which nobody else reads, are requested non-temporally.
 template <int BT, bool DUAL, int EPI, bool KREST, bool RAGK = false, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
-    static_assert(RAGK ? BT == 0 && !KREST && (EPI == EPI_STORE || EPI == EPI_STORE2) : !STREAM && EPI != EPI_STORE2, "forms");
+    static_assert(RAGK ? BT == 0 && !KREST && (EPI == EPI_STORE || EPI == EPI_STORE2) : EPI != EPI_STORE2 && !(KREST && STREAM), "forms");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kQTableOff);  // [E+1] rows of each expert
     int32_t* t_pref = t_off + MOE_MAX_EXPERTS + 1;                   // [E+1] tiles before expert e
-    // the workgroup's tiles: index of the weights (-1: no more tiles), m0, m_lim, n0; ragged K: expert, m0, its first row, n0
+    // the workgroup's tiles: index of the weights (-1: no more tiles), m0, m_lim (STREAM: negated where nobody else reads the
+    // weights), n0; ragged K: expert, m0, its first row, n0
     int4* list = reinterpret_cast<int4*>(smem + kQListOff);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave >> 2, wn = wave & 3;
@@ -157,6 +165,7 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                 }
                 d.w = nt * n_out;
                 if (d.y < d.z) d.x = weight_index(g, lo);
+                if (STREAM && en - b <= (part < 0 ? TM : TM / 2)) d.z = -d.z;
             }
         }
         list[pos & (kQList - 1)] = d;
@@ -193,15 +202,19 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     struct Tile {
         int w, m0, m_lim, n0;  // w: index of the weights, or of the result
         int row0, rows;        // ragged K: the expert's
+        bool alone;            // the weights are read by this tile only
     };
     auto tile_at = [&](int pos) -> Tile {
         const int4 d = list[pos & (kQList - 1)];
         Tile t{__builtin_amdgcn_readfirstlane(d.x), __builtin_amdgcn_readfirstlane(d.y), __builtin_amdgcn_readfirstlane(d.z),
-               __builtin_amdgcn_readfirstlane(d.w), 0, 0};
+               __builtin_amdgcn_readfirstlane(d.w), 0, 0, false};
         if constexpr (RAGK) {
             t.row0 = t.m_lim;
             t.rows = t.w < 0 ? 0 : __builtin_amdgcn_readfirstlane(t_off[t.w + 1]) - t.row0;
             t.m_lim = g.M;
+        } else if constexpr (STREAM) {
+            t.alone = t.m_lim < 0;
+            t.m_lim = t.alone ? -t.m_lim : t.m_lim;
         }
         return t;
     };
@@ -219,10 +232,12 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     const char* sA[2];
     const char* sB[2];            // per segment; DUAL: per matrix
     int ipos = 0, istage = 0, ibuf = 0, itotal = 0, irows = 0;
+    bool ialone = false;
     auto cursor_to = [&](const Tile& t) {
         if (t.w < 0) return;  // past the last tile: its first stages once more, which nobody reads
         itotal = stages_of(t);
         irows = t.rows;
+        ialone = t.alone;
         const int64_t eoff = RAGK ? (int64_t)t.row0 * ldb : (int64_t)t.w * g.strideB;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -295,7 +310,8 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
         const char* base = (DUAL ? sB[h] : sg ? sB[1] : sB[0]) + (BT == 1 ? (int64_t)k0 * 2 : (int64_t)k0 * ldb * 2);
         const uint32_t to = lds_wave + (ibuf ? kQBase1 : kQBase0) + (h ? kQB1 : kQB0) + u * 1024;
         if (!KREST || k0 + TK <= g.K) {
-            dma16_s(base, b_off[2 * h + u], to);
+            if (STREAM && ialone) dma16_s_stream(base, b_off[2 * h + u], to);
+            else dma16_s(base, b_off[2 * h + u], to);
         } else {
             const int r = (wave * 2 + u) * 8 + (lane >> 3);
             const int k = BT == 1 ? ((lane & 7) ^ swz_rows(r)) * 8 : k_row(u);

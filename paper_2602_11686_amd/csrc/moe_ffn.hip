@@ -387,19 +387,14 @@ namespace moe {
 
 // =============================== host dispatch ================================
 // Few rows per expert: the kernel of grouped_gemm_few_rows.h where it is the faster one.  The rows of each expert are
-// known on the device only, so the rule goes by their mean, and by whether gg256_kernel's tiles would leave half
-// of the chip idle.  Where the lines lie (us, gg256_kernel -> this; 64 experts of 2048 x 1408 and, with "half the chip
-// idle" in the products that end in d columns, 8 of 4096 x 7168; the products in the order forward 1, forward 2,
-// dgrad 1, dgrad 2):
-//   mean 16, 64 experts: 163 -> 133, 77 -> 67, 107 -> 87, 151 -> 125    8 experts: 220 -> 173, 153 -> 75, 107 -> 104, 299 -> 147
-//   mean 32, 64 experts: 166 -> 150, 78 -> 79 (not taken), 113 -> 82, 155 -> 148
-//   mean 64, 64 experts: 181 -> 153, 84 -> 108, 126 -> 124, 173 -> 195  8 experts: 222 -> 209, 153 -> 107, 107 -> 129, 306 -> 205
-//   mean 128, 64 experts: 201 -> 226, 116 -> 164, 146 -> 174, 240 -> 279 (none taken)
-// That is even routing.  With Zipf-skewed rows (exponents 0.5, 1 and 2; eight shapes of 8 to 256 experts, mean 1 to 64, weights
-// cold) the forward call takes 0.48 to 1.01 of gg256_kernel's time, the backward call 0.81 to 1.03.  Where most experts have
-// no rows and the others have many the smaller tiles cost: all rows on an eighth or fewer of 64 to 256 experts at mean
-// 24 to 64, forward up to 1.24, backward up to 1.14.  Both kernels launched, and one returning at once by what it
-// finds in the offsets, leaves 1.0 to 1.15 of that and costs every other call 2 to 3 %.
+// known on the device only, so the rule goes by their mean, and by whether gg_quad_kernel's tiles would leave a part (two matrices)
+// or half of the chip idle.  Where the lines lie, as whole calls (us, this kernel -> gg_quad_kernel in the products that
+// change at the line; even to Zipf-skewed rows):
+//   two matrices, 64 experts of 2048 x 1408, forward: mean 16 207 -> 214 (with the second product), 24 222 -> 217, 32 225 -> 219,
+//     48 247 -> 228, 64 249 -> 234; training: 48 780 -> 757; 128 of 2048 x 768, forward: 20 260 -> 254, 64 333 -> 284
+//   a part of the chip idle (32 of 512 x 768), training: 64 164 -> 167
+//   half of it idle in the products that end in d columns (8 of 4096 x 14336), forward: 32 508 -> 583, 48 565 -> 590
+//   dgrad, 64 of 2048 x 1408, training: mean 24 731 -> 727, 32 734 -> 735
 template <int BT, bool DUAL, int EPI>
 static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
     auto go = [&](auto kern, int bm, int n_out, int lds) {
@@ -413,8 +408,10 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
     if (R > 64 * (int64_t)g.E) return false;
     const bool to32 = R <= 32 * (int64_t)g.E;
     if constexpr (DUAL) {
-        if (to32) return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 2, 3>, 64, 64, few_rows_lds<64, 2, 3>());
-        return go(gg_few_rows_kernel<BT, DUAL, EPI, 128, 2, 2>, 128, 64, few_rows_lds<128, 2, 2>());
+        const bool part_idle = n256 * g.E < 256;
+        if (R <= 16 * (int64_t)g.E || (part_idle && to32))
+            return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 2, 3>, 64, 64, few_rows_lds<64, 2, 3>());
+        if (part_idle) return go(gg_few_rows_kernel<BT, DUAL, EPI, 128, 2, 2>, 128, 64, few_rows_lds<128, 2, 2>());
     } else if constexpr (BT == 0) {
         if (R <= 16 * (int64_t)g.E || (half_idle && to32))
             return go(gg_few_rows_kernel<BT, DUAL, EPI, 64, 2, 3>, 64, 128, few_rows_lds<64, 2, 3>());
@@ -437,6 +434,13 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
 // groups of 4096 x 14336, mean 4096: 18939, 18920), but after non-temporal ones the update of dx by moe_gate_topk_bwd
 // takes 67 us, after plain ones 46.
 static bool stream_gradients(int64_t R, int groups) { return R <= 2048 * (int64_t)groups; }
+
+// Whether gg_quad_kernel requests the weights of experts with a single row tile non-temporally.  The test costs the other tiles
+// (512 rows per expert: 4 % of the call), so it goes by the mean.  us, plain and by the tile; training passes over 64 experts of
+// 2048 x 1408, 128 and 256 rows: 1069, 1004; 1371, 1365; over 8 of 4096 x 7168, 128 and 192: 1198, 1122; 1453, 1389; forward calls
+// of the first, 32, 128, 192, 256, 512: 229, 227; 290, 280; 336, 334; 412, 416; 635, 662; of 32 of 4096 x 2048, 64, 128, 256:
+// 334, 325; 379, 380; 536, 545.
+static bool stream_weights(int64_t R, int groups) { return R <= 192 * (int64_t)groups; }
 
 // Whether a weight gradient's tiles are too short for gg_quad_kernel, which runs at least two k-stages per tile and fills its
 // pipeline first.  A training pass with the gradients on gg256_kernel and on gg_quad_kernel (us; experts of 4096 x 7168 (8),
@@ -474,7 +478,9 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             }
             if constexpr (!RAGK) {
                 if (ok) {
-                    auto kern = g.K % TK ? gg_quad_kernel<BT, DUAL, EPI, true> : gg_quad_kernel<BT, DUAL, EPI, false>;
+                    auto kern = g.K % TK ? gg_quad_kernel<BT, DUAL, EPI, true>
+                                : stream_weights(R, g.E) ? gg_quad_kernel<BT, DUAL, EPI, false, false, true>
+                                                         : gg_quad_kernel<BT, DUAL, EPI, false>;
                     ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kQuadLds);
                     kern<<<dim3(256), kThreads, kQuadLds, st>>>(g);  // persistent: one workgroup per CU
                     return;

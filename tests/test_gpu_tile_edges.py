@@ -114,6 +114,8 @@ def test_ffn_bf16_k_remainder(counts, d, f):
 # (the weight gradients too, from a mean of 80 rows on: experts of no rows, one, a stage, a stage and one; tiles of at most 128
 # of their rows; none to three tiles per workgroup from the queues)
 @pytest.mark.parametrize("counts,d,f", [((0, 300, 1, 63, 64, 65, 0), 136, 72), ((0, 400, 0, 160), 64, 520), ((81, 79), 384, 640),
+                                        # 17 to 64 rows, enough column tiles to fill the chip: weights requested non-temporally
+                                        ((18,) * 30 + (257, 0), 1024, 1088), ((64, 1, 129) * 12, 768, 1024),
                                         ((400, 0, 30, 200, 100, 129, 1, 90) * 8, 520, 1032), ((300, 1, 0, 128, 129), 64, 64), ((257, 200, 64), 128, 192), ((700, 0, 513), 320, 256),
                                         ((65,) * 30 + (300,) * 10, 1024, 1408), ((2000, 130, 384), 2048, 1032)])
 def test_ffn_quadrants(counts, d, f):
