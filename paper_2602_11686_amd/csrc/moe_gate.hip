@@ -364,13 +364,25 @@ static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, co
 
 // ---- backward -----------------------------------------------------------------------
 
-// wgT[e][c] = w_gate[c][e] as fp32 (makes the dx update a contiguous read)
+// The gate weight as the dx update reads it, by `blocks` workgroups of 256 threads of which this is number `block`.
+// wgT[e][c] = w_gate[c][e] as fp32 (a contiguous read)
 template <class T>
-__global__ void gate_transpose_kernel(const T* __restrict__ wg, float* __restrict__ wgT, int d, int E) {
+__device__ __forceinline__ void gate_transpose(const T* __restrict__ wg, float* __restrict__ wgT, int d, int E, int64_t block,
+                                               int blocks) {
     const int64_t n = (int64_t)d * E;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = block * 256 + threadIdx.x; i < n; i += (int64_t)blocks * 256) {
         const int e = (int)(i / d), c = (int)(i - (int64_t)e * d);
         wgT[i] = Elem<T>::load(wg + (size_t)c * E + e);
+    }
+}
+
+// wg_pad[c][j] = w_gate[c][j] for j < E, zero up to n_pad: a [N][K] operand with whole k-stages
+__device__ __forceinline__ void gate_pad(const bf16_t* __restrict__ wg, bf16_t* __restrict__ wg_pad, int d, int E, int n_pad,
+                                         int64_t block, int blocks) {
+    const int64_t n = (int64_t)d * n_pad;
+    for (int64_t i = block * 256 + threadIdx.x; i < n; i += (int64_t)blocks * 256) {
+        const int c = (int)(i / n_pad), j = (int)(i - (int64_t)c * n_pad);
+        wg_pad[i] = j < E ? wg[(size_t)c * E + j] : (bf16_t)0;
     }
 }
 
@@ -472,18 +484,28 @@ static dim3 token_grid(int64_t blocks) {
 }
 
 // one wavefront per token: dl[t,s] (fp32, for the dx update) and the dense rows, dl[t,s] = w_s (dw_s - sum_j w_j dw_j);
-// D = bf16_t: hi and lo, D = float: hi is the value itself.  It also writes the constants of the products after it: the
-// chunks' token ranges, a row of zeros, and the token range as a single group (in a launch of their own 1.4 us of the 11
-// that one fp32 token takes).
+// D = bf16_t: hi and lo, D = float: hi is the value itself.  It also writes what else the products after it need: the chunks'
+// token ranges, a row of zeros, the token range as a single group (in a launch of their own 1.4 us of the 11 that one
+// fp32 token takes), and, in kWeightBlocks workgroups behind those of the tokens, the gate weight: padded to n_pad columns
+// (wg_pad) or transposed (wgT), whichever is given (a launch of their own: 2 to 5 us).
+constexpr int kWeightBlocks = 256;
 template <class D>
 __global__ __launch_bounds__(256) void gate_dl_dense_kernel(const int32_t* __restrict__ ids, const float* __restrict__ w,
                                                             const float* __restrict__ dw, float* __restrict__ dl,
                                                             D* __restrict__ hi, D* __restrict__ lo, int Tn,
                                                             int k, int n_pad, int32_t* __restrict__ chunk_off, int nchunks,
                                                             int chunk_tokens, uint32_t* __restrict__ zero_row,
-                                                            int32_t* __restrict__ whole) {
+                                                            int32_t* __restrict__ whole, const D* __restrict__ w_gate,
+                                                            float* __restrict__ wgT, bf16_t* __restrict__ wg_pad, int d, int E) {
     const int lane = threadIdx.x & 63;
     const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t weight_block = block - ((int64_t)Tn + 3) / 4;
+    if (weight_block >= 0 && weight_block < kWeightBlocks) {
+        if constexpr (sizeof(D) == 2) {
+            if (wg_pad) gate_pad(w_gate, wg_pad, d, E, n_pad, weight_block, kWeightBlocks);
+        }
+        if (wgT) gate_transpose(w_gate, wgT, d, E, weight_block, kWeightBlocks);
+    }
     const int64_t t = block * 4 + (threadIdx.x >> 6);
     const int64_t i = block * 256 + threadIdx.x;  // (at least 256 threads, and 64 for every chunk)
     if (i < 128) zero_row[i] = 0u;
@@ -504,15 +526,6 @@ __global__ __launch_bounds__(256) void gate_dl_dense_kernel(const int32_t* __res
         } else {
             hi[(size_t)t * n_pad + e] = v;
         }
-    }
-}
-
-// wg_pad[c][j] = w_gate[c][j] for j < E, zero up to n_pad: the gate weight as a [N][K] operand with whole k-stages
-__global__ void gate_pad_wg_kernel(const bf16_t* __restrict__ wg, bf16_t* __restrict__ wg_pad, int d, int E, int n_pad) {
-    const int64_t n = (int64_t)d * n_pad;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i / n_pad), j = (int)(i - (int64_t)c * n_pad);
-        wg_pad[i] = j < E ? wg[(size_t)c * E + j] : (bf16_t)0;
     }
 }
 
@@ -623,18 +636,18 @@ static moe_status gate_bwd_launch(const moe_shape* s, const T* x, const T* w_gat
     int32_t* coff = static_cast<int32_t*>(cv.take((size_t)(nch + 1) * 4));
     uint32_t* zero_row = static_cast<uint32_t*>(cv.take(512));
     int32_t* whole = static_cast<int32_t*>(cv.take(256));
-    gate_dl_dense_kernel<T><<<token_grid(((int64_t)s->T + 3) / 4), 256, 0, st>>>(ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch,
-                                                            f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s), zero_row, whole);
-    if (dx && !f32 && s->k >= 4) {
+    const bool dx_gemm = dx && !f32 && s->k >= 4;
+    bf16_t* wg_pad = dx_gemm ? reinterpret_cast<bf16_t*>(wgT) : nullptr;
+    gate_dl_dense_kernel<T><<<token_grid(((int64_t)s->T + 3) / 4 + (dx ? kWeightBlocks : 0)), 256, 0, st>>>(
+        ids, w, dw, dl, hi, lo, s->T, s->k, n_pad, coff, nch, f32 ? f32_chunk_tokens(s) : mma_chunk_tokens(s), zero_row, whole,
+        w_gate, dx && !dx_gemm ? wgT : nullptr, wg_pad, s->d, s->E);
+    if (dx_gemm) {
         // dx += dL * W_g^T as a GEMM over the dense (hi + lo) dL: reads and writes dx once; the gate
         // weight stays in bf16 (padded to whole k-stages in the space of the fp32 transpose).  The
         // gather form below reads k rows of the fp32 gate weight per token from L2, which is what
         // costs from k = 4 on (measured: k = 8: 54 us against 89 us; k = 2: 93 us against 87 us).
-        bf16_t* wg_pad = reinterpret_cast<bf16_t*>(wgT);
-        gate_pad_wg_kernel<<<256, 256, 0, st>>>(reinterpret_cast<const bf16_t*>(w_gate), wg_pad, s->d, s->E, n_pad);
         launch_gate_dx_gemm(hi, lo, wg_pad, whole, s->d, n_pad, dx, st);
     } else if (dx) {
-        gate_transpose_kernel<T><<<256, 256, 0, st>>>(w_gate, wgT, s->d, s->E);
         launch_gate_bwd_dx<T>(dx, wgT, ids, dl, s->T, s->d, s->k, st);
     }
     // (fp32, 256 tokens x 128: 112 us with one thread per column and a serial walk of the tokens, 4 us here;
