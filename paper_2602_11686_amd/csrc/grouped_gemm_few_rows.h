@@ -13,6 +13,9 @@
 // tiles of 64 1.6, 200 rows in tiles of 128 2.0): with several row tiles the requests are plain (us, W1|W3 and both dgrads;
 // 2048 rows over 64 experts of 2048 x 1408, Zipf-skewed: 165 -> 150, 240 -> 218; 4096 rows on 16 of 128 experts of
 // 2048 x 768: 80 -> 67, 148 -> 115).  Two loops, because the test inside one costs 64 tokens of 128 experts 1 %.
+// (Replica groups: the test is the group's own.  Plain requests where another group has the expert, whole passes in us: 64 groups
+// of 8 experts of 4096 x 2048, 16 and 32 rows per group 1665 -> 1567, 1712 -> 1634; 32 of 16, 16 rows 915 -> 884; but 128 of 64
+// experts of 2048 x 1408, 16 and 32 rows 1258 -> 1270, 1323 -> 1361.)
 //
 // LDS: row form (K contiguous; A, and B in the dgrad products) as [64 or BM rows][128 B], read with ds_read_b128;
 // k-row form (N contiguous; B forward) as [64 k-rows][128 B], read with the transposing ds_read_b64_tr_b16.  The

@@ -59,7 +59,8 @@ constexpr int kQStaging0 = 3 * kQHalf, kQStaging1 = 4 * kQHalf;
 constexpr int kQTableOff = 9 * kQHalf;
 constexpr int kQList = 512;                                  // entries of the ring of tiles, built 256 at a time
 constexpr int kQListOff = kQTableOff + ((2 * (MOE_MAX_EXPERTS + 1) * 4 + 15) & ~15);
-constexpr int kQuadLds = kQListOff + kQList * 16;
+constexpr int kQUsersOff = kQListOff + kQList * 16;
+constexpr int kQuadLds = kQUsersOff + MOE_MAX_EXPERTS * 4;
 static_assert(kQuadLds <= kLdsBytes, "fits the unit's LDS");
 
 // 256-byte k-rows read transposed for 16x16x32 MFMAs: half a wavefront reads a pair of 16-byte pieces of the k-rows q, q+1, q+2,
@@ -76,7 +77,10 @@ __device__ __forceinline__ void dma16_s_stream(const void* sbase, uint32_t voff,
 //
 // RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).  STREAM, RAGK: C is stored non-temporally (an
 // instance of its own: of two stores behind a test at run time the compiler makes one plain store).  STREAM, ragged M: the
-// weights of experts with a single row tile, which nobody else reads, are requested non-temporally.
+// weights of experts with a single row tile, which nobody else reads, are requested non-temporally.  (Replica groups: weights
+// are nobody else's where no other group with rows has the expert.  Taken for a group's own whenever the group has one tile,
+// passes over 32 groups of 16 experts of 4096 x 2048, 128 groups of 64 of 2048 x 1408 and 64 groups of 8 of 4096 x 2048 took 1266,
+// 1846 and 2054 us at 128, 128 and 64 rows per group, and now take 1183, 1803 and 1837.)
 template <int BT, bool DUAL, int EPI, bool KREST, bool RAGK = false, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
@@ -87,6 +91,8 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
     // the workgroup's tiles: index of the weights (-1: no more tiles), m0, m_lim (STREAM: negated where nobody else reads the
     // weights), n0; ragged K: expert, m0, its first row, n0
     int4* list = reinterpret_cast<int4*>(smem + kQListOff);
+    int32_t* users = reinterpret_cast<int32_t*>(smem + kQUsersOff);  // [experts] groups with rows that have the expert
+    const bool count_users = STREAM && !RAGK && g.expert_of_group;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave >> 2, wn = wave & 3;
     const int n_out = DUAL ? TN / 2 : TN;     // output columns per tile
@@ -95,7 +101,9 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
 
     // ---- rows of each expert and the number of tiles before it ----
     for (int i = threadIdx.x; i <= g.E; i += kThreads) t_off[i] = g.offsets[i];
+    if (count_users && threadIdx.x < MOE_MAX_EXPERTS) users[threadIdx.x] = 0;
     __syncthreads();
+    if (count_users && threadIdx.x < g.E && t_off[threadIdx.x + 1] > t_off[threadIdx.x]) atomicAdd(&users[weight_index(g, threadIdx.x)], 1);
     if (wave == 0) {  // exclusive scan of the per-expert tile counts: 4 experts per lane, then across lanes
         int c[4], sum = 0;
 #pragma unroll
@@ -165,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                 }
                 d.w = nt * n_out;
                 if (d.y < d.z) d.x = weight_index(g, lo);
-                if (STREAM && en - b <= (part < 0 ? TM : TM / 2)) d.z = -d.z;
+                if (STREAM && en - b <= (part < 0 ? TM : TM / 2) && !(count_users && users[weight_index(g, lo)] > 1)) d.z = -d.z;
             }
         }
         list[pos & (kQList - 1)] = d;

@@ -235,3 +235,40 @@ def test_backward_over_replica_groups(T, d, f, E, k, N, C, Dn, rank):
         assert err_e <= tol, (name, "expert", ei, err_e)
     for g in np.nonzero(np.diff(go_ref) == 0)[0]:
         assert float(dw1[g].abs().max()) == 0 and float(dw2[g].abs().max()) == 0 and float(dw3[g].abs().max()) == 0
+
+
+# 17 to 192 rows per group on average and enough column tiles to fill the chip: the instances of the tile kernel that look
+# for groups with weights to themselves.  Replicas, an expert of one group, a replica without rows, entries out of range,
+# groups of one to three row tiles
+@pytest.mark.parametrize("counts,eog", [((64,) * 32, [g % 8 for g in range(32)]),
+                                        ((100, 0, 1, 129, 300, 64, 128, 65) * 4, [g // 2 for g in range(32)]),
+                                        ((20,) * 30 + (600, 0), [0] * 16 + list(range(14)) + [99, -3]),
+                                        ((192,) * 32, list(range(32)))])
+def test_few_row_groups_equal_the_plain_path_over_their_weights(counts, eog):
+    G, d, f = len(counts), 1280, 1024
+    E = 32 if max(eog[:-2]) >= 16 else 16
+    g = torch.Generator(device="cuda").manual_seed(sum(counts))
+    val = lambda *n, std=1.0: torch.empty(*n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    R = sum(counts)
+    off = i32(np.concatenate([[0], np.cumsum(counts)]))
+    x, dy, w1, w3, w2 = val(R, d), val(R, d), val(E, d, f, std=0.02), val(E, d, f, std=0.02), val(E, f, d, std=0.02)
+    at = torch.tensor(eog, device="cuda").clamp(0, E - 1)
+
+    def run(fwd, bwd, shape):
+        nan = lambda *n: torch.full(n, float("nan"), dtype=torch.bfloat16, device="cuda")
+        y, a, b, dx, g1, g3, g2 = nan(R, d), nan(R, f), nan(R, f), nan(R, d), nan(G, d, f), nan(G, d, f), nan(G, f, d)
+        ws = torch.empty(B.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+        fwd(y, a, b, ws)
+        bwd(a, b, dx, g1, g3, g2, ws)
+        return y, a, b, dx, g1, g3, g2
+
+    s = B.Shape(R, d, f, E, 1, torch.bfloat16)
+    got = run(lambda y, a, b, ws: B.moe_grouped_ffn_fwd_groups(s, G, i32(eog), x, off, w1, w3, w2, y, a, b, ws),
+              lambda a, b, dx, g1, g3, g2, ws: B.moe_grouped_ffn_bwd_groups(s, G, i32(eog), x, off, w1, w3, w2, a, b, dy, dx, g1,
+                                                                            g3, g2, ws), s)
+    p = B.Shape(R, d, f, G, 1, torch.bfloat16)
+    v1, v3, v2 = w1[at], w3[at], w2[at]
+    want = run(lambda y, a, b, ws: B.moe_grouped_ffn_fwd(p, x, off, v1, v3, v2, y, a, b, ws),
+               lambda a, b, dx, g1, g3, g2, ws: B.moe_grouped_ffn_bwd(p, x, off, v1, v3, v2, a, b, dy, dx, g1, g3, g2, ws), p)
+    for u, v in zip(got, want):
+        assert torch.isfinite(u).all() and torch.equal(u, v)

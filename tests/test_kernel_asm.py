@@ -169,3 +169,15 @@ def test_quadrant_pipeline_holds_only_the_hand_placed_vmcnt_waits(ffn_asm):
         assert sorted(seen) == ([4, 6, 8] if rest else [4, 6, 6, 8]), (name, seen)
     for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe\d+gg_quad_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
         assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", m.group(2)), m.group(1)
+
+
+def test_quadrant_kernel_counts_the_groups_that_share_weights(ffn_asm):
+    """The instances with ragged M that request a single tile's weights non-temporally count in LDS how many groups with rows
+    have each expert: replicas read the same weights.  The others have no use for the counts."""
+    counting = {}
+    for name, blocks in kernels(ffn_asm, "gg_quad_kernel").items():
+        _, ragk, stream = re.search(r"ELb([01])ELb([01])ELb([01])EEE", name).groups()
+        counts = any(i.startswith("ds_add_") for _, ins in blocks for i in ins)
+        assert counts == (ragk == "0" and stream == "1"), name
+        counting[name] = counts
+    assert sum(counting.values()) == 5, counting   # two forward and three backward products
