@@ -75,9 +75,11 @@ __device__ __forceinline__ void dma16_s_stream(const void* sbase, uint32_t voff,
 
 // KREST: K is no multiple of 64 (the last stage of a segment reads zeros past it); an instance of its own.
 //
-// RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).  STREAM, RAGK: C is stored non-temporally (an
-// instance of its own: of two stores behind a test at run time the compiler makes one plain store).  STREAM, ragged M: the
-// weights of experts with a single row tile, which nobody else reads, are requested non-temporally.  (Replica groups: weights
+// RAGK: the contraction is ragged (AT == 1: A in k-row form, BT == 0).
+//
+// STREAM: what is read or written once is requested and stored non-temporally (an instance of its own: of two stores behind a
+// test at run time the compiler makes one plain store).  Ragged K: C.  Ragged M: all outputs, but those of the derivative
+// epilogues, and the weights of experts with a single row tile, which nobody else reads.  (Replica groups: weights
 // are nobody else's where no other group with rows has the expert.  Taken for a group's own whenever the group has one tile,
 // passes over 32 groups of 16 experts of 4096 x 2048, 128 groups of 64 of 2048 x 1408 and 64 groups of 8 of 4096 x 2048 took 1266,
 // 1846 and 2054 us at 128, 128 and 64 rows per group, and now take 1183, 1803 and 1837.)

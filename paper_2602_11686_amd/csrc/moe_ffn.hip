@@ -435,12 +435,18 @@ static bool launch_few_rows(const GArgs& g, int64_t R, hipStream_t st) {
 // takes 67 us, after plain ones 46.
 static bool stream_gradients(int64_t R, int groups) { return R <= 2048 * (int64_t)groups; }
 
-// Whether gg_quad_kernel requests the weights of experts with a single row tile non-temporally.  The test costs the other tiles
-// (512 rows per expert: 4 % of the call), so it goes by the mean.  us, plain and by the tile; training passes over 64 experts of
-// 2048 x 1408, 128 and 256 rows: 1069, 1004; 1371, 1365; over 8 of 4096 x 7168, 128 and 192: 1198, 1122; 1453, 1389; forward calls
-// of the first, 32, 128, 192, 256, 512: 229, 227; 290, 280; 336, 334; 412, 416; 635, 662; of 32 of 4096 x 2048, 64, 128, 256:
-// 334, 325; 379, 380; 536, 545.
-static bool stream_weights(int64_t R, int groups) { return R <= 192 * (int64_t)groups; }
+// Whether the products over ragged rows go through the instances of gg_quad_kernel that request the weights of experts with a single
+// row tile, and store the outputs, non-temporally.  With few rows per expert the weights are the work: outputs that stay out of
+// the caches leave them to the weights that the next kernels read.  The test per tile costs where there are more rows, so it goes
+// by the mean.  us, all plain; the weights alone non-temporal; weights and outputs:
+//   forward, 64 experts of 2048 x 1408, mean 32: 227, 220, 214   64: 244, 241, 226   128: 282, 281, 268   192: 333, 337, 334
+//     256: 387, 393, 391   512: 622, 646, 646
+//     32 of 4096 x 2048, 64: 322, 306, 289   128: 365, 367, 353   192: 439, 440, 431   256: 523, 532, 533
+//     8 of 4096 x 14336, 128: 644, 658, 641   192: 708, 726, 717
+//   training, 64 of 2048 x 1408, 64: 847, 792, 765   128: 977, 962, 937   192: 1200, 1178, 1161   256: 1349, 1339, 1333
+//     8 of 4096 x 7168, 128: 1184, 1181, 1170   192: 1309, 1289, 1287   256: 1599, 1606, 1597
+//     128 of 2048 x 768, 80: 1040, 1010, 976   128: 1206, 1161, 1132   192: 1400, 1366, 1356
+static bool stream_few_rows(int64_t R, int groups) { return R <= 192 * (int64_t)groups; }
 
 // Whether a weight gradient's tiles are too short for gg_quad_kernel, which runs at least two k-stages per tile and fills its
 // pipeline first.  A training pass with the gradients on gg256_kernel and on gg_quad_kernel (us; experts of 4096 x 7168 (8),
@@ -479,7 +485,7 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             if constexpr (!RAGK) {
                 if (ok) {
                     auto kern = g.K % TK ? gg_quad_kernel<BT, DUAL, EPI, true>
-                                : stream_weights(R, g.E) ? gg_quad_kernel<BT, DUAL, EPI, false, false, true>
+                                : stream_few_rows(R, g.E) ? gg_quad_kernel<BT, DUAL, EPI, false, false, true>
                                                          : gg_quad_kernel<BT, DUAL, EPI, false>;
                     ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kQuadLds);
                     kern<<<dim3(256), kThreads, kQuadLds, st>>>(g);  // persistent: one workgroup per CU

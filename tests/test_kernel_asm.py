@@ -181,3 +181,11 @@ def test_quadrant_kernel_counts_the_groups_that_share_weights(ffn_asm):
         assert counts == (ragk == "0" and stream == "1"), name
         counting[name] = counts
     assert sum(counting.values()) == 5, counting   # two forward and three backward products
+
+
+def test_which_outputs_the_quadrant_kernel_stores_non_temporally(ffn_asm):
+    """All of the instances made for that (few rows per expert; the gradients) but the derivative epilogues, and no others."""
+    for name, blocks in kernels(ffn_asm, "gg_quad_kernel").items():
+        epilogue, stream = re.search(r"kernelILi\dELb[01]ELi(\d)ELb[01]ELb[01]ELb([01])EEE", name).groups()
+        nt = {" nt" in i for _, ins in blocks for i in ins if i.startswith("global_store_dwordx4")}
+        assert nt == {stream == "1" and epilogue not in "36"}, (name, nt)   # 3, 6: EPI_DH, EPI_DHP
