@@ -1,5 +1,5 @@
 // Grouped fp32 GEMM on v_mfma_f32_16x16x4: fp32 operands, products and sums, at twice the rate of the scalar FMA units.
-// Operand forms, tile walk and epilogues as in the bf16 kernels.
+// Operand forms, tile walk and epilogues as in the bf16 kernels.  (Products with very many tiles: grouped_gemm_f32_large.h.)
 //
 // What bounds it is the matrix pipe (154 TFLOP/s in a loop of these MFMAs alone, 139 at the 2.1 GHz that the power limit
 // leaves a whole kernel), and before that the last tiles: few experts of 64 to 1000 rows make few tiles.  So a workgroup of

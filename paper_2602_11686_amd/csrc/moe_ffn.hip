@@ -19,7 +19,8 @@
 // memory order, transposing LDS reads where the contraction index is not the contiguous one: gg_quad_kernel
 // (grouped_gemm_quad.h), and gg256_kernel (grouped_gemm_bf16.h) for the gradients of few rows.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
 // left for leading dimensions and extents beyond the 32-bit offsets of these.
-// fp32 path: 64x64 tiles on the fp32 matrix instructions (grouped_gemm_f32.h), same tile walk and epilogues.
+// fp32 path: 64x64 tiles on the fp32 matrix instructions (grouped_gemm_f32.h), 128x128 ones for products with many of them
+// (grouped_gemm_f32_large.h), same tile walk and epilogues.
 #include "moe_internal.h"
 
 namespace moe {
@@ -383,6 +384,7 @@ namespace moe {
 
 }  // namespace moe
 #include "grouped_gemm_f32.h"
+#include "grouped_gemm_f32_large.h"
 namespace moe {
 
 // =============================== host dispatch ================================
@@ -469,6 +471,23 @@ static void launch_f32(const GArgs& g, int64_t tiles, hipStream_t st) {
     kern<<<f32_grid(tiles), 256, kF32Lds, st>>>(g);
 }
 
+// Whether a product with B in k-row form is one for 128x128 tiles, by their number (ragged M: an upper bound) and the mean rows per
+// expert.  Kernel times, 128x128 over 64x64 tiles:
+//   gradients, dW2: 1024 to 1536 tiles 0.87 to 1.25, mostly above 1; 2816 0.91 to 0.93; 11264 to 28672 0.77 to 0.94
+//     dW1|dW3: 512 1.03 to 1.09; 2040 0.97 to 1.03; 2048 0.87 to 0.95; 2816 to 57344 0.75 to 0.97
+//   forward, two matrices, 512 rows per expert and more: 1056 to 1152 1.05 to 1.10; 1760 1.00 to 1.04; 2112 to 45408 0.86 to 0.99
+//     fewer rows, 2112 to 5376 0.97 to 1.40
+//   forward, one matrix, 1024 rows and more: 576 to 2304 0.92 to 1.40; 4128 to 18432 0.93 to 1.00; fewer rows 0.99 to 1.9
+// (the products with B in row form 0.95 to 2.1, above 1 but for 3 of 66).  Whole passes in us, 128x128 tiles from 512 on
+// in every product, 64x64 tiles alone, this rule:
+//   training, 8 experts of 4096 x 14336, 512 tokens 14153, 12293, 11719; 4096 73790, 75478, 73338; 16384 276856, 293322, 278733
+//     128 of 2048 x 768, 16384: 32699, 33754, 32443   16 of 4096 x 7168, 4096: 71890, 74683, 71773   8 of 1024 x 2816, 2048: 2363, 2156, 2132
+template <bool DUAL, bool RAGK>
+static bool f32_large_tiles(int64_t tiles, int64_t R, int groups) {
+    if (RAGK) return tiles >= 2048;
+    return DUAL ? tiles >= 2048 && R >= 512 * (int64_t)groups : tiles >= 4096 && R >= 1024 * (int64_t)groups;
+}
+
 // A(m,k) layout AT, B(k,n) layout BT as in the bf16 kernel.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t st) {
@@ -509,10 +528,19 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
         else grid = dim3((g.N + BN - 1) / BN, (unsigned)((R + BM - 1) / BM + g.E), 1);
         gg_bf16_kernel<AT, BT, DUAL, EPI, RAGK><<<grid, 256, 0, st>>>(g);
     } else {
-        const int64_t n_tiles = (g.N + (DUAL ? kF32Tile / 2 : kF32Tile) - 1) / (DUAL ? kF32Tile / 2 : kF32Tile);
-        const int64_t m_tiles = RAGK ? (int64_t)((g.M + kF32Tile - 1) / kF32Tile) * g.E
-                                     : (R + kF32Tile - 1) / kF32Tile + g.E;  // (upper bound with ragged M)
-        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, n_tiles * m_tiles, st);
+        auto tiles = [&](int bm) {
+            const int n_out = DUAL ? bm / 2 : bm;
+            const int64_t n = (g.N + n_out - 1) / n_out;
+            return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * g.E : (R + bm - 1) / bm + g.E);  // (upper bound with ragged M)
+        };
+        if constexpr (BT == 0) {
+            const int64_t large = tiles(kF32LargeTile);
+            if (f32_large_tiles<DUAL, RAGK>(large, R, g.E)) {
+                gg_f32_large_kernel<AT, DUAL, EPI, RAGK><<<f32_grid(large), 256, 0, st>>>(g);
+                return;
+            }
+        }
+        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, tiles(kF32Tile), st);
     }
 }
 

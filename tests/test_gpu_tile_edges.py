@@ -72,7 +72,7 @@ def check_ffn(counts, d, f, dtype, seed, backward=True, wstd=0.05):
         assert not buf.dw1[e].any() and not buf.dw3[e].any() and not buf.dw2[e].any()
 
 
-# fp32, 64x64 tiles (fewer than 512 of 128x128 in every product): remainders of rows, columns and k-stages
+# fp32, 64x64 tiles (too few for 128x128 ones in every product): remainders of rows, columns and k-stages
 @pytest.mark.parametrize("counts,d,f", [((1, 0, 63, 64, 65, 130), 68, 36), ((5, 17), 4, 132), ((0, 129, 300), 64, 16),
                                         ((1200, 127, 0, 1), 2048, 260), ((700, 900), 260, 2048)])
 def test_ffn_f32(counts, d, f):
@@ -86,13 +86,20 @@ def test_ffn_f32_stages(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 5 * d + f)
 
 
-# fp32, 128x128 tiles: at least 512 of them in every product (an upper bound with ragged rows, as the dispatch counts them)
-def test_ffn_f32_large_tiles():
-    counts, d, f = (0, 1, 127, 128, 129, 300, 17, 64) * 25, 260, 264
+# fp32, 128x128 tiles: enough of them, and of rows per expert, in the named products (an upper bound with ragged rows, as the
+# dispatch counts them); remainders of rows, columns and k-stages
+@pytest.mark.parametrize("products,counts,d,f", [("dW1", (0, 1, 127, 128, 129, 300, 17, 64) * 25, 260, 264),
+                                                 ("dW1 dW2", (0, 1, 127, 128, 129, 300, 17, 64) * 25, 260, 388),
+                                                 ("A", (0, 1, 127, 128, 129, 3000, 2500, 2400), 36, 1868),
+                                                 ("Yp", (0, 1, 127, 128, 129, 3000, 2500, 2400), 7300, 36),
+                                                 ("Yp", (1030, 1100, 1000, 1024), 14980, 4)])
+def test_ffn_f32_large_tiles(products, counts, d, f):
     up = lambda n, m: -(-n // m)
-    rows = sum(counts) // 128 + len(counts)
-    tiles = [up(f, 64) * rows, up(d, 128) * rows, up(f, 128) * rows, up(d, 128) * up(f, 128) * len(counts)]
-    assert min(tiles) >= 512
+    E, R = len(counts), sum(counts)
+    rows = up(R, 128) + E
+    large = {"A": up(f, 64) * rows >= 2048 and R >= 512 * E, "Yp": up(d, 128) * rows >= 4096 and R >= 1024 * E,
+             "dW2": up(d, 128) * up(f, 128) * E >= 2048, "dW1": up(f, 64) * up(d, 128) * E >= 2048}
+    assert {p for p in large if large[p]} == set(products.split())
     check_ffn(counts, d, f, torch.float32, 3)
 
 

@@ -189,3 +189,11 @@ def test_which_outputs_the_quadrant_kernel_stores_non_temporally(ffn_asm):
         epilogue, stream = re.search(r"kernelILi\dELb[01]ELi(\d)ELb[01]ELb[01]ELb([01])EEE", name).groups()
         nt = {" nt" in i for _, ins in blocks for i in ins if i.startswith("global_store_dwordx4")}
         assert nt == {stream == "1" and epilogue not in "36"}, (name, nt)   # 3, 6: EPI_DH, EPI_DHP
+
+
+def test_large_fp32_tiles_are_built_for_the_products_that_take_them(ffn_asm):
+    """Two forward products and two gradients; the accumulators of a 128x128 tile fit the registers."""
+    found = re.findall(r"\.amdhsa_kernel (_ZN3moe\d+gg_f32_large_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S)
+    assert len(found) == 4, [name for name, _ in found]
+    for name, body in found:
+        assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", body), name
