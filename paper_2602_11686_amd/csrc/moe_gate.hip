@@ -451,10 +451,22 @@ static void launch_gate_bwd_dx(T* dx, const float* wgT, const int32_t* ids, cons
 // dL is written out densely (bf16 layers: as two bf16 matrices hi + lo, the pair carries 16 mantissa bits
 // of the fp32 value), tokens are cut into chunks, each chunk's X^T * dL is a product of its own,
 // and the chunk partials are added in chunk order.
-// The product runs on gate_dwg_kernel, but for many experts and many tokens on the grouped GEMM, whose 256-wide tiles they
-// fill.  Training passes on either (us, grouped GEMM -> gate_dwg_kernel): 160 experts, 512, 4096 and 16384 tokens 441 -> 400,
-// 1374 -> 1339, 2722 -> 2659; 256 experts, 1000 and 8192 tokens 801 -> 757, 2783 -> 2771 (within the spread).
-static inline bool dwg_tokens_once(const moe_shape* s) { return s->E <= 192 || s->T <= 4096; }
+// The product runs on gate_dwg_kernel, but for very many tokens of few columns and many experts on the grouped GEMM: the dense dL
+// is the most of what there is to read then, and is read once per 256 columns of x instead of once per 128.
+// The whole call, gate_dwg_kernel over the grouped GEMM:
+//   tokens                                 65536     131072     262144     524288       2^20
+//   65 to 128 experts, d 192 to 1024                0.85-0.97  0.92-1.01  0.94-1.04  0.96-1.07
+//   129 to 192 experts, d 192 to 768    0.76-0.96   0.92-1.01  0.99-1.11  1.02-1.16  1.05-1.07
+//                       d 1024          0.87-0.90   0.87-0.91  0.96-0.98  1.00-1.01
+//   193 to 256 experts, d 192 to 768    0.79-1.01   0.97-1.08  1.05-1.22  1.07-1.28  1.12-1.14
+//                       d 1024          0.94-0.96   0.92-0.95  1.02-1.05  1.09-1.13
+//   more than 128, d 128                0.74-0.82   0.93-0.95  0.97-0.98  0.97-1.00  0.99-1.01
+//                  d 2048 and more      0.82-0.90   0.81-0.90  0.89-0.96  0.97-0.99
+// and fewer tokens down to 0.5 (4100 tokens of 1024, 193 experts: 92 -> 45 us).  64 experts and fewer: 0.83 to 0.92.
+static inline bool dwg_tokens_once(const moe_shape* s) {
+    const bool few_columns = s->d > 128 && s->d <= 1024;
+    return !(few_columns && (s->E > 192 ? s->T >= 1 << 17 : s->E > 128 && s->T > 1 << 18));
+}
 // 512 tokens (or more for very long batches: the GEMM's group table holds MOE_MAX_EXPERTS groups); gate_dwg_kernel: halved
 // while its 128 x 64 tiles of all chunks are too few to give every compute unit two
 static inline int mma_chunk_tokens(const moe_shape* s) {

@@ -132,10 +132,10 @@ def test_gate_bwd_more_tokens_than_a_grid_dimension():
 
 
 # the gate weight's gradient: token chunks of 64 to 512 (one token, a stage, its neighbours, several chunks with a rest), tiles of
-# 128 columns and their remainders, 16-expert blocks and 64-expert tiles, and the grouped GEMM (many experts and tokens)
+# 128 columns and their remainders, 16-expert blocks and 64-expert tiles, and the grouped GEMM (the last two)
 @pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (63, 120, 15, 2), (64, 128, 16, 3), (65, 136, 17, 4), (129, 264, 64, 1),
                                      (700, 1096, 65, 6), (300, 520, 130, 8), (2049, 640, 100, 2), (4097, 136, 200, 4),
-                                     (20000, 4096, 8, 2)])
+                                     (20000, 4096, 8, 2), (131072, 136, 200, 2), (262145, 136, 130, 1)])
 def test_gate_weight_gradient_edges(T, d, E, k):
     """Against 64 bits.  The gradient of a logit enters as a pair of bf16 values (2^-17 of it is lost), sums are in fp32:
     1e-5 of the result's 2-norm."""
