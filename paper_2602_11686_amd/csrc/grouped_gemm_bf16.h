@@ -159,11 +159,10 @@ struct TileDesc {
 // next tile is made when a tile starts (one lane; its latency hides behind the main loop), reaches LDS
 // before the last barrier of the main loop and is read by all wavefronts after it.
 //
-// STREAM (ragged K): C is stored non-temporally.  (An instance of its own: of two stores behind a test at run time
-// the compiler makes one plain store.)
-template <int AT, int BT, bool DUAL, int EPI, bool RAGK, bool STREAM = false>
+// bf16 results (the gradients of few rows per expert) are stored non-temporally.
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
-    static_assert(RAGK ? (AT == 1 && BT == 0) : (AT == 0 && BT == 1 && !DUAL && !STREAM), "operand forms");
+    static_assert(RAGK ? (AT == 1 && BT == 0) : (AT == 0 && BT == 1 && !DUAL), "operand forms");
     static_assert(RAGK ? EPI == EPI_STORE || EPI == EPI_STORE2 || EPI == EPI_STORE_F32 : EPI == EPI_ADD, "epilogues");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int32_t* t_off = reinterpret_cast<int32_t*>(smem + kTableOff);  // [E+1] rows of each expert
@@ -556,8 +555,7 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                         for (int z = 0; z < 8; ++z) d[z] = 0.f;
                     } else {
                         u32x4* to = reinterpret_cast<u32x4*>(dst + cbase + (int64_t)row * g.ldc + t.n0 + col);
-                        if constexpr (STREAM) __builtin_nontemporal_store((u32x4){0, 0, 0, 0}, to);
-                        else *to = (u32x4){0, 0, 0, 0};
+                        __builtin_nontemporal_store((u32x4){0, 0, 0, 0}, to);
                     }
                 }
             }
@@ -720,11 +718,8 @@ __global__ __launch_bounds__(kThreads) void gg256_kernel(const GArgs g) {
                     if (dst1 && col >= cols0) { col -= cols0; dst = dst1; }
                     // (offsets inside a tile fit 32 bits: at most 256 rows of ldc < 2^22 elements)
                     const uint32_t off = (uint32_t)trow * ldc_u + (uint32_t)col;
-                    if (t.m0 + trow < t.m_lim && t.n0 + col < g.N) {
-                        u32x4* to = reinterpret_cast<u32x4*>(dst + tile_base + off);
-                        if constexpr (STREAM) __builtin_nontemporal_store(v[u], to);
-                        else *to = v[u];
-                    }
+                    if (t.m0 + trow < t.m_lim && t.n0 + col < g.N)
+                        __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(dst + tile_base + off));
                 }
             };
             int pn = 0;  // passes so far

@@ -500,8 +500,6 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
                             (!RAGK || g.M >= 8);
             if constexpr (!RAGK) {
                 if (ok && launch_few_rows<BT, DUAL, EPI>(g, R, st)) return;
-            }
-            if constexpr (!RAGK) {
                 if (ok) {
                     auto kern = g.K % TK ? gg_quad_kernel<BT, DUAL, EPI, true>
                                 : stream_few_rows(R, g.E) ? gg_quad_kernel<BT, DUAL, EPI, false, false, true>
@@ -515,11 +513,9 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
                     ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
                     kern<<<dim3(256), kThreads, lds, st>>>(g);
                 };
-                const bool stream = stream_gradients(R, g.E);
-                if (few_rows_per_tile(R, g.E))
-                    go(stream ? gg256_kernel<AT, BT, DUAL, EPI, RAGK, true> : gg256_kernel<AT, BT, DUAL, EPI, RAGK>, kGemmLds);
-                else
-                    go(stream ? gg_quad_kernel<BT, DUAL, EPI, false, true, true> : gg_quad_kernel<BT, DUAL, EPI, false, true>, kQuadLds);
+                if (few_rows_per_tile(R, g.E)) go(gg256_kernel<AT, BT, DUAL, EPI, RAGK>, kGemmLds);  // (stores as stream_gradients says)
+                else if (stream_gradients(R, g.E)) go(gg_quad_kernel<BT, DUAL, EPI, false, true, true>, kQuadLds);
+                else go(gg_quad_kernel<BT, DUAL, EPI, false, true>, kQuadLds);
                 return;
             }
         }

@@ -55,7 +55,7 @@ def kernels(asm, which):
 
 def test_main_loops_hold_only_the_hand_placed_vmcnt_waits(ffn_asm):
     ks = kernels(ffn_asm, "gg256_kernel")
-    assert len(ks) >= 6, sorted(ks)
+    assert len(ks) == 4, sorted(ks)   # the gradients of few rows, the gate's two products: what is launched
     seen_loops = 0
     for name, blocks in ks.items():
         for label, ins in blocks:
@@ -135,7 +135,7 @@ def test_look_ahead_draw_is_first_read_behind_a_full_wait(ffn_asm):
                 # the wait may sit in the block in front of the predicated store: look through one label
                 window = straight if any("vmcnt(0)" in y for y in straight) else back
                 assert any(y.startswith("s_waitcnt") and "vmcnt(0)" in y for y in window), (m.group(1), x)
-    assert found >= 4   # the two weight-gradient products draw their tiles, with plain and with non-temporal stores
+    assert found >= 2   # the two weight-gradient products draw their tiles
 
 
 def test_kernels_do_not_spill(ffn_asm):
