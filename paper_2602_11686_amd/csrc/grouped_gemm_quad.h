@@ -571,12 +571,11 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                         const int item = tid + u * kThreads;
                         const int trow = tile_row(i, item >> 4), tcol = col0 + (item & 15) * 8;
                         // (offsets inside a tile fit 32 bits: at most 256 rows of ldc < 2^22 elements)
-                        if (t.m0 + trow < t.m_lim && t.n0 + tcol < g.N)
-                        {
-                        u32x4* to = reinterpret_cast<u32x4*>(dst + tile_base + ((uint32_t)trow * ldc_u + (uint32_t)tcol));
-                        if constexpr (STREAM) __builtin_nontemporal_store(v[u], to);
-                        else *to = v[u];
-                    }
+                        if (t.m0 + trow < t.m_lim && t.n0 + tcol < g.N) {
+                            u32x4* to = reinterpret_cast<u32x4*>(dst + tile_base + ((uint32_t)trow * ldc_u + (uint32_t)tcol));
+                            if constexpr (STREAM) __builtin_nontemporal_store(v[u], to);
+                            else *to = v[u];
+                        }
                     }
                 };
 #pragma unroll
@@ -608,10 +607,9 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
                     } else {
                         pass(i, [&](int r, int j) { return acc[r][j]; }, static_cast<bf16_t*>(g.C0), 0);
                         if constexpr (DUAL) pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C1), 0);
-                    else pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C0), 128);
+                        else pass(i, [&](int r, int j) { return acc[r][2 + j]; }, static_cast<bf16_t*>(g.C0), 128);
                     }
                 }
-                __syncthreads();  // the staging area has been read: the A1 half under it may be requested
             }
         };
 
@@ -632,7 +630,9 @@ __global__ __launch_bounds__(kThreads) void gg_quad_kernel(const GArgs g) {
         epilogue(t, smem + (buf ? kQStaging0 : kQStaging1));
         if constexpr (RAGK)
             if (wave == 0) place_draw(pos + 2, drawn);
-        if constexpr (EPI != EPI_DH && EPI != EPI_DHP) __syncthreads();  // the staging area has been read: the A1 half under it may be requested
+        // the staging area has been read: the A1 half under it may be requested (ragged K: and the drawn entry is in the list).
+        // (The derivative epilogues' last pass ends so.)
+        if constexpr (EPI != EPI_DH && EPI != EPI_DHP) __syncthreads();
     };
 
     // ================= the tiles of this workgroup =================

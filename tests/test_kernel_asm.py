@@ -197,3 +197,15 @@ def test_large_fp32_tiles_are_built_for_the_products_that_take_them(ffn_asm):
     assert len(found) == 4, [name for name, _ in found]
     for name, body in found:
         assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", body), name
+
+
+def test_quadrant_kernel_meets_no_barrier_twice_in_a_row(ffn_asm):
+    for name, blocks in kernels(ffn_asm, "gg_quad_kernel").items():
+        for label, ins in blocks:
+            seen = False   # a barrier, and nothing after it that another wavefront could see
+            for i in ins:
+                assert not (seen and i.startswith("s_barrier")), (name, label)
+                if i.startswith("s_barrier"):
+                    seen = True
+                elif i.startswith(("ds_", "global_", "v_mfma", "s_cbranch", "s_branch")):
+                    seen = False
