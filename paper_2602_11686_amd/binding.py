@@ -105,7 +105,9 @@ def _ptr(t: Optional[torch.Tensor], dtype, shape: tuple, name: str):
         raise MoeError(f"{name} has dtype {t.dtype}, expected {dtype}")
     if tuple(t.shape) != tuple(shape):
         raise MoeError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    raise MoeError(f"{name} must be contiguous")
+    if not t.is_contiguous():
+        raise MoeError(f"{name} must be contiguous")
+    return ctypes.c_void_p(t.data_ptr())  # (a shape that is right but no tuple)
 
 
 def _ws(ws: torch.Tensor):

@@ -106,3 +106,22 @@ def test_one_time_kernel_attributes_are_set_under_a_lock():
     for name in os.listdir(csrc):
         text = open(os.path.join(csrc, name)).read()
         assert not re.search(r"static\s+(thread_local\s+)?bool\s+attr", text), name
+
+
+def test_tensor_argument_checks():
+    """What is right passes whatever sequence the expected shape comes as; each fault is named for what it is."""
+    import torch
+    from paper_2602_11686_amd import binding as B
+
+    class OnGpu(torch.Tensor):
+        is_cuda = True
+
+    t = torch.zeros(4, 6).as_subclass(OnGpu)
+    for shape in ((4, 6), [4, 6], torch.Size([4, 6])):
+        assert B._ptr(t, torch.float32, shape, "t").value == t.data_ptr(), shape
+    assert B._ptr(None, torch.float32, (4, 6), "t").value is None
+    for bad, dtype, shape, words in ((t, torch.float16, (4, 6), "dtype"), (t, torch.float32, (6, 4), "shape"),
+                                     (t, torch.float32, [4], "shape"), (t.T, torch.float32, (6, 4), "contiguous"),
+                                     (t.T, torch.float32, [6, 4], "contiguous"), (torch.zeros(4, 6), torch.float32, (4, 6), "GPU")):
+        with pytest.raises(B.MoeError, match=words):
+            B._ptr(bad, dtype, shape, "t")
