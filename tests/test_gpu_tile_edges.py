@@ -121,7 +121,7 @@ def test_ffn_bf16_k_remainder(counts, d, f):
 # (the weight gradients too, from a mean of 80 rows on: experts of no rows, one, a stage, a stage and one; tiles of at most 128
 # of their rows; none to three tiles per workgroup from the queues)
 @pytest.mark.parametrize("counts,d,f", [((0, 300, 1, 63, 64, 65, 0), 136, 72), ((0, 400, 0, 160), 64, 520), ((81, 79), 384, 640),
-                                        # 17 to 64 rows, enough column tiles to fill the chip: weights requested non-temporally
+                                        # 17 to 192 rows, enough column tiles to fill the chip: non-temporal weights and outputs
                                         ((18,) * 30 + (257, 0), 1024, 1088), ((64, 1, 129) * 12, 768, 1024),
                                         ((400, 0, 30, 200, 100, 129, 1, 90) * 8, 520, 1032), ((300, 1, 0, 128, 129), 64, 64), ((257, 200, 64), 128, 192), ((700, 0, 513), 320, 256),
                                         ((65,) * 30 + (300,) * 10, 1024, 1408), ((2000, 130, 384), 2048, 1032)])
@@ -129,32 +129,41 @@ def test_ffn_quadrants(counts, d, f):
     check_ffn(counts, d, f, torch.bfloat16, 19 * d + f)
 
 
-def test_ffn_quadrants_long_tile_list():
-    """102400 tiles, 400 for each workgroup, which keeps a ring of 512.  Contractions of 8 and of 81920 terms; each output is
-    one rounding to bf16 (2^-9 of the value) plus fp32 sums of its terms (2^-24 of their absolute values each, partly
-    cancelling: 1e-5 of them covers 168)."""
-    E, d, f, big = 256, 320 * 256, 8, 65 * 256
-    g = torch.Generator(device="cuda").manual_seed(2)
-    counts = [1] * E
+# d = 64: stages of the whole contraction, so that requests run two tiles ahead; d = 8: a remainder of K
+@pytest.mark.parametrize("d", [64, 8])
+def test_ffn_quadrants_long_tile_list(d):
+    """772 tiles for each workgroup in the first product, which keeps a ring of 512 and refills either half once.  One rounding
+    to bf16 (2^-9 of the value) plus fp32 sums (2^-24 of their terms' absolute values each, partly cancelling: 1e-5 of
+    them covers 168) of 64 or 8 and of 65528 terms; |silu'| is at most 1.1."""
+    E, f, few, big = 256, 65528, 18, 130 * 256 + 5
+    counts = [few] * E
     counts[100] = big
+    R = sum(counts)
+    # the quadrant kernel, by the rules of the dispatch: enough rows, offsets in 32 bits; and its tiles
+    assert R > 64 * E and f * f < 1 << 32 and R * f < 1 << 32
+    assert sum(-(-c // 256) for c in counts) * -(-f // 128) // 256 > 768
+    g = torch.Generator(device="cuda").manual_seed(2)
     off = torch.tensor([0] + np.cumsum(counts).tolist(), dtype=torch.int32, device="cuda")
-    R = int(off[-1])
     val = lambda *n, std=1.0: torch.empty(*n, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
-    x, w1, w3, w2 = val(R, d), val(E, d, f, std=0.02), val(E, d, f, std=0.02), val(E, f, d)
+    x, w1, w3, w2 = val(R, d), val(E, d, f, std=0.2), val(E, d, f, std=0.2), val(E, f, d)
     s = B.Shape(R, d, f, E, 1, torch.bfloat16)
     y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
     h, p, q = (torch.full((R, f), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
     B.moe_grouped_ffn_fwd_products(s, x, off, w1, w3, w2, y, h, p, q)
-    for e in (0, 99, 100, 101, 255):
-        for b in range(int(off[e]), int(off[e + 1]), 4096):
-            r = slice(b, min(b + 4096, int(off[e + 1])))
-            want, terms = h[r].float() @ w2[e].float(), h[r].float().abs() @ w2[e].float().abs()
-            assert bool(((y[r].float() - want).abs() <= want.abs() * 2.0**-8 + terms * 1e-5).all()), (e, b)
-        r = slice(int(off[e]), min(int(off[e + 1]), int(off[e]) + 300))
-        a, c = x[r].double() @ w1[e].double(), x[r].double() @ w3[e].double()
-        want = torch.nn.functional.silu(a) * c
-        assert float((h[r].double() - want).norm() / want.norm()) <= 4e-3, e   # (2^-9 and the sums of 81920 terms)
-    assert bool(torch.isfinite(y).all())
+    first = np.concatenate([[0], np.cumsum(counts)])
+    for e in range(E):
+        a1, a3, a2 = w1[e].double(), w3[e].double(), w2[e].double()
+        for b in range(first[e], first[e + 1], 2048):
+            r = slice(b, min(b + 2048, first[e + 1]))
+            xr, hr = x[r].double(), h[r].double()
+            a, c = xr @ a1, xr @ a3
+            ta, tc = (xr.abs() @ a1.abs()) * 1e-5, (xr.abs() @ a3.abs()) * 1e-5
+            sa = torch.nn.functional.silu(a)
+            assert bool(((q[r].double() - sa).abs() <= sa.abs() * 2.0**-8 + 1.1 * ta).all()), (e, b)
+            assert bool(((hr - sa * c).abs() <= (sa * c).abs() * 2.0**-8 + 1.1 * ta * c.abs() + tc * sa.abs()).all()), (e, b)
+            want, terms = hr @ a2, hr.abs() @ a2.abs()
+            assert bool(((y[r].double() - want).abs() <= want.abs() * 2.0**-8 + terms * 1e-5).all()), (e, b)
+    assert bool(torch.isfinite(p).all())
 
 
 # few rows per expert: 64-row tiles (mean at most 32) and 128-row ones (mean 33 .. 64, with and without enough column
