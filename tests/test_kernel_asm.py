@@ -147,26 +147,45 @@ def test_kernels_do_not_spill(ffn_asm):
         assert vgpr and int(vgpr.group(1)) <= 256, (m.group(1), vgpr and vgpr.group(1))
 
 
+def stage_loop(lines, mfmas):
+    """First and last line of the innermost loop with so many MFMAs."""
+    label = {m.group(1): n for n, l in enumerate(lines) if (m := re.match(r"(\.LBB\d+_\d+):", l))}
+    edges = [(label[m.group(1)], n) for n, l in enumerate(lines) if (m := re.match(r"s_c?branch\w*\s+(\.LBB\d+_\d+)", l))]
+    count = lambda h, n: sum(l.startswith("v_mfma") for l in lines[h:n])
+    head, last = max((h, n) for h, n in edges if h < n and count(h, n) == mfmas)
+    while True:   # what jumps back into it from behind, and what it jumps back to, belongs to it
+        h = min([h for h, n in edges if h < head <= n <= last] + [head])
+        n = max([n for h, n in edges if head <= h <= last < n] + [last])
+        if (h, n) == (head, last):
+            break
+        head, last = h, n
+    assert count(head, last) == mfmas
+    return head, last
+
+
 def test_quadrant_pipeline_holds_only_the_hand_placed_vmcnt_waits(ffn_asm):
-    """gg_quad_kernel counts its DMA loads across stages and tiles: in the blocks with MFMAs (one loop for tiles of more than
-    128 rows, one for the others) the compiler adds no vmcnt wait, the written ones are 8 and 6, 4 and 6, and nothing
-    is read or requested between each and its barrier; nothing spills."""
-    ks = kernels(ffn_asm, "gg_quad_kernel")
-    assert len(ks) == 19, sorted(ks)
-    for name, blocks in ks.items():
-        seen = []
-        for label, ins in blocks:
-            if not any(i.startswith("v_mfma") for i in ins):
-                continue
-            waits = [(k, int(re.search(r"vmcnt\((\d+)\)", i).group(1))) for k, i in enumerate(ins)
-                     if i.startswith("s_waitcnt") and "vmcnt" in i]
-            seen += [w for _, w in waits]
-            for k, _ in waits:
-                after = next((i for i in ins[k + 1:] if i.startswith(("s_barrier", "global_load", "ds_"))), "")
-                assert after.startswith("s_barrier"), (name, label, after)
-        # (where a stage may end early or a tile has its weights to itself the requests sit behind branches, the half loop's second wait in a block without MFMAs)
-        rest = re.search(r"ELb([01])ELb([01])ELb([01])EEE", name).groups() != ("0", "0", "0")
-        assert sorted(seen) == ([4, 6, 8] if rest else [4, 6, 6, 8]), (name, seen)
+    """gg_quad_kernel counts its DMA loads across stages and tiles.  The loop of tiles of more than 128 rows waits in a stage for
+    all but 8 of them and then for all but 6, the loop of the others for all but 4 and then 6; each wait stands in front of
+    its barrier with nothing read or requested between, and no other vmcnt wait is in the loops, whether in
+    a block with MFMAs or not; nothing spills."""
+    found = re.findall(r"^(_ZN3moe\d+gg_quad_kernel\w+):(.*?)^\.Lfunc_end", ffn_asm, re.S | re.M)
+    assert len(found) == 19, [name for name, _ in found]
+    for name, text in found:
+        lines = [l.strip() for l in text.split("\n")]
+        for mfmas, counted in ((64, [8, 6]), (32, [4, 6])):
+            head, last = stage_loop(lines, mfmas)
+            by_hand, waits = False, []
+            for n in range(head, last):
+                l = lines[n]
+                if l.startswith(";;#ASM"):
+                    by_hand = l.startswith(";;#ASMSTART")
+                elif l.startswith("s_waitcnt") and "vmcnt" in l:
+                    assert by_hand, (name, mfmas, l)
+                    waits.append(int(re.search(r"vmcnt\((\d+)\)", l).group(1)))
+                    after = next(x for x in lines[n + 1:] if x.startswith(("s_barrier", "global_", "ds_", "s_cbranch")))
+                    assert after.startswith("s_barrier"), (name, mfmas, after)
+            assert waits == counted, (name, mfmas, waits)
+            assert sum(l.startswith("s_barrier") for l in lines[head:last]) == 2, (name, mfmas)
     for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe\d+gg_quad_kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
         assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", m.group(2)), m.group(1)
 
