@@ -17,8 +17,9 @@
 //
 // bf16 path: persistent 256x256x64 kernels, 8 wavefronts, fp32 accumulators, operands brought into LDS by DMA in
 // memory order, transposing LDS reads where the contraction index is not the contiguous one: gg_quad_kernel
-// (grouped_gemm_quad.h), and gg256_kernel (grouped_gemm_bf16.h) for the gradients of few rows.  A K that is no multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is
-// left for leading dimensions and extents beyond the 32-bit offsets of these.
+// (grouped_gemm_quad.h), and gg256_kernel (grouped_gemm_bf16.h) for the gradients of few rows.  A K that is no
+// multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is left for leading
+// dimensions beyond the 32-bit offsets of these, and for operands of 2^32 elements and more.
 // fp32 path: 64x64 tiles on the fp32 matrix instructions (grouped_gemm_f32.h), 128x128 ones for products with many of them
 // (grouped_gemm_f32_large.h), same tile walk and epilogues.
 #include "moe_internal.h"
@@ -494,7 +495,9 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
     if (s->dtype == MOE_BF16) {
         constexpr bool fast_form = RAGK ? (AT == 1 && BT == 0) : (AT == 0);
         if constexpr (fast_form) {
-            // (the kernel keeps per-lane offsets in 32 bits; inside a tile they stay below 2^31 bytes)
+            // The tile kernels keep a lane's offsets from its tile's base in 32 bits: at most 256 rows of a leading dimension
+            // below 2^21 (results: 2^22) are below 2^31 bytes.  The bases are in 64 bits, so no offset asks for the bounds on R*lda
+            // and N*ldb; operands that large have not been run on the tile kernels.
             const bool ok = g.lda % 8 == 0 && g.ldb % 8 == 0 && g.N >= 8 && g.lda < (1 << 21) && g.ldb < (1 << 21) && g.ldc < (1 << 22) &&
                             (uint64_t)R * (uint64_t)g.lda < (1ull << 32) && (uint64_t)g.N * (uint64_t)g.ldb < (1ull << 32) &&
                             (!RAGK || g.M >= 8);
