@@ -19,7 +19,7 @@ SOURCES = ["moe_api.hip", "moe_gate.hip", "moe_permute.hip", "moe_ffn.hip", "moe
 HOST_SOURCES = ["moe_planner.cpp"]  # host-only C++ (the CPU planner), compiled with g++
 HOST_FLAGS = ["-O2", "-fPIC", "-std=c++17", "-ffp-contract=off", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-         # packed fp32 VALU forms are kept out of the generated code on the test machines
+         # packed fp32 VALU forms are kept out of the generated code on this hardware
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 
