@@ -474,12 +474,12 @@ static void launch_f32(const GArgs& g, int64_t tiles, hipStream_t st) {
 
 // Whether a product with B in k-row form is one for 128x128 tiles, by their number (ragged M: an upper bound) and the mean rows per
 // expert.  Kernel times, 128x128 over 64x64 tiles:
-//   gradients, dW2: 1024 to 1536 tiles 0.87 to 1.25, mostly above 1; 2816 0.91 to 0.93; 11264 to 28672 0.77 to 0.94
-//     dW1|dW3: 512 1.03 to 1.09; 2040 0.97 to 1.03; 2048 0.87 to 0.95; 2816 to 57344 0.75 to 0.97
-//   forward, two matrices, 512 rows per expert and more: 1056 to 1152 1.05 to 1.10; 1760 1.00 to 1.04; 2112 to 45408 0.86 to 0.99
+//   gradients, dW2: 16 to 512 tiles 1.24 to 3.5; 1024 to 1536 0.87 to 1.20, mostly above 1; 2816 and more 0.77 to 0.94
+//     dW1|dW3: 32 to 512 1.03 to 3.3; 2040 0.97 to 1.03; 2048 0.87 to 0.95; 2816 to 57344 0.75 to 0.97
+//   forward, two matrices, 512 rows per expert and more: 576 to 1152 0.87 to 1.10; 1760 1.00 to 1.04; 2112 to 45408 0.86 to 0.99
 //     fewer rows, 2112 to 5376 0.97 to 1.40
-//   forward, one matrix, 1024 rows and more: 576 to 2304 0.92 to 1.40; 4128 to 18432 0.93 to 1.00; fewer rows 0.99 to 1.9
-// (the products with B in row form 0.95 to 2.1, above 1 but for 3 of 66).  Whole passes in us, 128x128 tiles from 512 on
+//   forward, one matrix, 1000 rows and more: 288 to 2304 0.92 to 1.41; 4128 to 18432 0.93 to 1.00; fewer rows 0.99 to 1.9
+// (below 1 under the lines: mostly a single expert; the products with B in row form 0.95 to 2.1, above 1 in 79 of 84).  Whole passes in us, 128x128 tiles from 512 on
 // in every product, 64x64 tiles alone, this rule:
 //   training, 8 experts of 4096 x 14336, 512 tokens 14153, 12293, 11719; 4096 73790, 75478, 73338; 16384 276856, 293322, 278733
 //     128 of 2048 x 768, 16384: 32699, 33754, 32443   16 of 4096 x 7168, 4096: 71890, 74683, 71773   8 of 1024 x 2816, 2048: 2363, 2156, 2132
