@@ -21,7 +21,8 @@
 // multiple of 64 ends in a stage padded with zeros.  The plain 128x128x64 kernel below is left for leading
 // dimensions beyond the 32-bit offsets of these, and for operands of 2^32 elements and more.
 // fp32 path: 64x64 tiles on the fp32 matrix instructions (grouped_gemm_f32.h), 128x128 ones for products with many of them
-// (grouped_gemm_f32_large.h), same tile walk and epilogues.
+// (grouped_gemm_f32_large.h), 32x32 ones with the contraction split over the wavefronts for products with few
+// (grouped_gemm_f32_split.h), same tile walk and epilogues.
 #include "moe_internal.h"
 
 namespace moe {
@@ -386,6 +387,7 @@ namespace moe {
 }  // namespace moe
 #include "grouped_gemm_f32.h"
 #include "grouped_gemm_f32_large.h"
+#include "grouped_gemm_f32_split.h"
 namespace moe {
 
 // =============================== host dispatch ================================
@@ -465,6 +467,32 @@ static dim3 f32_grid(int64_t tiles) {
     return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
 }
 
+// Whether a product is one for gg_f32_split_kernel, by the number of 64x64 tiles (ragged M: an upper bound) and the mean rows per
+// expert.  Kernel times, gg_f32_kernel -> gg_f32_split_kernel (us):
+//   one matrix, tiles: 32 9.6 -> 5.2 (contraction 512: 14.6 -> 6.9)   64 9.3 -> 6.0   96 47 -> 28   128 27 -> 17   160 68 -> 31   192 27 -> 23
+//     contraction of 512: 256 16 -> 18   288 23 -> 27   320 38 -> 40   640 34 -> 36  (1024 and more: 288 42 -> 34, 320 43 -> 36, 264 36 -> 39)
+//   two matrices: 128 8.0 -> 6.7   192 8.7 -> 11.0, 15 -> 22 (contraction 128)   320 23 -> 29 (256)
+//     of 2048 and more: 192 52 -> 42   256 97 -> 80   320 81 -> 65   640 149 -> 145
+//   at most 16 rows per expert (a tile of 64 rows would be empty but for a quarter): 64 experts of 2048 x 1408, 4 rows, the products
+//     over ragged rows 538, 262, 265, 475 -> 411, 178, 174, 349; 8 of 1024 x 2816, 4 rows 65, 66, 40, 118 -> 64, 32, 27, 37, 16 rows 69,
+//     68, 43, 122 -> 64, 31, 25, 39; 4 of 2048 x 4096, 8 rows 99, 94, 47, 170 -> 104, 31, 30, 54   32 rows: 46, 26, 28, 42 -> 57, 32, 30, 46
+//   gradients: 48 51 -> 17   64 16 -> 7.4   96 53 -> 29   128 29 -> 17, 6.8 -> 6.1   256 11 -> 13, 30 -> 30   640 and more 1.1 to 2.8
+//     times as long (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
+template <bool DUAL, bool RAGK>
+static bool f32_split_tiles(const GArgs& g, int64_t tiles, int64_t R) {
+    if (RAGK) return tiles <= 128;
+    if (R <= 16 * (int64_t)g.E) return true;
+    if (DUAL) return tiles <= 128 || (tiles <= 320 && g.K >= 2048);
+    return tiles <= 192;
+}
+
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
+static void launch_f32_split(const GArgs& g, int64_t tiles, hipStream_t st) {
+    auto kern = gg_f32_split_kernel<AT, BT, DUAL, EPI, RAGK>;
+    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kF32SplitLds);
+    kern<<<f32_grid(tiles), 256, kF32SplitLds, st>>>(g);
+}
+
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_f32(const GArgs& g, int64_t tiles, hipStream_t st) {
     auto kern = gg_f32_kernel<AT, BT, DUAL, EPI, RAGK>;
@@ -532,6 +560,10 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             const int64_t n = (g.N + n_out - 1) / n_out;
             return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * g.E : (R + bm - 1) / bm + g.E);  // (upper bound with ragged M)
         };
+        if (f32_split_tiles<DUAL, RAGK>(g, tiles(kF32Tile), R)) {
+            launch_f32_split<AT, BT, DUAL, EPI, RAGK>(g, tiles(kF32SplitTile), st);
+            return;
+        }
         if constexpr (BT == 0) {
             const int64_t large = tiles(kF32LargeTile);
             if (f32_large_tiles<DUAL, RAGK>(large, R, g.E)) {

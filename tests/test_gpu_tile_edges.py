@@ -72,18 +72,34 @@ def check_ffn(counts, d, f, dtype, seed, backward=True, wstd=0.05):
         assert not buf.dw1[e].any() and not buf.dw3[e].any() and not buf.dw2[e].any()
 
 
-# fp32, 64x64 tiles (too few for 128x128 ones in every product): remainders of rows, columns and k-stages
+# fp32, 32x32 and 64x64 tiles (too few for 128x128 ones in every product): remainders of rows, columns and k-stages
 @pytest.mark.parametrize("counts,d,f", [((1, 0, 63, 64, 65, 130), 68, 36), ((5, 17), 4, 132), ((0, 129, 300), 64, 16),
                                         ((1200, 127, 0, 1), 2048, 260), ((700, 900), 260, 2048)])
 def test_ffn_f32(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 7 * d + f)
 
 
-# fp32, a ring of three 32-wide k-stages: none to five of them in either contraction, with every kind of remainder
+# fp32, 32-wide k-stages: none to five of them in either contraction, with every kind of remainder
 @pytest.mark.parametrize("counts,d,f", [((28, 32, 36, 0), 32, 64), ((64, 68, 96, 1), 96, 28), ((4, 31, 33, 160), 100, 128),
                                         ((130, 3), 36, 160)])
 def test_ffn_f32_stages(counts, d, f):
     check_ffn(counts, d, f, torch.float32, 5 * d + f)
+
+
+# fp32, 32x32 tiles with the contraction split over four wavefronts: tiles, columns and slabs of 32 with remainders; fewer slabs
+# than wavefronts, one more than they can hold in their rings, segments that begin in the middle of the four; few rows per expert
+# with many tiles.  The last case is over every line of the dispatch: 64x64 tiles in all products, with remainders everywhere.
+@pytest.mark.parametrize("split,counts,d,f", [(True, (31, 0, 32, 33, 1), 36, 68), (True, (2, 5), 4, 160), (True, (65, 0, 127), 132, 292),
+                                              (True, (300, 4), 100, 36), (True, (9, 0, 16, 1, 40, 3) * 4, 1028, 776),
+                                              (False, (65, 130, 0, 63, 1, 300), 836, 1092)])
+def test_ffn_f32_split(split, counts, d, f):
+    up = lambda n, m: -(-n // m)
+    E, R = len(counts), sum(counts)
+    rows, few = up(R, 64) + E, R <= 16 * E
+    over_rows = [few or rows * up(f, 32) <= 128, few or rows * up(d, 64) <= 192, few or rows * up(f, 64) <= 192]
+    grads = [E * up(f, 64) * up(d, 64) <= 128, E * up(d, 64) * up(f, 32) <= 128]
+    assert all(over_rows) if split else not any(over_rows + grads)
+    check_ffn(counts, d, f, torch.float32, 3 * d + f)
 
 
 # fp32, 128x128 tiles: enough of them, and of rows per expert, in the named products (an upper bound with ragged rows, as the
