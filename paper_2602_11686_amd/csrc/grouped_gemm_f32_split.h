@@ -62,20 +62,19 @@ struct F32SlabIssue {
     }
 };
 
+// One workgroup's tile: workgroup b0 of the product.
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
-__global__ __launch_bounds__(256) void gg_f32_split_kernel(const GArgs g) {
+__device__ __forceinline__ void f32_split_tile(const GArgs& g, int b0, char* smem) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
     using TA = F32SlabIssue<AT>;
     using TB = F32SlabIssue<BT == 0 ? 1 : 0>;
     constexpr int BM = kF32SplitTile, S = kF32SplitStages;
     constexpr int WB = DUAL ? 1 : 2;  // blocks that share a read of B in k-row form
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n_out = DUAL ? BM / 2 : BM;
     const int n_tiles = (g.N + n_out - 1) / n_out;
 
-    // ---- which tile (as in gg_f32_kernel; the grid is a multiple of 64) ----
-    const int b0 = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    // ---- which tile (as in gg_f32_kernel; a product has a multiple of 64 workgroups) ----
     const int L = (((b0 >> 6) * 8 + (b0 & 7)) << 3) + ((b0 >> 3) & 7);
     int e, m0, m_lim, kbeg, kend, m, nt;
     if constexpr (RAGK) {
@@ -205,6 +204,28 @@ __global__ __launch_bounds__(256) void gg_f32_split_kernel(const GArgs g) {
         const f32x4v v0 = sum(wave), v1 = DUAL ? sum(2 + wave) : v0;
         epilogue_x4<float, EPI>(g, (RAGK ? (int64_t)e * g.strideC : 0) + (int64_t)row * g.ldc + col, v0, v1);
     }
+}
+
+template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
+__global__ __launch_bounds__(256) void gg_f32_split_kernel(const GArgs g) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    f32_split_tile<AT, BT, DUAL, EPI, RAGK>(g, (int)(blockIdx.y * gridDim.x + blockIdx.x), smem);
+}
+
+// The three products behind dH, which need nothing of one another, in one launch: as launches of their own each leaves most
+// of the chip idle and pays its start and its end.  The rows' gradient first, its contraction is the longest.  256 tokens, 8
+// experts of 128 x 256 (us): four launches (the experts' order among them) of 6.9, 1.6, 4.6, 6.1 -> 10.2; the training pass, bound by
+// the host's launches, 89 -> 80.
+struct F32SplitBwdArgs {
+    GArgs dx, dw2, dw13;
+    int dx_blocks, dw2_blocks;
+};
+__global__ __launch_bounds__(256) void gg_f32_split_bwd_kernel(const F32SplitBwdArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    if (b < a.dx_blocks) f32_split_tile<0, 1, false, EPI_STORE, false>(a.dx, b, smem);
+    else if (b < a.dx_blocks + a.dw2_blocks) f32_split_tile<1, 0, false, EPI_STORE, true>(a.dw2, b - a.dx_blocks, smem);
+    else f32_split_tile<1, 0, true, EPI_STORE2, true>(a.dw13, b - a.dx_blocks - a.dw2_blocks, smem);
 }
 
 }  // namespace moe

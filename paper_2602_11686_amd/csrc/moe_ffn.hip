@@ -467,6 +467,14 @@ static dim3 f32_grid(int64_t tiles) {
     return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
 }
 
+// number of bm x bm tiles (ragged M: an upper bound)
+template <bool DUAL, bool RAGK>
+static int64_t f32_tiles(const GArgs& g, int64_t R, int bm) {
+    const int n_out = DUAL ? bm / 2 : bm;
+    const int64_t n = (g.N + n_out - 1) / n_out;
+    return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * g.E : (R + bm - 1) / bm + g.E);
+}
+
 // Whether a product is one for gg_f32_split_kernel, by the number of 64x64 tiles (ragged M: an upper bound) and the mean rows per
 // expert.  Kernel times, gg_f32_kernel -> gg_f32_split_kernel (us):
 //   one matrix, tiles: 32 9.6 -> 5.2 (contraction 512: 14.6 -> 6.9)   64 9.3 -> 6.0   96 47 -> 28   128 27 -> 17   160 68 -> 31   192 27 -> 23
@@ -479,7 +487,8 @@ static dim3 f32_grid(int64_t tiles) {
 //   gradients: 48 51 -> 17   64 16 -> 7.4   96 53 -> 29   128 29 -> 17, 6.8 -> 6.1   256 11 -> 13, 30 -> 30   640 and more 1.1 to 2.8
 //     times as long (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
 template <bool DUAL, bool RAGK>
-static bool f32_split_tiles(const GArgs& g, int64_t tiles, int64_t R) {
+static bool f32_split_tiles(const GArgs& g, int64_t R) {
+    const int64_t tiles = f32_tiles<DUAL, RAGK>(g, R, kF32Tile);
     if (RAGK) return tiles <= 128;
     if (R <= 16 * (int64_t)g.E) return true;
     if (DUAL) return tiles <= 128 || (tiles <= 320 && g.K >= 2048);
@@ -487,10 +496,18 @@ static bool f32_split_tiles(const GArgs& g, int64_t tiles, int64_t R) {
 }
 
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
-static void launch_f32_split(const GArgs& g, int64_t tiles, hipStream_t st) {
+static void launch_f32_split(const GArgs& g, int64_t R, hipStream_t st) {
     auto kern = gg_f32_split_kernel<AT, BT, DUAL, EPI, RAGK>;
     ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kF32SplitLds);
-    kern<<<f32_grid(tiles), 256, kF32SplitLds, st>>>(g);
+    kern<<<f32_grid(f32_tiles<DUAL, RAGK>(g, R, kF32SplitTile)), 256, kF32SplitLds, st>>>(g);
+}
+
+static void launch_f32_split_bwd(const GArgs& dx, const GArgs& dw2, const GArgs& dw13, int64_t R, hipStream_t st) {
+    auto blocks = [](int64_t tiles) { return (int)((tiles + 63) / 64 * 64); };
+    F32SplitBwdArgs a{dx, dw2, dw13, blocks(f32_tiles<false, false>(dx, R, kF32SplitTile)), blocks(f32_tiles<false, true>(dw2, R, kF32SplitTile))};
+    const int64_t all = (int64_t)a.dx_blocks + a.dw2_blocks + blocks(f32_tiles<true, true>(dw13, R, kF32SplitTile));
+    ensure_dynamic_lds(reinterpret_cast<const void*>(&gg_f32_split_bwd_kernel), kF32SplitLds);
+    gg_f32_split_bwd_kernel<<<f32_grid(all), 256, kF32SplitLds, st>>>(a);
 }
 
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
@@ -555,23 +572,18 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
         else grid = dim3((g.N + BN - 1) / BN, (unsigned)((R + BM - 1) / BM + g.E), 1);
         gg_bf16_kernel<AT, BT, DUAL, EPI, RAGK><<<grid, 256, 0, st>>>(g);
     } else {
-        auto tiles = [&](int bm) {
-            const int n_out = DUAL ? bm / 2 : bm;
-            const int64_t n = (g.N + n_out - 1) / n_out;
-            return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * g.E : (R + bm - 1) / bm + g.E);  // (upper bound with ragged M)
-        };
-        if (f32_split_tiles<DUAL, RAGK>(g, tiles(kF32Tile), R)) {
-            launch_f32_split<AT, BT, DUAL, EPI, RAGK>(g, tiles(kF32SplitTile), st);
+        if (f32_split_tiles<DUAL, RAGK>(g, R)) {
+            launch_f32_split<AT, BT, DUAL, EPI, RAGK>(g, R, st);
             return;
         }
         if constexpr (BT == 0) {
-            const int64_t large = tiles(kF32LargeTile);
+            const int64_t large = f32_tiles<DUAL, RAGK>(g, R, kF32LargeTile);
             if (f32_large_tiles<DUAL, RAGK>(large, R, g.E)) {
                 gg_f32_large_kernel<AT, DUAL, EPI, RAGK><<<f32_grid(large), 256, 0, st>>>(g);
                 return;
             }
         }
-        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, tiles(kF32Tile), st);
+        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, f32_tiles<DUAL, RAGK>(g, R, kF32Tile), st);
     }
 }
 
@@ -848,11 +860,6 @@ static moe_status ffn_bwd_impl(const char* who, const moe_shape* s, int groups, 
     void* H = cv.take(rf);  // (not used in the products form, which reads h_save)
     void* dA = cv.take(rf);
     void* dB = cv.take(rf);
-    int32_t* order = static_cast<int32_t*>(cv.take(1024));
-    void* zero_row = cv.take(512);
-    uint32_t* sched = static_cast<uint32_t*>(cv.take(kBwdLaunches * kSchedBytes));
-    expert_order_kernel<<<1, 256, 0, st>>>(offsets, groups, order, static_cast<uint32_t*>(zero_row), sched,
-                                           kBwdLaunches * kSchedWords);
     if (!a_save || !b_save) {  // expert-only recomputation: rebuild A and B (H is rewritten below anyway)
         void* A = cv.take(rf);
         void* B = cv.take(rf);
@@ -870,34 +877,41 @@ static moe_status ffn_bwd_impl(const char* who, const moe_shape* s, int groups, 
         if (h_save) launch_gg<0, 1, false, EPI_DHP, false>(s, g, R, st);  // dA = dH*P, dB = dH*Q
         else launch_gg<0, 1, false, EPI_DH, false>(s, g, R, st);
     }
-    {  // dXp = dA * W1^T + dB * W3^T
-        GArgs g{};
-        g.offsets = offsets; g.E = groups; g.N = s->d; g.K = s->f; g.nseg = 2;
-        g.expert_of_group = expert_of_group; g.n_weights = s->E;
-        g.seg[0] = {dA, w1, nullptr};
-        g.seg[1] = {dB, w3, nullptr};
-        g.lda = s->f; g.ldb = s->f; g.strideB = (int64_t)s->d * s->f;
-        g.C0 = dx_perm; g.ldc = s->d;
-        launch_gg<0, 1, false, EPI_STORE, false>(s, g, R, st);
+    GArgs gx{};  // dXp = dA * W1^T + dB * W3^T
+    gx.offsets = offsets; gx.E = groups; gx.N = s->d; gx.K = s->f; gx.nseg = 2;
+    gx.expert_of_group = expert_of_group; gx.n_weights = s->E;
+    gx.seg[0] = {dA, w1, nullptr};
+    gx.seg[1] = {dB, w3, nullptr};
+    gx.lda = s->f; gx.ldb = s->f; gx.strideB = (int64_t)s->d * s->f;
+    gx.C0 = dx_perm; gx.ldc = s->d;
+    GArgs g2{};  // dW2[e] = H_e^T * dYp_e
+    g2.offsets = offsets; g2.E = groups; g2.M = s->f; g2.N = s->d; g2.nseg = 1;
+    g2.seg[0] = {h_save ? h_save : H, dy_perm, nullptr};
+    g2.lda = s->f; g2.ldb = s->d; g2.strideC = (int64_t)s->f * s->d;
+    g2.C0 = dw2; g2.ldc = s->d;
+    GArgs g13{};  // [dW1|dW3][e] = Xp_e^T * [dA_e|dB_e]
+    g13.offsets = offsets; g13.E = groups; g13.M = s->d; g13.N = s->f; g13.nseg = 1;
+    g13.seg[0] = {x_perm, dA, dB};
+    g13.lda = s->d; g13.ldb = s->f; g13.strideC = (int64_t)s->d * s->f;
+    g13.C0 = dw1; g13.C1 = dw3; g13.ldc = s->f;
+    if (s->dtype == MOE_F32 && f32_split_tiles<false, false>(gx, R) && f32_split_tiles<false, true>(g2, R) &&
+        f32_split_tiles<true, true>(g13, R)) {
+        // (neither the experts' order nor the tile queues: the tiles are few enough to run all at once)
+        launch_f32_split_bwd(gx, g2, g13, R, st);
+        return launch_status(who);
     }
-    {  // dW2[e] = H_e^T * dYp_e
-        GArgs g{};
-        g.offsets = offsets; g.E = groups; g.M = s->f; g.N = s->d; g.nseg = 1;
-        g.seg[0] = {h_save ? h_save : H, dy_perm, nullptr};
-        g.lda = s->f; g.ldb = s->d; g.strideC = (int64_t)s->f * s->d;
-        g.C0 = dw2; g.ldc = s->d; g.order = order; g.zero_row = zero_row;
-        g.sched = sched;
-        launch_gg<1, 0, false, EPI_STORE, true>(s, g, R, st);
-    }
-    {  // [dW1|dW3][e] = Xp_e^T * [dA_e|dB_e]
-        GArgs g{};
-        g.offsets = offsets; g.E = groups; g.M = s->d; g.N = s->f; g.nseg = 1;
-        g.seg[0] = {x_perm, dA, dB};
-        g.lda = s->d; g.ldb = s->f; g.strideC = (int64_t)s->d * s->f;
-        g.C0 = dw1; g.C1 = dw3; g.ldc = s->f; g.order = order; g.zero_row = zero_row;
-        g.sched = sched + kSchedWords;
-        launch_gg<1, 0, true, EPI_STORE2, true>(s, g, R, st);
-    }
+    launch_gg<0, 1, false, EPI_STORE, false>(s, gx, R, st);
+    int32_t* order = static_cast<int32_t*>(cv.take(1024));
+    void* zero_row = cv.take(512);
+    uint32_t* sched = static_cast<uint32_t*>(cv.take(kBwdLaunches * kSchedBytes));
+    expert_order_kernel<<<1, 256, 0, st>>>(offsets, groups, order, static_cast<uint32_t*>(zero_row), sched,
+                                           kBwdLaunches * kSchedWords);
+    g2.order = g13.order = order;
+    g2.zero_row = g13.zero_row = zero_row;
+    g2.sched = sched;
+    g13.sched = sched + kSchedWords;
+    launch_gg<1, 0, false, EPI_STORE, true>(s, g2, R, st);
+    launch_gg<1, 0, true, EPI_STORE2, true>(s, g13, R, st);
     return launch_status(who);
 }
 
