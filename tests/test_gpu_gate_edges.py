@@ -35,13 +35,6 @@ SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260,
          (905, 768, 200, 8, torch.bfloat16), (2000, 264, 129, 2, torch.float32)]  # 57 and 125 token tiles: no even split of 256
 
 
-# bf16 kernels that contract the whole hidden dimension: one to 16 expert tiles, 16 and 32 tokens per workgroup with a remainder,
-# fewer k-steps than wavefronts, k-steps with a remainder, more than a wavefront's first pair of chunks
-SIZES += [(2049, d, E, k, torch.bfloat16) for d, E, k in [(8, 3, 2), (24, 17, 3), (1096, 16, 4), (264, 40, 2), (2072, 100, 8), (520, 200, 6)]]
-SIZES += [(8191, 40, 20, 2, torch.bfloat16), (8192, 72, 32, 2, torch.bfloat16), (8205, 296, 50, 2, torch.bfloat16),
-          (8205, 296, 9, 2, torch.bfloat16), (16401, 136, 128, 3, torch.bfloat16), (1025, 2048, 200, 4, torch.bfloat16)]
-
-
 @pytest.mark.parametrize("least_ws", [False, True])  # with the least workspace the dimension is never split
 @pytest.mark.parametrize("T,d,E,k,dtype", SIZES)
 def test_gate_topk_edges(T, d, E, k, dtype, least_ws):
