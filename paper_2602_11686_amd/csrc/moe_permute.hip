@@ -466,33 +466,45 @@ __global__ __launch_bounds__(256) void permute_scatter_rows_kernel(const u32x4* 
 }
 
 // ---- 1 to 4 in one launch, for few pairs -----------------------------------------------------
-// Up to kSmallPairs pairs every workgroup sorts all of them by itself in LDS (16 wavefronts, one chunk of 256 pairs
-// each; about what one of the launches above waits for) and then copies its share of the rows; the first one
+// Up to kSmallPairs pairs every workgroup sorts all of them by itself in LDS (16 wavefronts, a chunk of 64, 128 or 256 pairs each: a
+// wavefront ranks 64 at a time, one after the other) and then copies its share of the rows; the first one
 // also writes the tables.  What bounds three launches at these sizes is that each waits for the one before, and the
-// host's time to make them (us in a graph, and launched one by one): 64 tokens, top-8 of 128 experts, 2048 wide: 7.6 -> 6.4,
-// 17 -> 11; 512 tokens, top-4 of 64: 9.1 -> 6.5, 17 -> 11.  Past 2^19 pieces of x the copy is what counts and its own kernel
-// the better one (us, three launches and one; 1024 tokens, top-4 of 16, 4096 wide, just within: 14.4, 13.5; 1000 of 5120:
-// 15.7, 16.3; 1000 of 8192: 21.2, 22.8; 4096 tokens, top-1 of 4, 1536 wide: 10.9, 11.6; of 64 experts 12.0, 10.8).
+// host's time to make them (us in a graph, and launched one by one: 64 tokens, top-8 of 128 experts, 2048 wide 7.6 -> 6.4,
+// 17 -> 11).  What bounds the one launch is its chain: the pairs, the ranks, x, the stores.  So x is requested before the pairs are
+// sorted, and where the pieces of x would leave units without work the slots of a token go to several threads.  us, chunks of
+// 256, x behind the ranks, all slots by one thread -> this: 8 tokens, top-2 of 8, 4096 wide 5.4 -> 3.7; 64, top-8 of 128, 2048 6.5 -> 4.1;
+// 256, top-4 of 64, 2048 6.2 -> 4.4; 512 of these 6.7 -> 5.6; 1024, top-4 of 16, 4096 13.8 -> 11.2; 4096, top-1 of 8, 512 7.2 -> 7.2.
+// Past 2^19 pieces of x the copy is what counts and its own kernel the better one (us, three launches and one launch before these
+// changes; 1024 tokens, top-4 of 16, 4096 wide, just within: 14.4, 13.5; 1000 of 5120: 15.7, 16.3; 1000 of 8192: 21.2, 22.8; 4096 tokens,
+// top-1 of 4, 1536 wide: 10.9, 11.6; of 64 experts 12.0, 10.8).
 constexpr uint32_t kSmallPieces = 1u << 19;
-constexpr int kSmallWaves = 16, kSmallChunk = 256, kSmallPairs = kSmallWaves * kSmallChunk;
+constexpr int64_t kSmallItems = 1 << 18;  // a thread's single item in a grid that fills the chip
+constexpr int kSmallWaves = 16, kSmallPairs = kSmallWaves * 256;
+// CHUNK: pairs per wavefront.  An item of the copy is a 16-byte piece of x and one of `parts` sets of the k slots (s, s + parts, ...).
+template <int CHUNK>
 __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(
     const int32_t* __restrict__ ids, int R, int E, int k, const u32x4* __restrict__ x, int vecs_per_row, uint32_t pieces,
-    int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ row_of_pair,
+    int parts, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ row_of_pair,
     int32_t* __restrict__ pair_of_row, u32x4* __restrict__ x_perm) {
     __shared__ int32_t next[kSmallWaves * MOE_MAX_EXPERTS];  // [wave][expert]: histogram, then the next row
     __shared__ int32_t total[MOE_MAX_EXPERTS], off[MOE_MAX_EXPERTS + 1];
     __shared__ int32_t rows[kSmallPairs];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    int e[kSmallChunk / 64];
+    int e[CHUNK / 64];
 #pragma unroll
-    for (int i = 0; i < kSmallChunk / 64; ++i) {
-        const int p = wave * kSmallChunk + i * 64 + lane;
+    for (int i = 0; i < CHUNK / 64; ++i) {
+        const int p = wave * CHUNK + i * 64 + lane;
         e[i] = p < R ? ids[p] : -1;
     }
+    // this thread's first piece is on its way while the pairs are sorted
+    const uint32_t items = pieces * (uint32_t)parts, step = gridDim.x * (uint32_t)(kSmallWaves * 64);
+    uint32_t item = blockIdx.x * (uint32_t)(kSmallWaves * 64) + tid;
+    u32x4 val = {0, 0, 0, 0};
+    if (item < items) val = x[item % pieces];
     for (int i = tid; i < kSmallWaves * E; i += kSmallWaves * 64) next[i] = 0;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSmallChunk / 64; ++i)
+    for (int i = 0; i < CHUNK / 64; ++i)
         if (e[i] >= 0) atomicAdd(&next[wave * E + e[i]], 1);
     __syncthreads();
     if (tid < E) {  // rows of the expert in earlier chunks
@@ -536,8 +548,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(
     }
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-    for (int i = 0; i < kSmallChunk / 64; ++i) {
-        const int p = wave * kSmallChunk + i * 64 + lane;
+    for (int i = 0; i < CHUNK / 64; ++i) {
+        const int p = wave * CHUNK + i * 64 + lane;
         const bool live = e[i] >= 0;
         uint64_t same = __ballot(live);
         if (!live) same = 0;
@@ -560,10 +572,12 @@ __global__ __launch_bounds__(kSmallWaves * 64) void permute_small_kernel(
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    for (uint32_t i = blockIdx.x * blockDim.x + tid; i < pieces; i += gridDim.x * blockDim.x) {
-        const uint32_t t = i / (uint32_t)vecs_per_row, v = i - t * (uint32_t)vecs_per_row;
-        const u32x4 val = __builtin_nontemporal_load(&x[i]);
-        for (int s = 0; s < k; ++s) __builtin_nontemporal_store(val, &x_perm[(size_t)rows[t * k + s] * vecs_per_row + v]);
+    while (item < items) {
+        const uint32_t q = item / pieces, piece = item - q * pieces;
+        const uint32_t t = piece / (uint32_t)vecs_per_row, v = piece - t * (uint32_t)vecs_per_row;
+        for (int s = (int)q; s < k; s += parts) __builtin_nontemporal_store(val, &x_perm[(size_t)rows[t * k + s] * vecs_per_row + v]);
+        item += step;
+        if (item < items) val = x[item % pieces];
     }
 }
 
@@ -763,9 +777,16 @@ static moe_status permute_launch(const char* who, const moe_shape* s, const void
     const int R = s->T * s->k, E = s->E;
     const int64_t pieces = x_perm ? (int64_t)s->T * (int64_t)((size_t)s->d * el_size(s) / 16) : 0;
     if (R <= kSmallPairs && pieces <= kSmallPieces) {
-        permute_small_kernel<<<grid_for(pieces, kSmallWaves * 64, 256), kSmallWaves * 64, 0, st>>>(
-            topk_ids, R, E, s->k, static_cast<const u32x4*>(x), (int)((size_t)s->d * el_size(s) / 16), (uint32_t)pieces, counts,
-            offsets, row_of_pair, pair_of_row, static_cast<u32x4*>(x_perm));
+        const int64_t fit = pieces ? kSmallItems / pieces : 1;
+        const int parts = fit >= s->k ? s->k : fit < 1 ? 1 : (int)fit;
+        auto go = [&](auto kern) {
+            kern<<<grid_for(pieces * parts, kSmallWaves * 64, 256), kSmallWaves * 64, 0, st>>>(
+                topk_ids, R, E, s->k, static_cast<const u32x4*>(x), (int)((size_t)s->d * el_size(s) / 16), (uint32_t)pieces, parts,
+                counts, offsets, row_of_pair, pair_of_row, static_cast<u32x4*>(x_perm));
+        };
+        if (R <= kSmallWaves * 64) go(permute_small_kernel<64>);
+        else if (R <= kSmallWaves * 128) go(permute_small_kernel<128>);
+        else go(permute_small_kernel<256>);
         return launch_status(who);
     }
     const int nchunks = num_chunks(R);
