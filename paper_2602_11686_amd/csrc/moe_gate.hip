@@ -43,38 +43,48 @@ size_t gate_workspace_bytes(const moe_shape* s) {
 }
 
 // ---- bf16 forward on the matrix cores ------------------------------------------------------
-// One workgroup = 32 tokens, 4 wavefronts; wavefront w contracts the quarter
-// [w*d/4, (w+1)*d/4) of the hidden dimension for all 32 tokens and all experts with MFMA
-// 32x32x16 (operands straight from global memory: a lane reads 64 contiguous bytes of its
-// token row / of its expert's row of the transposed gate weight per 64-wide k chunk), the
-// four partial sums meet in LDS and are added in a fixed order, then each wavefront runs
-// the top-k of 8 tokens.
+// One workgroup = 16 or 32 tokens; each of its wavefronts contracts a part of the hidden dimension for all tokens and all experts,
+// with operands straight from global memory: for a 16x16x32 MFMA a lane reads 16 bytes of its token's row, two lanes 32 contiguous
+// bytes, and the next MFMA takes the other halves of those lines.  The partial sums meet in LDS and are added in a fixed order,
+// then each wavefront runs the top-k of its share of the tokens.
+//
+// The order of the sums is that of 32x32x16 MFMAs whose lanes hold k and k+32 (which k-values a step takes, how many parts there
+// are): logits, and with them the picks among near equals, are the same bit for bit as from those.
+//
+// What bounds it is reading the tokens and, per workgroup, the whole gate weight (7 to 12 TB/s of both out of L2), and up to some
+// 4000 tokens the chain of one workgroup.  Measured (the whole call with the packing of the weight, us; 32 tokens in
+// 32x32x16 MFMAs, whose lanes read pieces of 16 bytes 64 bytes apart -> this): 1777 x 4096, 16 experts 19 -> 11; 4096 x 4096, 16 22 -> 13;
+// 2048 x 2048, 64 19 -> 11; 8192 x 2048, 64 21 -> 18; 4096 x 2048, 128 45 -> 20; 16384 x 2048, 128 56 -> 47; 16384 x 4096, 8 42 -> 38
+// (3.6 TB/s); 16384 x 2048, 160 137 -> 88; 16384 x 6144, 32 59 -> 61.
 typedef __bf16 gbf16x8 __attribute__((ext_vector_type(8)));
-typedef float gf32x16 __attribute__((ext_vector_type(16)));
 typedef float gf32x4 __attribute__((ext_vector_type(4)));
-constexpr int kGateMT = 32;
 
 // The gate weight in the order the MFMA lanes of gate_topk_mfma_kernel consume it ("fragment-major"): the
 // 64 lanes x 8 values of one B operand are 1 KB of consecutive memory, so that every operand load of a
 // wavefront is one fully coalesced 1 KB read (a plain transposed copy makes each lane read 16 bytes of a
-// different row: 32 cache lines per load instruction).  Block index: ((wavefront's K range, 64-wide chunk),
-// expert tile j, k-step s4); inside a block lane (l32, kg) holds expert j*32 + l32,
-// k = range*kq + chunk*64 + kg*32 + s4*8 + 0..7.  Experts past E are zero.
-__global__ void gate_pack_wg_kernel(const bf16_t* __restrict__ wg, bf16_t* __restrict__ wfrag, int d, int E, int NT,
-                                    int NW) {
-    const int64_t n = (int64_t)d * NT * 32;
-    const int kq = d / NW, nchunk = kq / 64;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int z = (int)(i & 7), lane = (int)((i >> 3) & 63), s4 = (int)((i >> 9) & 3);
-        const int64_t blk = i >> 11;  // (range*nchunk + chunk)*NT + j
-        const int j = (int)(blk % NT);
-        const int64_t rc = blk / NT;
-        const int ci = (int)(rc % nchunk), w = (int)(rc / nchunk);
-        const int e = j * 32 + (lane & 31);
-        const int k = w * kq + ci * 64 + (lane >> 5) * 32 + s4 * 8 + z;
-        wfrag[i] = e < E ? wg[(size_t)k * E + e] : (bf16_t)0;
+// different row).  Block index: (k-step, expert tile j); inside a block lane (l16, kg) holds expert j*16 + l16 and, of the
+// 64-wide chunk step/2, k = (kg%2)*32 + (step%2)*16 + (kg/2)*8 + 0..7.  Experts past E are zero.  A thread writes the 16 bytes of
+// one lane (one value each: some 2 us more).
+__global__ __launch_bounds__(256) void gate_pack_wg_kernel(const bf16_t* __restrict__ wg, bf16_t* __restrict__ wfrag, int d, int E, int NT) {
+    const int64_t n = (int64_t)(d / 32) * NT * 64;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int lane = (int)(i & 63), blk = (int)(i >> 6), kg = lane >> 4;
+        const int step = blk / NT, e = (blk - step * NT) * 16 + (lane & 15);
+        const int k = (step >> 1) * 64 + (kg & 1) * 32 + ((step & 1) * 2 + (kg >> 1)) * 8;
+        bf16_t v[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) v[z] = e < E ? wg[(size_t)(k + z) * E + e] : (bf16_t)0;
+        uint4 o;
+        o.x = v[0] | (uint32_t)v[1] << 16; o.y = v[2] | (uint32_t)v[3] << 16;
+        o.z = v[4] | (uint32_t)v[5] << 16; o.w = v[6] | (uint32_t)v[7] << 16;
+        *reinterpret_cast<uint4*>(wfrag + i * 8) = o;
     }
 }
+
+template <int N>
+struct GateTag {
+    static constexpr int value = N;
+};
 
 // Maximum over the 64 lanes, returned wave-uniform: DPP row shifts build the maximum of each
 // row of 16 in its last lane, two row broadcasts carry it to lane 63.
@@ -172,66 +182,115 @@ __device__ __forceinline__ void gate_finish(float* part, const float* __restrict
     }
 }
 
-template <int NT, int NW>  // expert tiles of 32; wavefronts (the contraction is split NW ways)
-__global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgT,
+// NT expert tiles of 16, MB token tiles of 16, NW wavefronts.  A wavefront goes through its part in pairs of chunks of U units, a unit
+// is a k-step and G of the expert tiles; the operands of one chunk are requested before the MFMAs of the other.
+template <int NT, int MB, int NW>
+__global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wfrag,
                                                              const float* __restrict__ bias, int32_t* __restrict__ ids,
                                                              float* __restrict__ wout, float* __restrict__ logits_out,
                                                              int Tn, int d, int E, int k) {
-    extern __shared__ float part[];  // [NW][32][NT*32] partial logits, then the picked logits [32][MOE_MAX_EXPERTS]
-    constexpr int EP = NT * 32;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int l32 = lane & 31, kg = lane >> 5;
-    const int t0 = blockIdx.x * kGateMT;
-    int trow = t0 + l32;
-    trow = trow < Tn ? trow : Tn - 1;
-    const int kq = d / NW;
-    const bf16_t* xa = x + (size_t)trow * d + wave * kq + kg * 32;
-    const bf16_t* wb = wgT + ((size_t)wave * (kq / 64) * NT) * 2048 + lane * 8;  // fragment-major, see gate_pack_wg_kernel
+    extern __shared__ float part[];  // [NW][MT][EP] partial logits, then the picked logits [MT][MOE_MAX_EXPERTS]
+    constexpr int EP = NT * 16, MT = MB * 16, G = NT < 8 ? NT : 8, H = NT / G;
+    constexpr int U = NT <= 2 ? 2 : 1;
+    constexpr int kSteps = 2 * U / H;  // k-steps of a pair
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int64_t first = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * MT;
+    if (first >= Tn) return;
+    const int t0 = (int)first;
+    const int ns = d / (32 * NW), pairs = (ns + kSteps - 1) / kSteps;  // of this wavefront's part of the hidden dimension
+    const int k_lane = wave * ns * 32 + (kg & 1) * 32 + (kg >> 1) * 8;
+    const bf16_t* xa[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) xa[i] = x + (size_t)min(t0 + i * 16 + l16, Tn - 1) * d;
+    const bf16_t* wb = wfrag + (size_t)wave * ns * NT * 512 + lane * 8;
 
-    gf32x16 acc[NT];
+    gf32x4 acc[MB][NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-
-    // operands of chunk c+1 are requested before the MFMAs of chunk c (HBM latency, not
-    // bandwidth, is what a 32-token tile has to hide)
-    gbf16x8 a[2][4], b[2][NT][4];
-    auto load_chunk = [&](int c, gbf16x8 (&aa)[4], gbf16x8 (&bb)[NT][4]) {
+        for (int j = 0; j < NT; ++j) acc[i][j] = (gf32x4){0.f, 0.f, 0.f, 0.f};
+    gbf16x8 a[2][U][MB], b[2][U][G];
+    auto step_of = [&](int p, int c, int u) { return p * kSteps + (c * U + u) / H; };
+    // (past the end: any valid addresses, mma leaves them out)
+    auto load = [&](int p, auto c_tag) {
+        constexpr int c = decltype(c_tag)::value;
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) aa[s4] = *reinterpret_cast<const gbf16x8*>(xa + c + s4 * 8);
+        for (int u = 0; u < U; ++u) {
+            const int step = min(step_of(p, c, u), ns - 1), h = (c * U + u) % H;
+            const int kk = k_lane + (step >> 1) * 64 + (step & 1) * 16;
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+            for (int i = 0; i < MB; ++i) a[c][u][i] = *reinterpret_cast<const gbf16x8*>(xa[i] + kk);
 #pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4)
-                bb[j][s4] = *reinterpret_cast<const gbf16x8*>(wb + (((size_t)(c >> 6) * NT + j) * 4 + s4) * 512);
-    };
-    auto mma_chunk = [&](const gbf16x8 (&aa)[4], const gbf16x8 (&bb)[NT][4]) {
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4)
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa[s4], bb[j][s4], acc[j], 0, 0, 0);
-    };
-    load_chunk(0, a[0], b[0]);
-    for (int c = 0; c < kq; c += 128) {   // kq is a multiple of 64
-        const int c1 = c + 64 < kq ? c + 64 : c, c2 = c + 128 < kq ? c + 128 : c;
-        load_chunk(c1, a[1], b[1]);
-        mma_chunk(a[0], b[0]);
-        load_chunk(c2, a[0], b[0]);
-        if (c + 64 < kq) mma_chunk(a[1], b[1]);
-    }
-    // partial sums -> LDS (accumulator layout: col = lane%32, row = 8*(r/4) + 4*(lane/32) + r%4)
-    float* mine = part + (size_t)wave * kGateMT * EP;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = (r >> 2) * 8 + kg * 4 + (r & 3);
-            mine[row * EP + j * 32 + l32] = acc[j][r];
+            for (int j = 0; j < G; ++j) b[c][u][j] = *reinterpret_cast<const gbf16x8*>(wb + ((size_t)step * NT + h * G + j) * 512);
         }
+    };
+    auto mma = [&](int p, auto c_tag) {
+        constexpr int c = decltype(c_tag)::value;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int step = step_of(p, c, u);
+            const int h = (c * U + u) % H;
+            if (step >= ns) break;
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+                    acc[i][h * G + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c][u][i], b[c][u][j], acc[i][h * G + j], 0, 0, 0);
+        }
+    };
+    load(0, GateTag<0>{});
+    for (int p = 0; p < pairs; ++p) {
+        load(p, GateTag<1>{});
+        mma(p, GateTag<0>{});
+        if (p + 1 < pairs) load(p + 1, GateTag<0>{});
+        mma(p, GateTag<1>{});
+    }
+    // partial sums -> LDS (accumulator layout: col = lane%16, row = 4*(lane/16) + r)
+    float* mine = part + (size_t)wave * MT * EP;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mine[(i * 16 + kg * 4 + r) * EP + j * 16 + l16] = acc[i][j][r];
     __syncthreads();
-    gate_finish<NT * 32, NW, NW, kGateMT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
+    gate_finish<EP, NW, NW, MT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
+}
+
+// Tokens per workgroup: 32 read the weight half as often from L2, 16 fill the chip twice as well.  The whole call in us, 16 tokens
+// and 32: up to 32 experts, 8192 x 6144 37, 34, 8192 x 4096 26, 25, 16384 x 6144 67, 60; 64 experts, 2048 x 2048 11, 15, 8192 x 2048 18.6,
+// 18.0, 16384 x 4096 57, 48; 128 experts of 2048, 8192 28, 34, 12000 39, 45, 16384 49, 47, of 6144, 16384 120, 92; up to 16 experts
+// the same at 16384 and 1777 tokens of 4096 in 11 and 17; more than 128 experts 4096 x 2048 29, 43, 16384 x 2048 91, 93.
+// Wavefronts: 8 where every part is whole 64-wide chunks, 4 from 128 padded experts on (their partial sums leave room for fewer
+// workgroups on a unit).
+static void launch_gate_topk_mfma(const moe_shape* s, const bf16_t* x, const bf16_t* w_gate, const float* bias, int32_t* ids, float* w,
+                                  float* logits, bf16_t* wfrag, hipStream_t st) {
+    const int NT = gate_tiles16(s->E);
+    const int64_t pieces = (int64_t)(s->d / 32) * NT * 64;
+    gate_pack_wg_kernel<<<(unsigned)((pieces + 255) / 256 < 2048 ? (pieces + 255) / 256 : 2048), 256, 0, st>>>(w_gate, wfrag, s->d, s->E, NT);
+    auto go = [&](auto kern, int mt, int nw) {
+        size_t lds = (size_t)nw * mt * NT * 16 * sizeof(float);                                           // partial logits
+        if (lds < (size_t)mt * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)mt * MOE_MAX_EXPERTS * sizeof(float);
+        ensure_dynamic_lds(reinterpret_cast<const void*>(kern), 4 * 32 * MOE_MAX_EXPERTS * sizeof(float));
+        constexpr int64_t kMost = 1 << 20;
+        const int64_t blocks = ((int64_t)s->T + mt - 1) / mt;
+        const dim3 grid = blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
+        kern<<<grid, nw * 64, lds, st>>>(x, wfrag, bias, ids, w, logits, s->T, s->d, s->E, s->k);
+    };
+    const bool many = s->T >= (NT == 8 ? 16384 : 8192), eight = s->d % 512 == 0;
+#define MOE_GATE_LAUNCH(N, W)                             \
+    if (many) go(gate_topk_mfma_kernel<N, 2, W>, 32, W);  \
+    else go(gate_topk_mfma_kernel<N, 1, W>, 16, W);
+    if (NT == 1 && eight) { MOE_GATE_LAUNCH(1, 8) }
+    else if (NT == 1) { MOE_GATE_LAUNCH(1, 4) }
+    else if (NT == 2 && eight) { MOE_GATE_LAUNCH(2, 8) }
+    else if (NT == 2) { MOE_GATE_LAUNCH(2, 4) }
+    else if (NT == 4 && eight) { MOE_GATE_LAUNCH(4, 8) }
+    else if (NT == 4) { MOE_GATE_LAUNCH(4, 4) }
+    else if (NT == 8) { MOE_GATE_LAUNCH(8, 4) }
+    else go(gate_topk_mfma_kernel<16, 1, 4>, 16, 4);
+#undef MOE_GATE_LAUNCH
 }
 
 // ---- fp32, and bf16 with a hidden dimension that the kernel above does not split evenly ------------------
@@ -241,11 +300,6 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* _
 // wavefront requests U 16-wide pieces before it uses the first.  bf16 values are widened, which is exact.
 // Measured against one lane per expert and a serial walk of the hidden dimension (us): fp32, 2048 tokens x 1024, 8
 // experts 200 -> 7; fp32, 256 x 128, 8 experts 33 -> 4; bf16, 4099 x 1096, 24 experts 300 -> 26.
-template <int N>
-struct GateTag {
-    static constexpr int value = N;
-};
-
 __device__ __forceinline__ gf32x4 gate_load4(const float* p) { return *reinterpret_cast<const gf32x4*>(p); }
 __device__ __forceinline__ gf32x4 gate_load4(const bf16_t* p) {
     const uint2 u = *reinterpret_cast<const uint2*>(p);
@@ -630,28 +684,8 @@ extern "C" moe_status moe_gate_topk(const moe_shape* s, const void* x, const voi
     const size_t split = gate_split_bytes(s);
     float* slices = split && ws && aligned16(ws) && ws_bytes >= split ? static_cast<float*>(ws) : nullptr;
     if (packed && !slices) {
-        const int nt = (s->E + 31) / 32;
-        const int NT = nt <= 1 ? 1 : nt <= 2 ? 2 : nt <= 4 ? 4 : 8;
-        bf16_t* wgT = static_cast<bf16_t*>(ws);
-        const int grid = (s->T + kGateMT - 1) / kGateMT;
-        // 8 wavefronts (the contraction split 8 ways) halve the chain of dependent loads of a 32-token tile;
-        // from 128 padded experts on, 4 wavefronts and half the partial-sum area (two workgroups per CU) do better.
-        const int NW = (s->d % 512 == 0 && NT <= 2) ? 8 : 4;
-        gate_pack_wg_kernel<<<256, 256, 0, st>>>(static_cast<const bf16_t*>(w_gate), wgT, s->d, s->E, NT, NW);
-        size_t lds = (size_t)NW * kGateMT * NT * 32 * sizeof(float);            // partial logits
-        if (lds < (size_t)kGateMT * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)kGateMT * MOE_MAX_EXPERTS * sizeof(float);
-#define MOE_GATE_LAUNCH(N, W)                                                                                      \
-    {                                                                                                              \
-        ensure_dynamic_lds(reinterpret_cast<const void*>(&gate_topk_mfma_kernel<N, W>), 4 * kGateMT * 256 * 4);    \
-        gate_topk_mfma_kernel<N, W><<<grid, W * 64, lds, st>>>(static_cast<const bf16_t*>(x), wgT, bias, topk_ids, \
-                                                               topk_w, logits_out, s->T, s->d, s->E, s->k);        \
-    }
-        if (NW == 8) {
-            if (NT == 1) MOE_GATE_LAUNCH(1, 8) else if (NT == 2) MOE_GATE_LAUNCH(2, 8) else MOE_GATE_LAUNCH(4, 8)
-        } else {
-            if (NT == 1) MOE_GATE_LAUNCH(1, 4) else if (NT == 2) MOE_GATE_LAUNCH(2, 4) else if (NT == 4) MOE_GATE_LAUNCH(4, 4) else MOE_GATE_LAUNCH(8, 4)
-        }
-#undef MOE_GATE_LAUNCH
+        launch_gate_topk_mfma(s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w_gate), bias, topk_ids, topk_w, logits_out,
+                              static_cast<bf16_t*>(ws), st);
         return launch_status(who);
     }
     if (s->dtype == MOE_BF16)

@@ -35,6 +35,13 @@ SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260,
          (905, 768, 200, 8, torch.bfloat16), (2000, 264, 129, 2, torch.float32)]  # 57 and 125 token tiles: no even split of 256
 
 
+# bf16 kernels that contract the whole hidden dimension: one to 16 expert tiles, 16 and 32 tokens per workgroup with a remainder,
+# four and eight parts of the hidden dimension, of one chunk (half a pair) and of several
+SIZES += [(1030, d, E, k, torch.bfloat16) for d, E, k in [(256, 3, 2), (512, 17, 3), (768, 40, 2), (2560, 16, 4), (768, 100, 8), (256, 200, 6)]]
+SIZES += [(8191, 256, 20, 2, torch.bfloat16), (8192, 512, 32, 2, torch.bfloat16), (8205, 256, 50, 2, torch.bfloat16), (8205, 512, 50, 2, torch.bfloat16),
+          (8205, 768, 9, 2, torch.bfloat16), (16383, 256, 128, 3, torch.bfloat16), (16401, 256, 128, 3, torch.bfloat16)]
+
+
 @pytest.mark.parametrize("least_ws", [False, True])  # with the least workspace the dimension is never split
 @pytest.mark.parametrize("T,d,E,k,dtype", SIZES)
 def test_gate_topk_edges(T, d, E, k, dtype, least_ws):
