@@ -1,22 +1,25 @@
-// Grouped fp32 GEMM on v_mfma_f32_16x16x4: fp32 operands, products and sums, at twice the rate of the scalar FMA units.
+// Grouped fp32 GEMM on v_mfma_f32_32x32x2: fp32 operands, products and sums, at twice the rate of the scalar FMA units.
 // Operand forms, tile walk and epilogues as in the bf16 kernels.  (Products with very many tiles: grouped_gemm_f32_large.h.)
 //
-// What bounds it is the matrix pipe (154 TFLOP/s in a loop of these MFMAs alone, 139 at the 2.1 GHz that the power limit
+// What bounds it is the matrix pipe (154 TFLOP/s in a loop of 16x16x4 MFMAs alone, 139 at the 2.1 GHz that the power limit
 // leaves a whole kernel), and before that the last tiles: few experts of 64 to 1000 rows make few tiles.  So a workgroup of
 // four wavefronts owns a tile of 64 x 64 only, and a ring of three LDS stages of 32 contraction indices (48 KB, three
-// workgroups per unit), filled by DMA two stages ahead.  A wavefront computes 32 x 32 in 2 x 2 blocks; MFMA z of 16
-// contraction indices contracts z, 4+z, 8+z, 12+z.
+// workgroups per unit), filled by DMA two stages ahead.  A wavefront computes one block of 32 x 32; of 16 contraction indices MFMAs
+// 2z and 2z+1 contract z, 4+z and 8+z, 12+z (the sums are those of 16x16x4 MFMAs that contract z, 4+z, 8+z, 12+z, bit for bit).
 //
 // Measured, training passes (us; 128x128 or 64x64 tiles staged through registers, 16 indices per stage -> this): 2048 tokens, 8
 // experts of 1024 x 2816 2368 -> 2157; 4096 tokens, 4 of 2048 x 5632 8428 -> 7870; 512 tokens, 8 of 1024 x 2816 970 -> 816;
 // 2000 tokens, 24 of 516 x 1036 925 -> 798; forward of 64 tokens, 64 of 2048 x 1408 1230 -> 665, of 8 tokens, 8 of
 // 1024 x 2816 205 -> 142.  80 to 110 TFLOP/s.  Tried: 64 x 128 tiles (-4 to +1.5 %), 128 x 128 with two stages (0 to -18 %), two
-// or four stages (-2 to +1, -3 to -6 %), fragments of the next half stage read under the MFMAs of this one (0).
+// or four stages (-2 to +1, -3 to -6 %), fragments of the next half stage read under the MFMAs of this one (0).  2 x 2 blocks in
+// 16x16x4 instead of the one: 2124 us where this takes 2105 (2048 tokens, 8 experts of 1024 x 2816).  What the DMA costs, from copies
+// of that one with pieces left out: without requests in the loop 1882 of 2123 us, without LDS reads 2102, without barriers too 1862.
 //
 // LDS: an operand whose contraction index is contiguous in memory ("row form") lies as [64 rows][128 B], the 16-byte piece
-// p of row r in slot p ^ ((r >> 1) & 7); a lane reads its row's k = 4*(lane/16) .. +3 at once.  An operand whose other index is
-// contiguous ("k-row form") lies as [32 k-rows][256 B], piece p of k-row q in slot p ^ swz_f32(q); a lane reads W neighbouring
-// columns of a k-row at once, one for each of W blocks: block j of those holds columns W*n + j, n = 0 .. 15.
+// p of row r in slot p ^ ((r >> 1) & 7); a lane reads its row's k = 8*p + 4*(lane/32) .. +3 at once.  An operand whose other index is
+// contiguous ("k-row form") lies as [32 k-rows][256 B], piece p of k-row q in slot p ^ swz_f32(q); half a wavefront reads 32
+// columns of a k-row, the other half those of the k-row four further on, from the other half of the banks (two matrices, 16 columns of
+// each: from the other two quarters).
 #pragma once
 
 namespace moe {
@@ -25,10 +28,11 @@ constexpr int kF32Tile = 64, kF32K = 32, kF32Stages = 3;
 constexpr int kF32Operand = kF32Tile * kF32K * 4;              // bytes of one operand's stage
 constexpr int kF32Lds = kF32Stages * 2 * kF32Operand;
 
-__device__ __forceinline__ int swz_f32(int q) { return 8 * ((q >> 2) & 1) + 4 * ((q >> 3) & 1); }
+template <bool DUAL>
+__device__ __forceinline__ int swz_f32(int q) { return (DUAL ? 4 : 8) * ((q >> 2) & 1); }
 
 // This wavefront's DMA chunks (1 KB) of one operand's stages.
-template <int FORM>  // 0: row form; 1: k-row form
+template <int FORM, bool DUAL>  // 0: row form; 1: k-row form
 struct F32Issue {
     static constexpr int kChunks = kF32Operand / 4096;  // per wavefront and stage
     static constexpr int kRowPieces = FORM == 0 ? 8 : kF32Tile / 4;
@@ -48,7 +52,7 @@ struct F32Issue {
                 r = line;
                 kk[i] = (slot ^ swz_rows(line)) * 4;
             } else {
-                r = (slot ^ swz_f32(line)) * 4;
+                r = (slot ^ swz_f32<DUAL>(line)) * 4;
                 kk[i] = line;
             }
             const bool second = split && r >= kF32Tile / 2;
@@ -78,11 +82,9 @@ __device__ __forceinline__ void lds_floats(const char* p, float (&v)[W]) {
 template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GArgs g) {
     static_assert(!(DUAL && BT == 1), "two B matrices are taken in k-row form only");
-    using TA = F32Issue<AT>;
-    using TB = F32Issue<BT == 0 ? 1 : 0>;
+    using TA = F32Issue<AT, false>;
+    using TB = F32Issue<BT == 0 ? 1 : 0, DUAL>;
     constexpr int BM = kF32Tile, S = kF32Stages;
-    constexpr int NB = BM / 32;              // 16x16 blocks per wavefront along each side
-    constexpr int WB = DUAL ? NB / 2 : NB;   // blocks that share a read of B in k-row form
     constexpr int kOperand = kF32Operand, kStage = 2 * kOperand;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -134,50 +136,40 @@ __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GArgs g) {
     segment(0);
 
     // ---- compute side ----
-    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, kg = lane >> 4;
-    f32x4v acc[NB][NB];
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    // v[p][z]: this lane's row or column `line` at k = 16*h + 8*p + 4*kg + z
+    auto frags = [&](auto form, auto dual, const char* s, int line, int h, float (&v)[2][4]) {
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = (f32x4v){0.f, 0.f, 0.f, 0.f};
-    // v[j][z]: block j's value at k = 16*h + 4*kg + z
-    auto frags = [&](auto form, auto width, const char* s, int first, int h, float (&v)[NB][4]) {
-        constexpr int W = decltype(width)::value;
-        if constexpr (decltype(form)::value == 0) {
+        for (int p = 0; p < 2; ++p) {
+            if constexpr (decltype(form)::value == 0) {
+                lds_floats<4>(s + line * 128 + (((h * 4 + p * 2 + kg) ^ swz_rows(l32)) << 4), v[p]);  // (swz_rows repeats every 16 rows)
+            } else {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int r = first + j * 16 + l16;
-                lds_floats<4>(s + r * 128 + (((h * 4 + kg) ^ swz_rows(l16)) << 4), v[j]);  // (swz_rows repeats every 16 rows)
-            }
-        } else {
-#pragma unroll
-            for (int z = 0; z < 4; ++z)
-#pragma unroll
-                for (int q = 0; q < NB / W; ++q) {  // (DUAL: q is the matrix)
-                    const int col = q * (BM / 2) + first + l16 * W, k = kg * 4 + z;
-                    float x[W];
-                    lds_floats<W>(s + (h * 16 + k) * (BM * 4) + (((col >> 2) ^ swz_f32(k)) << 4) + (col & 3) * 4, x);
-#pragma unroll
-                    for (int j = 0; j < W; ++j) v[q * W + j][z] = x[j];
+                for (int z = 0; z < 4; ++z) {
+                    const int k = h * 16 + p * 8 + kg * 4 + z;
+                    v[p][z] = *reinterpret_cast<const float*>(s + k * (BM * 4) + (((line >> 2) ^ swz_f32<decltype(dual)::value>(kg * 4)) << 4) + (line & 3) * 4);
                 }
+            }
         }
     };
+    // (two matrices: 16 columns of each)
+    const int a_line = wm * 32 + l32, b_line = DUAL ? (l32 >> 4) * (BM / 2) + wn * 16 + (l32 & 15) : wn * 32 + l32;
     auto compute = [&](int buf) {
         const char* sa = smem + buf * kStage;
         const char* sb = sa + kOperand;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            float a[NB][4], b[NB][4];
-            frags(IntTag<AT>{}, IntTag<NB>{}, sa, wm * (BM / 2), h, a);
-            frags(IntTag<BT == 0 ? 1 : 0>{}, IntTag<WB>{}, sb, wn * 16 * WB, h, b);
-            // (B first: blocks are accumulated transposed)
+            float a[2][4], b[2][4];
+            frags(IntTag<AT>{}, IntTag<0>{}, sa, a_line, h, a);
+            frags(IntTag<BT == 0 ? 1 : 0>{}, IntTag<DUAL>{}, sb, b_line, h, b);
+            // (B first: the block is accumulated transposed)
 #pragma unroll
             for (int z = 0; z < 4; ++z)
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][z], a[i][z], acc[i][j], 0, 0, 0);
+                for (int p = 0; p < 2; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[p][z], a[p][z], acc, 0, 0, 0);
         }
     };
     for (int s = 0; s < S - 1 && s < total; ++s) issue(s, s);
@@ -194,24 +186,15 @@ __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GArgs g) {
         fill = fill + 1 == S ? 0 : fill + 1;
     }
 
-    // ---- epilogue: a lane holds, of each of its rows, quads of four consecutive columns ----
+    // ---- epilogue: a lane holds quads of four consecutive columns of one row ----
     const int64_t cbase = RAGK ? (int64_t)e * g.strideC : 0;
+    const int row = m0 + wm * 32 + l32;
+    auto quad = [&](int t) { return (f32x4v){acc[4 * t], acc[4 * t + 1], acc[4 * t + 2], acc[4 * t + 3]}; };
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int row = m0 + wm * (BM / 2) + (AT == 0 ? i * 16 + l16 : l16 * NB + i);
-        auto quad = [&](int q, int t) {  // matrix q, quad t
-            if constexpr (BT == 1) return acc[i][t];
-            f32x4v v;
-#pragma unroll
-            for (int z = 0; z < 4; ++z) v[z] = acc[i][q * WB + (4 * t + z) % WB][(4 * t + z) / WB];
-            return v;
-        };
-#pragma unroll
-        for (int t = 0; t < WB; ++t) {
-            const int col = n0 + wn * 16 * WB + (BT == 1 ? t * 16 + kg * 4 : kg * 4 * WB + t * 4);
-            if (row < m_lim && col < g.N)
-                epilogue_x4<float, EPI>(g, cbase + (int64_t)row * g.ldc + col, quad(0, t), quad(DUAL ? 1 : 0, t));
-        }
+    for (int t = 0; t < (DUAL ? 2 : 4); ++t) {
+        const int col = n0 + wn * (DUAL ? 16 : 32) + t * 8 + kg * 4;
+        if (row < m_lim && col < g.N)
+            epilogue_x4<float, EPI>(g, cbase + (int64_t)row * g.ldc + col, quad(t), quad(DUAL ? t + 2 : t));
     }
 }
 

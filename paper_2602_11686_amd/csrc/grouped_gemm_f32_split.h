@@ -1,5 +1,5 @@
 // Grouped fp32 GEMM for products with few tiles: the wavefronts of a workgroup share a 32 x 32 tile and split its contraction.
-// Operand forms, tile walk, epilogues and MFMAs as in grouped_gemm_f32.h.
+// Operand forms, tile walk and epilogues as in grouped_gemm_f32.h; MFMAs 16x16x4, in 2 x 2 blocks.
 //
 // What bounds a product that leaves units idle is the chain of one tile: 32 MFMAs (1024 clocks) per wavefront and stage of 32
 // contraction indices, one memory latency at the start, and a barrier per stage.  Here wavefront w contracts the slabs
