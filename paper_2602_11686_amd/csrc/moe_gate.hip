@@ -16,6 +16,8 @@ static inline size_t gate_needed_bytes(const moe_shape* s) { return align_up((si
 // ---- short batches: the hidden dimension split over workgroups --------------------------------------------
 constexpr int kGateF32Tokens = 16, kGateF32Waves = 8;
 static inline int gate_tiles16(int E) { const int n = (E + 15) / 16; return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : n <= 8 ? 8 : 16; }
+// the gate weight in blocks of 16 experts x 16 k-values
+static inline size_t gate_pack16_bytes(const moe_shape* s) { return (size_t)((s->d + 15) / 16) * 16 * gate_tiles16(s->E) * 16 * 2; }
 static inline bool gate_packed(const moe_shape* s) { return s->dtype == MOE_BF16 && s->d % 256 == 0; }
 // Workgroups per token tile: enough for every compute unit, at least 16 values of the hidden dimension per wavefront.  With
 // more than 128 experts a workgroup's partial sums (128 KB) leave no room for a second one on its unit, and the few past
@@ -38,8 +40,9 @@ static inline size_t gate_split_bytes(const moe_shape* s) {
     return s->T <= (gate_packed(s) ? 1024 : 2048) && gate_splits(s) > 1 ? (size_t)gate_splits(s) * s->T * gate_tiles16(s->E) * 16 * sizeof(float) : 0;
 }
 size_t gate_workspace_bytes(const moe_shape* s) {
-    const size_t a = gate_needed_bytes(s), b = align_up(gate_split_bytes(s), 256);
-    return a > b ? a : b;
+    size_t n = gate_needed_bytes(s);
+    for (const size_t b : {align_up(gate_split_bytes(s), 256), align_up(gate_pack16_bytes(s), 256)}) n = n > b ? n : b;
+    return n;
 }
 
 // ---- bf16 forward on the matrix cores ------------------------------------------------------
@@ -307,9 +310,24 @@ __device__ __forceinline__ gf32x4 gate_load4(const bf16_t* p) {
                     __uint_as_float(u.y & 0xFFFF0000u)};
 }
 
+// PACKED: the gate weight (bf16) in the order the lanes consume it: block (16 k-values, expert tile j), lane (l16, kg) holds expert
+// j*16 + l16, k = 4*kg .. +3.  One load of 8 bytes per lane and block instead of four of 2 bytes.
+// Experts past E and k past d are zero.
+__global__ __launch_bounds__(256) void gate_pack16_wg_kernel(const bf16_t* __restrict__ wg, bf16_t* __restrict__ wfrag, int d, int E, int NT) {
+    const int64_t n = (int64_t)((d + 15) / 16) * NT * 64;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int lane = (int)(i & 63), blk = (int)(i >> 6), step = blk / NT;
+        const int e = (blk - step * NT) * 16 + (lane & 15), k = step * 16 + (lane >> 4) * 4;
+        bf16_t v[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) v[z] = e < E && k < d ? wg[(size_t)(k + z) * E + e] : (bf16_t)0;  // (d is a multiple of four)
+        *reinterpret_cast<uint2*>(wfrag + i * 4) = make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
+    }
+}
+
 // SPLIT: blockIdx.y picks a slice of the hidden dimension; the sums over the slice go to `slices`
 // ([gridDim.y][Tn][NT*16]) and gate_split_finish_kernel does the rest.
-template <class T, int NT, bool SPLIT>  // NT expert tiles of 16
+template <class T, int NT, bool SPLIT, bool PACKED>  // NT expert tiles of 16
 __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     const T* __restrict__ x, const T* __restrict__ wg, const float* __restrict__ bias, int32_t* __restrict__ ids,
     float* __restrict__ wout, float* __restrict__ logits_out, float* __restrict__ slices, int Tn, int d, int E, int k) {
@@ -341,6 +359,13 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 const int e = j * 16 + l16;
+                if constexpr (PACKED) {
+                    gf32x4 v = {0.f, 0.f, 0.f, 0.f};
+                    if (in) v = gate_load4(wg + ((size_t)(c / 16 + u) * NT + j) * 256 + lane * 4);
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) b[u][j][z] = v[z];
+                    continue;
+                }
 #pragma unroll
                 for (int z = 0; z < 4; ++z) b[u][j][z] = in && e < E ? Elem<T>::load(wg + (size_t)(kk + z) * E + e) : 0.f;
             }
@@ -394,16 +419,28 @@ __global__ __launch_bounds__(256) void gate_split_finish_kernel(const float* __r
 
 template <class T>
 static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, const float* bias, int32_t* ids, float* w,
-                                 float* logits, float* slices, hipStream_t st) {
+                                 float* logits, float* slices, T* wfrag, hipStream_t st) {
     auto go = [&](auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
         size_t lds = (size_t)kGateF32Waves * kGateF32Tokens * NT * 16 * sizeof(float);
         if (lds < (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float);
         const unsigned tiles = (unsigned)(((int64_t)s->T + kGateF32Tokens - 1) / kGateF32Tokens), most = 1 << 22;
         const dim3 grid(tiles < most ? tiles : most, slices ? gate_splits(s) : 1, (tiles + most - 1) / most);
-        auto kern = slices ? gate_topk_f32_kernel<T, NT, true> : gate_topk_f32_kernel<T, NT, false>;
+        auto kern = slices ? gate_topk_f32_kernel<T, NT, true, false> : gate_topk_f32_kernel<T, NT, false, false>;
+        const T* w_in = wg;
+        // Packing the weight is a launch of 2 to 3 us.  The whole call without and with it, us: 16384 x 128, 5 experts 9.3, 10.9; 16384 x 640, 8
+        // 19.7, 19.0; 3000 x 520, 100 22.5, 22.4; 2100 x 1096, 24 20.3, 16.3; 4099 x 1096, 24 24.3, 18.8; 9000 x 1000, 160 158, 128;
+        // 5000 x 4488, 16 83, 48; 16384 x 2176, 128 263, 176.
+        if constexpr (sizeof(T) == 2) {
+            if (wfrag && !slices && s->d > 512) {
+                const int64_t blocks = ((int64_t)((s->d + 15) / 16) * NT * 64 + 255) / 256;
+                gate_pack16_wg_kernel<<<(unsigned)(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(wg, wfrag, s->d, s->E, NT);
+                kern = gate_topk_f32_kernel<T, NT, false, true>;
+                w_in = wfrag;
+            }
+        }
         ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kGateF32Waves * kGateF32Tokens * MOE_MAX_EXPERTS * 4);
-        kern<<<grid, kGateF32Waves * 64, lds, st>>>(x, wg, bias, ids, w, logits, slices, s->T, s->d, s->E, s->k);
+        kern<<<grid, kGateF32Waves * 64, lds, st>>>(x, w_in, bias, ids, w, logits, slices, s->T, s->d, s->E, s->k);
         if (slices)
             gate_split_finish_kernel<NT><<<(s->T + 3) / 4, 256, 0, st>>>(slices, (int)grid.y, bias, ids, w, logits, s->T, s->E, s->k);
     };
@@ -690,10 +727,10 @@ extern "C" moe_status moe_gate_topk(const moe_shape* s, const void* x, const voi
     }
     if (s->dtype == MOE_BF16)
         launch_gate_topk_f32(s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w_gate), bias, topk_ids, topk_w,
-                             logits_out, slices, st);
+                             logits_out, slices, ws && aligned16(ws) && ws_bytes >= gate_pack16_bytes(s) ? static_cast<bf16_t*>(ws) : nullptr, st);
     else
         launch_gate_topk_f32(s, static_cast<const float*>(x), static_cast<const float*>(w_gate), bias, topk_ids, topk_w,
-                             logits_out, slices, st);
+                             logits_out, slices, static_cast<float*>(nullptr), st);
     return launch_status(who);
 }
 

@@ -39,6 +39,8 @@ SIZES = [(1, 36, 1, 1, torch.float32), (15, 4, 16, 16, torch.float32), (17, 260,
 # four and eight parts of the hidden dimension, of one chunk (half a pair) and of several
 SIZES += [(1030, d, E, k, torch.bfloat16) for d, E, k in [(256, 3, 2), (512, 17, 3), (768, 40, 2), (2560, 16, 4), (768, 100, 8), (256, 200, 6)]]
 SIZES += [(8191, 256, 20, 2, torch.bfloat16), (8192, 512, 32, 2, torch.bfloat16), (8205, 256, 50, 2, torch.bfloat16), (8205, 512, 50, 2, torch.bfloat16),
+          # hidden dimensions that are no multiple of 256, past the batches whose dimension is split: the packed weight of the fp32 MFMAs
+          (2050, 1096, 24, 3, torch.bfloat16), (2060, 520, 200, 8, torch.bfloat16), (2049, 2056, 100, 4, torch.bfloat16), (2049, 648, 3, 1, torch.bfloat16),
           (8205, 768, 9, 2, torch.bfloat16), (16383, 256, 128, 3, torch.bfloat16), (16401, 256, 128, 3, torch.bfloat16)]
 
 
