@@ -327,7 +327,13 @@ __global__ __launch_bounds__(256) void gate_pack16_wg_kernel(const bf16_t* __res
 
 // SPLIT: blockIdx.y picks a slice of the hidden dimension; the sums over the slice go to `slices`
 // ([gridDim.y][Tn][NT*16]) and gate_split_finish_kernel does the rest.
-template <class T, int NT, bool SPLIT, bool PACKED>  // NT expert tiles of 16
+//
+// ROWS: E fills the expert tiles.  Tile j's column l16 is expert l16*NT + j, so that a lane reads its NT experts of a k-row at once
+// (plain: of 64 experts four loads of 2 bytes 32 bytes apart).  The whole call, us: 64 x 2048, 128 experts 11.5 -> 10.6; 512 x 2048, 64
+// 10.0 -> 8.6; 1024 x 2048, 64 15.8 -> 12.3; 1024 x 2048, 128 27.1 -> 17.9; 1000 x 4096, 32 21.3 -> 15.7; 300 x 1096, 256 18.2 -> 18.8 (so not
+// there).  The same bits.
+enum { GATE_PLAIN = 0, GATE_PACKED = 1, GATE_ROWS = 2 };
+template <class T, int NT, bool SPLIT, int WFORM>  // NT expert tiles of 16
 __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     const T* __restrict__ x, const T* __restrict__ wg, const float* __restrict__ bias, int32_t* __restrict__ ids,
     float* __restrict__ wout, float* __restrict__ logits_out, float* __restrict__ slices, int Tn, int d, int E, int k) {
@@ -350,16 +356,28 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
     for (int c = kb; c < ke; c += 16 * U) {
         gf32x4 a[U];
         float b[U][NT][4];
+        struct alignas(NT * sizeof(T) < 16 ? NT * sizeof(T) : 16) Row { T v[NT]; };
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int kk = c + u * 16 + kg * 4;  // (d is a multiple of four: four values are inside or outside together)
             const bool in = kk < ke;
             a[u] = (gf32x4){0.f, 0.f, 0.f, 0.f};
             if (in) a[u] = gate_load4(x + (size_t)trow * d + kk);
+            if constexpr (WFORM == GATE_ROWS) {
+                Row row[4] = {};
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    if (in) row[z] = *reinterpret_cast<const Row*>(wg + (size_t)(kk + z) * EP + l16 * NT);
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) b[u][j][z] = Elem<T>::load(&row[z].v[j]);
+                continue;
+            }
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 const int e = j * 16 + l16;
-                if constexpr (PACKED) {
+                if constexpr (WFORM == GATE_PACKED) {
                     gf32x4 v = {0.f, 0.f, 0.f, 0.f};
                     if (in) v = gate_load4(wg + ((size_t)(c / 16 + u) * NT + j) * 256 + lane * 4);
 #pragma unroll
@@ -383,7 +401,7 @@ __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) mine[(kg * 4 + r) * EP + j * 16 + l16] = acc[j][r];
+        for (int r = 0; r < 4; ++r) mine[(kg * 4 + r) * EP + (WFORM == GATE_ROWS ? l16 * NT + j : j * 16 + l16)] = acc[j][r];
     __syncthreads();
     if constexpr (SPLIT) {
         for (int i = threadIdx.x; i < MT * EP; i += NW * 64) {
@@ -426,7 +444,10 @@ static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, co
         if (lds < (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float)) lds = (size_t)kGateF32Tokens * MOE_MAX_EXPERTS * sizeof(float);
         const unsigned tiles = (unsigned)(((int64_t)s->T + kGateF32Tokens - 1) / kGateF32Tokens), most = 1 << 22;
         const dim3 grid(tiles < most ? tiles : most, slices ? gate_splits(s) : 1, (tiles + most - 1) / most);
-        auto kern = slices ? gate_topk_f32_kernel<T, NT, true, false> : gate_topk_f32_kernel<T, NT, false, false>;
+        auto kern = slices ? gate_topk_f32_kernel<T, NT, true, GATE_PLAIN> : gate_topk_f32_kernel<T, NT, false, GATE_PLAIN>;
+        if constexpr (NT > 1 && NT < 16 && sizeof(T) == 2) {
+            if (s->E == NT * 16) kern = slices ? gate_topk_f32_kernel<T, NT, true, GATE_ROWS> : gate_topk_f32_kernel<T, NT, false, GATE_ROWS>;
+        }
         const T* w_in = wg;
         // Packing the weight is a launch of 2 to 3 us.  The whole call without and with it, us: 16384 x 128, 5 experts 9.3, 10.9; 16384 x 640, 8
         // 19.7, 19.0; 3000 x 520, 100 22.5, 22.4; 2100 x 1096, 24 20.3, 16.3; 4099 x 1096, 24 24.3, 18.8; 9000 x 1000, 160 158, 128;
@@ -435,7 +456,7 @@ static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, co
             if (wfrag && !slices && s->d > 512) {
                 const int64_t blocks = ((int64_t)((s->d + 15) / 16) * NT * 64 + 255) / 256;
                 gate_pack16_wg_kernel<<<(unsigned)(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(wg, wfrag, s->d, s->E, NT);
-                kern = gate_topk_f32_kernel<T, NT, false, true>;
+                kern = gate_topk_f32_kernel<T, NT, false, GATE_PACKED>;
                 w_in = wfrag;
             }
         }

@@ -41,6 +41,8 @@ SIZES += [(1030, d, E, k, torch.bfloat16) for d, E, k in [(256, 3, 2), (512, 17,
 SIZES += [(8191, 256, 20, 2, torch.bfloat16), (8192, 512, 32, 2, torch.bfloat16), (8205, 256, 50, 2, torch.bfloat16), (8205, 512, 50, 2, torch.bfloat16),
           # hidden dimensions that are no multiple of 256, past the batches whose dimension is split: the packed weight of the fp32 MFMAs
           (2050, 1096, 24, 3, torch.bfloat16), (2060, 520, 200, 8, torch.bfloat16), (2049, 2056, 100, 4, torch.bfloat16), (2049, 648, 3, 1, torch.bfloat16),
+          # as many experts as the tiles hold: a lane reads those of a k-row at once; split and not, with a remainder of k
+          (100, 1032, 32, 3, torch.bfloat16), (33, 72, 64, 2, torch.bfloat16), (700, 520, 128, 8, torch.bfloat16), (2049, 264, 64, 4, torch.bfloat16),
           (8205, 768, 9, 2, torch.bfloat16), (16383, 256, 128, 3, torch.bfloat16), (16401, 256, 128, 3, torch.bfloat16)]
 
 
