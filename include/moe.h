@@ -174,7 +174,9 @@ moe_status moe_permute_lite(const moe_shape* shape, int32_t G, int32_t n_rep, co
 /* moe_grouped_ffn_fwd over replica groups: the rows [group_offsets[g], group_offsets[g+1]) are
  * multiplied with the weights of expert expert_of_group[g] (DEVICE array [G]; entries are clamped
  * into [0, E-1]).  Replicas of one expert share its weights, so with the rows of moe_permute_lite
- * the layer output equals that of the plain path bit for bit.  Everything else as moe_grouped_ffn_fwd. */
+ * the layer output equals that of the plain path bit for bit.  (The same shape is meant.  In fp32 the order in which
+ * a row's products are added up depends on T*k, E, d and f, so calls of other shapes can differ in last bits; in bf16,
+ * with operands of fewer than 2^32 elements, it does not.)  Everything else as moe_grouped_ffn_fwd. */
 moe_status moe_grouped_ffn_fwd_groups(const moe_shape* shape, int32_t G, const int32_t* expert_of_group,
                                       const void* x_perm, const int32_t* group_offsets, const void* w1,
                                       const void* w3, const void* w2, void* y_perm, void* a_save,

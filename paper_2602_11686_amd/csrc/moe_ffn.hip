@@ -467,12 +467,12 @@ static dim3 f32_grid(int64_t tiles) {
     return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)((blocks + kMost - 1) / kMost));
 }
 
-// number of bm x bm tiles (ragged M: an upper bound)
+// number of bm x bm tiles (ragged M: an upper bound) where the rows belong to `groups` groups
 template <bool DUAL, bool RAGK>
-static int64_t f32_tiles(const GArgs& g, int64_t R, int bm) {
+static int64_t f32_tiles(const GArgs& g, int64_t R, int bm, int groups) {
     const int n_out = DUAL ? bm / 2 : bm;
     const int64_t n = (g.N + n_out - 1) / n_out;
-    return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * g.E : (R + bm - 1) / bm + g.E);
+    return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * groups : (R + bm - 1) / bm + groups);
 }
 
 // Whether a product is one for gg_f32_split_kernel, by the number of 64x64 tiles (ragged M: an upper bound) and the mean rows per
@@ -486,11 +486,14 @@ static int64_t f32_tiles(const GArgs& g, int64_t R, int bm) {
 //     68, 43, 122 -> 64, 31, 25, 39; 4 of 2048 x 4096, 8 rows 99, 94, 47, 170 -> 104, 31, 30, 54   32 rows: 46, 26, 28, 42 -> 57, 32, 30, 46
 //   gradients: 48 51 -> 17   64 16 -> 7.4   96 53 -> 29   128 29 -> 17, 6.8 -> 6.1   256 11 -> 13, 30 -> 30   640 and more 1.1 to 2.8
 //     times as long (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
+// Its sums are in another order than those of the other fp32 kernels.  So the products over ragged rows count the experts, not the
+// replica groups that their rows may be cut into: those must give the same bits.
 template <bool DUAL, bool RAGK>
 static bool f32_split_tiles(const GArgs& g, int64_t R) {
-    const int64_t tiles = f32_tiles<DUAL, RAGK>(g, R, kF32Tile);
+    const int experts = RAGK ? g.E : g.n_weights;
+    const int64_t tiles = f32_tiles<DUAL, RAGK>(g, R, kF32Tile, experts);
     if (RAGK) return tiles <= 128;
-    if (R <= 16 * (int64_t)g.E) return true;
+    if (R <= 16 * (int64_t)experts) return true;
     if (DUAL) return tiles <= 128 || (tiles <= 320 && g.K >= 2048);
     return tiles <= 192;
 }
@@ -499,13 +502,13 @@ template <int AT, int BT, bool DUAL, int EPI, bool RAGK>
 static void launch_f32_split(const GArgs& g, int64_t R, hipStream_t st) {
     auto kern = gg_f32_split_kernel<AT, BT, DUAL, EPI, RAGK>;
     ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kF32SplitLds);
-    kern<<<f32_grid(f32_tiles<DUAL, RAGK>(g, R, kF32SplitTile)), 256, kF32SplitLds, st>>>(g);
+    kern<<<f32_grid(f32_tiles<DUAL, RAGK>(g, R, kF32SplitTile, g.E)), 256, kF32SplitLds, st>>>(g);
 }
 
 static void launch_f32_split_bwd(const GArgs& dx, const GArgs& dw2, const GArgs& dw13, int64_t R, hipStream_t st) {
     auto blocks = [](int64_t tiles) { return (int)((tiles + 63) / 64 * 64); };
-    F32SplitBwdArgs a{dx, dw2, dw13, blocks(f32_tiles<false, false>(dx, R, kF32SplitTile)), blocks(f32_tiles<false, true>(dw2, R, kF32SplitTile))};
-    const int64_t all = (int64_t)a.dx_blocks + a.dw2_blocks + blocks(f32_tiles<true, true>(dw13, R, kF32SplitTile));
+    F32SplitBwdArgs a{dx, dw2, dw13, blocks(f32_tiles<false, false>(dx, R, kF32SplitTile, dx.E)), blocks(f32_tiles<false, true>(dw2, R, kF32SplitTile, dw2.E))};
+    const int64_t all = (int64_t)a.dx_blocks + a.dw2_blocks + blocks(f32_tiles<true, true>(dw13, R, kF32SplitTile, dw13.E));
     ensure_dynamic_lds(reinterpret_cast<const void*>(&gg_f32_split_bwd_kernel), kF32SplitLds);
     gg_f32_split_bwd_kernel<<<f32_grid(all), 256, kF32SplitLds, st>>>(a);
 }
@@ -577,13 +580,13 @@ static void launch_gg(const moe_shape* s, const GArgs& g, int64_t R, hipStream_t
             return;
         }
         if constexpr (BT == 0) {
-            const int64_t large = f32_tiles<DUAL, RAGK>(g, R, kF32LargeTile);
+            const int64_t large = f32_tiles<DUAL, RAGK>(g, R, kF32LargeTile, g.E);
             if (f32_large_tiles<DUAL, RAGK>(large, R, g.E)) {
                 gg_f32_large_kernel<AT, DUAL, EPI, RAGK><<<f32_grid(large), 256, 0, st>>>(g);
                 return;
             }
         }
-        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, f32_tiles<DUAL, RAGK>(g, R, kF32Tile), st);
+        launch_f32<AT, BT, DUAL, EPI, RAGK>(g, f32_tiles<DUAL, RAGK>(g, R, kF32Tile, g.E), st);
     }
 }
 

@@ -11,7 +11,7 @@ from oracle import planner_oracle as PO
 from paper_2602_11686_amd import binding as B
 from paper_2602_11686_amd import inputs as I
 from tests.gpu_common import TOL, host
-from tests.helpers import rel_max
+from tests.helpers import rel_max, rel_max_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -272,3 +272,54 @@ def test_few_row_groups_equal_the_plain_path_over_their_weights(counts, eog):
                lambda a, b, dx, g1, g3, g2, ws: B.moe_grouped_ffn_bwd(p, x, off, v1, v3, v2, a, b, dy, dx, g1, g3, g2, ws), p)
     for u, v in zip(got, want):
         assert torch.isfinite(u).all() and torch.equal(u, v)
+
+
+# An expert's rows cut into groups: the rows keep their order and their results must keep their bits, although the mean rows per group
+# and the number of tiles, by which the bf16 and fp32 kernels are chosen, are not those of the experts.  Replicas without rows, entries
+# out of range (the first below, the last above).  Where the line to the fp32 kernel with a split contraction, counted over groups
+# instead of experts, would put the groups on the other side; fp32 tiles of 128x128 (experts) and 64x64 (groups); the fp32 products
+# behind dH in one launch (small); on the split kernel by the mean rows alone (at most 16 per expert, 24 experts); bf16 with 64 rows
+# per expert and 16 per group, and with contractions that are no multiple of 64
+GROUPED = {"f32 W1|W3, dgrad 1": (torch.float32, [16] * 32, [g // 4 for g in range(32)], 8, 512, 1024),
+           "f32 W1|W3 the other way": (torch.float32, [16, 0, 41, 8] * 8, [g // 4 for g in range(32)], 8, 128, 192),
+           "f32 large": (torch.float32, [128] * 15 + [150], [g // 8 for g in range(16)], 2, 36, 7300),
+           "f32 small": (torch.float32, [5, 33, 0, 64, 31, 0, 40, 1], [-3, 0, 1, 1, 2, 3, 3, 99], 4, 100, 68),
+           "f32 few rows": (torch.float32, [9, 0, 1, 16, 3, 7] * 8, [g // 2 for g in range(48)], 24, 1028, 776),
+           "bf16": (torch.bfloat16, [16] * 31 + [9], [-1] + [g // 4 for g in range(1, 31)] + [8], 8, 512, 768),
+           "bf16 remainders": (torch.bfloat16, [30, 0, 33, 1] * 8, [g // 4 for g in range(32)], 8, 520, 776)}
+
+
+@pytest.mark.parametrize("case", GROUPED)
+def test_groups_of_an_experts_rows_give_its_bits(case):
+    dt, counts, eog, E, d, f = GROUPED[case]
+    print(f"case {case}", flush=True)
+    G, R = len(counts), sum(counts)
+    at = np.clip(eog, 0, E - 1)
+    g_off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    e_off = np.concatenate([[0], np.cumsum(np.bincount(at, weights=counts, minlength=E))]).astype(np.int32)
+    assert (np.diff(at) >= 0).all()
+    rng = np.random.default_rng(R + d)
+    values = lambda *n, std=1.0: torch.from_numpy((rng.standard_normal(n) * std).astype(np.float32)).to(dt)
+    data = x, dy, w1, w3, w2 = values(R, d), values(R, d), values(E, d, f, std=0.05), values(E, d, f, std=0.05), values(E, f, d, std=0.05)
+    x, dy, w1, w3, w2 = (v.cuda() for v in data)
+    s = B.Shape(R, d, f, E, 1, dt)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    nan = lambda *n: torch.full(n, float("nan"), dtype=dt, device="cuda")
+    y, a, b, dx, g1, g3, g2 = nan(R, d), nan(R, f), nan(R, f), nan(R, d), nan(E, d, f), nan(E, d, f), nan(E, f, d)
+    B.moe_grouped_ffn_fwd(s, x, i32(e_off), w1, w3, w2, y, a, b, ws)
+    B.moe_grouped_ffn_bwd(s, x, i32(e_off), w1, w3, w2, a, b, dy, dx, g1, g3, g2, ws)
+    yg, ag, bg, dxg, g1, g3, g2 = nan(R, d), nan(R, f), nan(R, f), nan(R, d), nan(G, d, f), nan(G, d, f), nan(G, f, d)
+    B.moe_grouped_ffn_fwd_groups(s, G, i32(eog), x, i32(g_off), w1, w3, w2, yg, ag, bg, ws)
+    B.moe_grouped_ffn_bwd_groups(s, G, i32(eog), x, i32(g_off), w1, w3, w2, ag, bg, dy, dxg, g1, g3, g2, ws)
+    torch.cuda.synchronize()
+    for name, u, v in (("A", a, ag), ("B", b, bg), ("Yp", y, yg), ("dXp", dx, dxg)):
+        assert torch.isfinite(u).all() and torch.equal(u, v), name
+    # the gradients of the groups, against the oracle over the gathered weights
+    x, dy, w1, w3, w2 = (v.double().numpy() for v in data)
+    ref_dx, r1, r3, r2 = O.ffn_bwd(x, g_off, w1[at], w3[at], w2[at], dy)
+    assert rel_max(host(dxg), ref_dx) <= TOL[dt]
+    for name, got, want in (("dW1", g1, r1), ("dW3", g3, r3), ("dW2", g2, r2)):
+        got = host(got)
+        assert np.isfinite(got).all(), name
+        err, g = rel_max_blocks(got, want, range(G))
+        assert err <= TOL[dt], (name, "group", g, err)
