@@ -475,17 +475,19 @@ static int64_t f32_tiles(const GArgs& g, int64_t R, int bm, int groups) {
     return n * (RAGK ? (int64_t)((g.M + bm - 1) / bm) * groups : (R + bm - 1) / bm + groups);
 }
 
-// Whether a product is one for gg_f32_split_kernel, by the number of 64x64 tiles (ragged M: an upper bound) and the mean rows per
-// expert.  Kernel times, gg_f32_kernel -> gg_f32_split_kernel (us):
-//   one matrix, tiles: 32 9.6 -> 5.2 (contraction 512: 14.6 -> 6.9)   64 9.3 -> 6.0   96 47 -> 28   128 27 -> 17   160 68 -> 31   192 27 -> 23
-//     contraction of 512: 256 16 -> 18   288 23 -> 27   320 38 -> 40   640 34 -> 36  (1024 and more: 288 42 -> 34, 320 43 -> 36, 264 36 -> 39)
-//   two matrices: 128 8.0 -> 6.7   192 8.7 -> 11.0, 15 -> 22 (contraction 128)   320 23 -> 29 (256)
-//     of 2048 and more: 192 52 -> 42   256 97 -> 80   320 81 -> 65   640 149 -> 145
-//   at most 16 rows per expert (a tile of 64 rows would be empty but for a quarter): 64 experts of 2048 x 1408, 4 rows, the products
-//     over ragged rows 538, 262, 265, 475 -> 411, 178, 174, 349; 8 of 1024 x 2816, 4 rows 65, 66, 40, 118 -> 64, 32, 27, 37, 16 rows 69,
-//     68, 43, 122 -> 64, 31, 25, 39; 4 of 2048 x 4096, 8 rows 99, 94, 47, 170 -> 104, 31, 30, 54   32 rows: 46, 26, 28, 42 -> 57, 32, 30, 46
-//   gradients: 48 51 -> 17   64 16 -> 7.4   96 53 -> 29   128 29 -> 17, 6.8 -> 6.1   256 11 -> 13, 30 -> 30   640 and more 1.1 to 2.8
-//     times as long (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
+// Whether a product is one for gg_f32_split_kernel, by the number of 64x64 tiles (ragged M: an upper bound), the mean rows per
+// expert and the contraction.  Kernel times over those of gg_f32_kernel in 2x2 blocks, least and most of 4 to 256 experts of 128 x 128
+// to 4096 x 1024:
+//   more than 16 rows per expert, one matrix, tiles: up to 64 0.33 to 0.90   128 0.31 to 0.73   192 0.32 to 0.97   320 0.59 to 1.40
+//     640 0.53 to 1.79 (the shorter the contraction the worse)
+//   two matrices: up to 64 0.72 to 0.78   128 0.35 to 0.76   192 0.37 to 0.93   320 0.59 to 1.33.  Contractions of 2048 and more: 192
+//     0.37 to 0.63, 256 0.61 and 0.62, 264 0.59 (4 experts with 32 rows), but 320 tiles all of which have rows 53 us -> 58
+//   at most 16 rows per expert (a tile of 64 rows would be empty but for a quarter), more tiles than that, rows even and Zipf-skewed:
+//     contractions of 128 0.74 to 1.41, of 256 0.58 to 1.15, of 512 and more 0.31 to 1.0 but for 1.11 at one row for each of 256 experts
+//     and 1.10 at 16 rows for each of 4.  Where a sixteenth of 128 or 256 experts has all the rows (the host cannot know) up to 1.8: the
+//     grid is made for every expert, and finding that a tile does not exist is what the empty workgroups do.
+//   gradients: up to 32 tiles 0.46 to 1.10   64 0.49 to 0.95   128 0.64 to 1.13 (the most: 4.4 us -> 4.9)   256 0.97 to 1.9   more
+//     up to 6 (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
 // Its sums are in another order than those of the other fp32 kernels.  So the products over ragged rows count the experts, not the
 // replica groups that their rows may be cut into: those must give the same bits.
 template <bool DUAL, bool RAGK>
@@ -493,8 +495,8 @@ static bool f32_split_tiles(const GArgs& g, int64_t R) {
     const int experts = RAGK ? g.E : g.n_weights;
     const int64_t tiles = f32_tiles<DUAL, RAGK>(g, R, kF32Tile, experts);
     if (RAGK) return tiles <= 128;
-    if (R <= 16 * (int64_t)experts) return true;
-    if (DUAL) return tiles <= 128 || (tiles <= 320 && g.K >= 2048);
+    if (R <= 16 * (int64_t)experts && (int64_t)g.K * g.nseg >= 512) return true;
+    if (DUAL) return tiles <= 128 || (g.K >= 2048 && tiles <= 320 && f32_tiles<DUAL, RAGK>(g, R, kF32Tile, 0) <= 192);
     return tiles <= 192;
 }
 

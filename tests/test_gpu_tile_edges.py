@@ -88,17 +88,23 @@ def test_ffn_f32_stages(counts, d, f):
 
 # fp32, 32x32 tiles with the contraction split over four wavefronts: tiles, columns and slabs of 32 with remainders; fewer slabs
 # than wavefronts, one more than they can hold in their rings, segments that begin in the middle of the four; few rows per expert
-# with many tiles.  The last case is over every line of the dispatch: 64x64 tiles in all products, with remainders everywhere.
-@pytest.mark.parametrize("split,counts,d,f", [(True, (31, 0, 32, 33, 1), 36, 68), (True, (2, 5), 4, 160), (True, (65, 0, 127), 132, 292),
-                                              (True, (300, 4), 100, 36), (True, (9, 0, 16, 1, 40, 3) * 4, 1028, 776),
-                                              (False, (65, 130, 0, 63, 1, 300), 836, 1092)])
+# with many tiles, and with contractions on the two sides of 512; two matrices with a long contraction and tiles that have no rows, and
+# with rows in all.  By product over ragged rows (W1|W3, W2, dgrad 1, dX) which are split (s), and whether the three products behind dH
+# go into one launch (1), the gradients are split alone (s) or not (-).
+@pytest.mark.parametrize("split,counts,d,f", [("ssss1", (31, 0, 32, 33, 1), 36, 68), ("ssss1", (2, 5), 4, 160), ("ssss1", (65, 0, 127), 132, 292),
+                                              ("ssss1", (300, 4), 100, 36), ("ssss-", (9, 0, 16, 1, 40, 3) * 4, 1028, 776),
+                                              ("-----", (65, 130, 0, 63, 1, 300), 836, 1092), ("-s-s-", (9, 0, 16, 1, 40, 3) * 8, 508, 512),
+                                              ("---s-", (9, 0, 16, 1, 40, 3) * 8, 508, 508), ("s-s--", (9, 0, 16, 1, 40, 3) * 8, 512, 252),
+                                              ("s-s--", (70, 0, 30, 29), 2048, 1380), ("--s--", (66, 400, 500, 34), 2048, 508)])
 def test_ffn_f32_split(split, counts, d, f):
     up = lambda n, m: -(-n // m)
     E, R = len(counts), sum(counts)
-    rows, few = up(R, 64) + E, R <= 16 * E
-    over_rows = [few or rows * up(f, 32) <= 128, few or rows * up(d, 64) <= 192, few or rows * up(f, 64) <= 192]
+    rows, few = up(R, 64) + E, lambda k: R <= 16 * E and k >= 512
+    dual = rows * up(f, 32) <= 128 or (d >= 2048 and rows * up(f, 32) <= 320 and up(R, 64) * up(f, 32) <= 192)
+    over_rows = [few(d) or dual, few(f) or rows * up(d, 64) <= 192, few(d) or rows * up(f, 64) <= 192, few(2 * f) or rows * up(d, 64) <= 192]
     grads = [E * up(f, 64) * up(d, 64) <= 128, E * up(d, 64) * up(f, 32) <= 128]
-    assert all(over_rows) if split else not any(over_rows + grads)
+    assert "".join("s" if p else "-" for p in over_rows) == split[:4]
+    assert ("1" if all(grads + over_rows[3:]) else "s" if all(grads) else "-" if not any(grads) else "?") == split[4]
     check_ffn(counts, d, f, torch.float32, 3 * d + f)
 
 
