@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void gate_pack16_wg_kernel(const bf16_t* __res
 // ROWS: E fills the expert tiles.  Tile j's column l16 is expert l16*NT + j, so that a lane reads its NT experts of a k-row at once
 // (plain: of 64 experts four loads of 2 bytes 32 bytes apart).  The whole call, us: 64 x 2048, 128 experts 11.5 -> 10.6; 512 x 2048, 64
 // 10.0 -> 8.6; 1024 x 2048, 64 15.8 -> 12.3; 1024 x 2048, 128 27.1 -> 17.9; 1000 x 4096, 32 21.3 -> 15.7; 300 x 1096, 256 18.2 -> 18.8 (so not
-// there).  The same bits.
+// there).  The same bits.  Against PACKED: gate_pack_pays.
 enum { GATE_PLAIN = 0, GATE_PACKED = 1, GATE_ROWS = 2 };
 template <class T, int NT, bool SPLIT, int WFORM>  // NT expert tiles of 16
 __global__ __launch_bounds__(kGateF32Waves * 64) void gate_topk_f32_kernel(
@@ -435,6 +435,30 @@ __global__ __launch_bounds__(256) void gate_split_finish_kernel(const float* __r
     gate_finish<EP, 1, 4, MT>(part, bias, ids, wout, logits_out, t0, Tn, E, k);
 }
 
+// Whether the bf16 weight is packed for gate_topk_f32_kernel when the hidden dimension is not split.  Packing is a launch of 2 to 3 us, and what
+// it saves grows with the hidden dimension and the tokens; the packed form goes over all of the expert tiles that an instance has, the plain one
+// skips those without experts (65 to 80 experts fill 5 of 8).  The whole call in us, plain and packed (tokens x d, experts):
+//   one tile: 2049 x 520, 8 7.3, 8.3   4096 x 520 8.3, 8.8   16384 x 520 16.7, 16.2   2049 x 648, 16 8.2, 8.6   3000 x 648 9.2,
+//     9.0   2049 x 776, 8 9.2, 9.2   2049 x 904, 12 11.4, 9.8   16384 x 2056 53, 40
+//   all of 2, 4, 8 or 16 (or 15): 2049 x 520, 17 10.6, 10.6, 28 10.8, 10.7, 120 25.2, 22.9, 255 49, 39   4099 x 1096, 24 24.3, 18.8
+//   7 of 8, 11 to 14 of 16: 2049 x 520, 100 22.4, 23.1, 176 38.6, 39.8   3000 x 520, 100 23.1, 22.8   2049 x 1000, 176 62, 55
+//   3 of 4, 6 of 8: 2049 x 776, 48 17.7, 18.4   4096 x 520, 40 14.5, 15.6   2049 x 904, 96 33.2, 31.2   6000 x 520, 96 29.4, 28.8
+//   5 of 8: 8192 x 776, 72 36.5, 39.4   2049 x 2056, 72 55, 62   4096 x 2056, 72 64, 63   12000 x 776, 72 69, 67   16384 x 520, 65 55, 52
+//   9 or 10 of 16: 4096 x 520, 144 34.9, 40.1   2049 x 1496, 129 75, 82   2049 x 2056, 160 119, 117   6000 x 520, 129 68, 64
+// As many experts as the tiles hold (GATE_ROWS needs no packing): 2049 x 520, 32 8.0, 10.7   16384 x 2056, 64 75, 111, 128 132, 175   8200 wide, 128
+// 2049 154, 223; but of 32 experts from some 3000 on: 4096 x 3080 33.9, 32.9   2049 x 4104 42.6, 41.0   8192 x 6152 104, 94   (16384 x 4104 131, 133).
+static bool gate_pack_pays(const moe_shape* s) {
+    const int NT = gate_tiles16(s->E), live = (s->E + 15) / 16;
+    if (s->d <= 512) return false;
+    if (s->E == NT * 16 && NT > 1 && NT < 16) return NT == 2 && s->d > 3072;
+    if (NT == 1) return s->d > 768 || s->T > 8192 || (s->d > 640 && s->T > 2900);
+    if (8 * live > 7 * NT) return true;
+    if (NT == 8 && live == 5) return (int64_t)s->d * s->T > 7600000;
+    if (NT == 16 && live <= 10) return s->d > 2048 || s->T > 4096;
+    if (4 * live == 3 * NT && NT < 16) return s->d > 896 || s->T > 4096;
+    return (int64_t)s->d * s->T > 1200000;
+}
+
 template <class T>
 static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, const float* bias, int32_t* ids, float* w,
                                  float* logits, float* slices, T* wfrag, hipStream_t st) {
@@ -449,11 +473,8 @@ static void launch_gate_topk_f32(const moe_shape* s, const T* x, const T* wg, co
             if (s->E == NT * 16) kern = slices ? gate_topk_f32_kernel<T, NT, true, GATE_ROWS> : gate_topk_f32_kernel<T, NT, false, GATE_ROWS>;
         }
         const T* w_in = wg;
-        // Packing the weight is a launch of 2 to 3 us.  The whole call without and with it, us: 16384 x 128, 5 experts 9.3, 10.9; 16384 x 640, 8
-        // 19.7, 19.0; 3000 x 520, 100 22.5, 22.4; 2100 x 1096, 24 20.3, 16.3; 4099 x 1096, 24 24.3, 18.8; 9000 x 1000, 160 158, 128;
-        // 5000 x 4488, 16 83, 48; 16384 x 2176, 128 263, 176.
         if constexpr (sizeof(T) == 2) {
-            if (wfrag && !slices && s->d > 512) {
+            if (wfrag && !slices && gate_pack_pays(s)) {
                 const int64_t blocks = ((int64_t)((s->d + 15) / 16) * NT * 64 + 255) / 256;
                 gate_pack16_wg_kernel<<<(unsigned)(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(wg, wfrag, s->d, s->E, NT);
                 kern = gate_topk_f32_kernel<T, NT, false, GATE_PACKED>;

@@ -46,6 +46,24 @@ SIZES += [(8191, 256, 20, 2, torch.bfloat16), (8192, 512, 32, 2, torch.bfloat16)
           (8205, 768, 9, 2, torch.bfloat16), (16383, 256, 128, 3, torch.bfloat16), (16401, 256, 128, 3, torch.bfloat16)]
 
 
+# the packed weight on either side of its lines: one tile of experts, 16 of 17, 5 of 8, 9 of 16, 3 of 4, 6 of 8, the 2 tiles that 32 experts
+# fill, 7 of 8
+PACKED = [(2049, 904, 7, 2), (2049, 760, 7, 2), (2901, 648, 7, 2), (2051, 520, 20, 2), (3900, 2056, 70, 2), (2060, 1096, 70, 2), (4097, 520, 130, 2), (2049, 520, 130, 2),
+          (2049, 904, 40, 2), (2049, 904, 90, 2), (2049, 520, 90, 2), (2049, 3080, 32, 2), (2049, 1096, 32, 2), (2310, 520, 100, 2), (2049, 520, 100, 2)]
+SIZES += [(T, d, E, k, torch.bfloat16) for T, d, E, k in PACKED]
+
+
+@pytest.mark.parametrize("T,d,E,k", PACKED)
+def test_gate_weight_forms_give_the_same_bits(T, d, E, k):
+    """Packed or not, which goes by the sizes and by the workspace that the caller brings."""
+    s, x, wg, bias, ws, out = gate_case(T, d, E, k, torch.bfloat16, T + E)
+    B.moe_gate_topk(s, x, wg, bias, *out, ws)
+    other = [torch.empty_like(v) for v in out]
+    B.moe_gate_topk(s, x, wg, bias, *other, ws[:0])
+    torch.cuda.synchronize()
+    assert all(torch.equal(u, v) for u, v in zip(out, other))
+
+
 @pytest.mark.parametrize("least_ws", [False, True])  # with the least workspace the dimension is never split
 @pytest.mark.parametrize("T,d,E,k,dtype", SIZES)
 def test_gate_topk_edges(T, d, E, k, dtype, least_ws):
