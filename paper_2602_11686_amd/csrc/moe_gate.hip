@@ -57,8 +57,8 @@ size_t gate_workspace_bytes(const moe_shape* s) {
 // What bounds it is reading the tokens and, per workgroup, the whole gate weight (7 to 12 TB/s of both out of L2), and up to some
 // 4000 tokens the chain of one workgroup.  Measured (the whole call with the packing of the weight, us; 32 tokens in
 // 32x32x16 MFMAs, whose lanes read pieces of 16 bytes 64 bytes apart -> this): 1777 x 4096, 16 experts 19 -> 11; 4096 x 4096, 16 22 -> 13;
-// 2048 x 2048, 64 19 -> 11; 8192 x 2048, 64 21 -> 18; 4096 x 2048, 128 45 -> 20; 16384 x 2048, 128 56 -> 47; 16384 x 4096, 8 42 -> 38
-// (3.6 TB/s); 16384 x 2048, 160 137 -> 88; 16384 x 6144, 32 59 -> 61.
+// 2048 x 2048, 64 19 -> 11; 8192 x 2048, 64 21 -> 18; 4096 x 2048, 128 45 -> 20; 16384 x 2048, 128 56 -> 47; 16384 x 4096, 8 42 -> 33
+// (4.0 TB/s); 16384 x 2048, 160 137 -> 88; 16384 x 6144, 32 58 -> 54, 65536 200 -> 181 (a unit's tokens and weights requested together: 59, 207).
 typedef __bf16 gbf16x8 __attribute__((ext_vector_type(8)));
 typedef float gf32x4 __attribute__((ext_vector_type(4)));
 
@@ -218,12 +218,17 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* _
     // (past the end: any valid addresses, mma leaves them out)
     auto load = [&](int p, auto c_tag) {
         constexpr int c = decltype(c_tag)::value;
+        // (all units of a row one after the other: they are halves of the same lines)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int step = min(step_of(p, c, u), ns - 1), kk = k_lane + (step >> 1) * 64 + (step & 1) * 16;
+                a[c][u][i] = *reinterpret_cast<const gbf16x8*>(xa[i] + kk);
+            }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int step = min(step_of(p, c, u), ns - 1), h = (c * U + u) % H;
-            const int kk = k_lane + (step >> 1) * 64 + (step & 1) * 16;
-#pragma unroll
-            for (int i = 0; i < MB; ++i) a[c][u][i] = *reinterpret_cast<const gbf16x8*>(xa[i] + kk);
 #pragma unroll
             for (int j = 0; j < G; ++j) b[c][u][j] = *reinterpret_cast<const gbf16x8*>(wb + ((size_t)step * NT + h * G + j) * 512);
         }
