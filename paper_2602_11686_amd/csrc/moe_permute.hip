@@ -474,10 +474,10 @@ __global__ __launch_bounds__(256) void permute_scatter_rows_kernel(const u32x4* 
 // sorted, and where the pieces of x would leave units without work the slots of a token go to several threads.  us, chunks of
 // 256, x behind the ranks, all slots by one thread -> this: 8 tokens, top-2 of 8, 4096 wide 5.4 -> 3.7; 64, top-8 of 128, 2048 6.5 -> 4.1;
 // 256, top-4 of 64, 2048 6.2 -> 4.4; 512 of these 6.7 -> 5.6; 1024, top-4 of 16, 4096 13.8 -> 11.2; 4096, top-1 of 8, 512 7.2 -> 7.2.
-// Past 2^19 pieces of x the copy is what counts and its own kernel the better one (us, three launches and one launch before these
-// changes; 1024 tokens, top-4 of 16, 4096 wide, just within: 14.4, 13.5; 1000 of 5120: 15.7, 16.3; 1000 of 8192: 21.2, 22.8; 4096 tokens,
-// top-1 of 4, 1536 wide: 10.9, 11.6; of 64 experts 12.0, 10.8).
-constexpr uint32_t kSmallPieces = 1u << 19;
+// Three launches take longer whatever the pieces of x, as far as that was measured (2^23 of them; us, three and one): 1024 tokens, top-4 of
+// 16, 4096 wide 13.7, 10.9, 8192 wide 21.9, 17.6, 24576 54, 42; 4096 tokens, top-1 of 16, 1032 wide 10.1, 8.7, 4096 17.6, 15.1, 16384 53, 44;
+// 2048, top-2 of 64, 3072 13.7, 9.6; 512, top-8 of 16, 8192 21.0, 17.6; 16384 36, 32.
+constexpr uint32_t kSmallPieces = 1u << 23;
 constexpr int64_t kSmallItems = 1 << 18;  // a thread's single item in a grid that fills the chip
 constexpr int kSmallWaves = 16, kSmallPairs = kSmallWaves * 256;
 // CHUNK: pairs per wavefront.  An item of the copy is a 16-byte piece of x and one of `parts` sets of the k slots (s, s + parts, ...).

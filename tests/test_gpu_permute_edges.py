@@ -1,4 +1,4 @@
-"""moe_permute around the numbers of pairs (4096) and of 16-byte pieces of x (2^19) up to which one launch does all of it, the
+"""moe_permute around the numbers of pairs (4096) and of 16-byte pieces of x (2^23) up to which one launch does all of it, the
 numbers of pairs (1024, 2048) where its wavefronts take longer chunks, and the sizes where a thread copies to all slots of a
 token, to some or to one: whole numbers, exact."""
 import numpy as np
@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
                                            (300, 8192, 70, 2, torch.float32),
                                            (128, 4096, 16, 8, torch.bfloat16), (129, 4096, 16, 8, torch.bfloat16),
                                            (1024, 1040, 9, 2, torch.bfloat16), (683, 1800, 30, 3, torch.bfloat16),
-                                           (205, 5000, 256, 5, torch.bfloat16), (8, 4096, 8, 7, torch.bfloat16)])
+                                           (205, 5000, 256, 5, torch.bfloat16), (8, 4096, 8, 7, torch.bfloat16),
+                                           (1024, 65536, 5, 1, torch.bfloat16), (1025, 65536, 5, 1, torch.bfloat16), (2048, 8200, 9, 2, torch.bfloat16)])
 def test_permute(T, d, E, k, dtype):
     rng = np.random.default_rng(T + E)
     # skewed: low experts are picked more often, some not at all
