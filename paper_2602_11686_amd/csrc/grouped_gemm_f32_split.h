@@ -1,14 +1,14 @@
 // Grouped fp32 GEMM for products with few tiles: the wavefronts of a workgroup share a 32 x 32 tile and split its contraction.
 // Operand forms, tile walk and epilogues as in grouped_gemm_f32.h; MFMAs 16x16x4, in 2 x 2 blocks.
 //
-// What bounds a product that leaves units idle is the chain of one tile: 32 MFMAs (1024 clocks) per wavefront and stage of 32
-// contraction indices, one memory latency at the start, and a barrier per stage.  Here wavefront w contracts the slabs
+// What bounds a product that leaves units idle is the chain of one tile: 1024 clocks of MFMAs per wavefront and stage of 32
+// contraction indices (32 16x16x4 or 16 32x32x2), one memory latency at the start, and a barrier per stage.  Here wavefront w contracts the slabs
 // w, w+4, w+8, ... of 32 indices on its own, from a ring of two slabs (16 KB) that only it fills and reads: a quarter of the
 // chain, no barrier before the end, and 256 indices requested at once.  The four sums meet in LDS, added in the order of the
 // wavefronts.  A tile a quarter as large is four times the workgroups, at twice the operand traffic per FLOP: with enough tiles
 // the 64 x 64 kernel is the faster one (f32_split_tiles has the line).
 //
-// Measured, kernels of a training pass in launch order (us; 64 x 64 tiles -> this): 256 tokens, 8 experts of 128 x 256 8.0, 9.6, 9.3, 14.6,
+// Measured, kernels of a training pass in launch order (us; 64 x 64 tiles in 2 x 2 blocks -> this): 256 tokens, 8 experts of 128 x 256 8.0, 9.6, 9.3, 14.6,
 // 6.8, 6.8 -> 6.7, 5.2, 6.0, 6.9, 4.6, 6.1.  Whole passes: forward of 8 tokens, 8 experts of 1024 x 2816 151 -> 88, of 64 tokens, 64 of
 // 2048 x 1408 720 -> 540; training, 64 tokens, 8 of 1024 x 2816 411 -> 282, 2048 tokens, 4 of 256 x 512 239 -> 220.  Against 64 bits
 // four sums of a quarter each are closer than one (y of the first two 1.3e-6 -> 6.4e-7, 1.4e-6 -> 6.9e-7).

@@ -32,10 +32,14 @@ static inline int gate_splits(const moe_shape* s) {
     const int n = want < most ? want : most;
     return n < 32 ? n : 32;
 }
-// Up to how many tokens: a token tile of the kernels that contract the whole hidden dimension takes its 10 to 70 us
-// however few tiles there are (bf16, 8 .. 1024 tokens of 2048 x 64 experts: 15-18 us with the packing of the weight,
-// 7-15 us split; of 4096 x 128: 59-64 and 12-45).  At 2048 tokens the packed bf16 kernel is the faster one again
-// (18 and 23; 64 and 87), the fp32 one is not (of 2048 x 128: 38 us whole, 26 split).
+// Up to how many tokens: a token tile of the kernels that contract the whole hidden dimension takes its 6 to 70 us however few tiles
+// there are.  us, whole (with the packing of the weight) and split, 8, 512, 1024, 2048 tokens:
+//   bf16 MFMAs: 2048 x 64 experts 8.8, 7.1   10.1, 8.7   10.4, 12.0   10.7, 16.6    4096 x 128 20, 11   22, 17   23, 26   23, 40
+//     4096 x 8 8.2, 6.4   10.0, 8.3   10.2, 13.3   10.4, 20.6    2048 x 256 25, 18   28, 28   28, 48   28, 82
+//   fp32 MFMAs: fp32, 2048 x 128 34, 9   39, 13   39, 19   40, 27, at 4096 tokens (never split) 43; 1024 x 8 5.6, 5.1   7.0, 5.9   7.0, 7.1   7.4, 7.5
+//     bf16, 1096 x 24 15, 7   15, 8   15, 10   16, 14;   2056 x 128 68, 11   66, 15   65, 20   63, 28
+// So from some 600 tokens on the bf16 MFMAs would be faster whole.  They are split up to 1024 all the same: the two ways add in different
+// orders, so moving the line moves the logits of those batches in their last bits, and now and then a pick among near equals.
 static inline size_t gate_split_bytes(const moe_shape* s) {
     return s->T <= (gate_packed(s) ? 1024 : 2048) && gate_splits(s) > 1 ? (size_t)gate_splits(s) * s->T * gate_tiles16(s->E) * 16 * sizeof(float) : 0;
 }
@@ -267,9 +271,9 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(const bf16_t* _
 }
 
 // Tokens per workgroup: 32 read the weight half as often from L2, 16 fill the chip twice as well.  The whole call in us, 16 tokens
-// and 32: up to 32 experts, 8192 x 6144 37, 34, 8192 x 4096 26, 25, 16384 x 6144 67, 60; 64 experts, 2048 x 2048 11, 15, 8192 x 2048 18.6,
-// 18.0, 16384 x 4096 57, 48; 128 experts of 2048, 8192 28, 34, 12000 39, 45, 16384 49, 47, of 6144, 16384 120, 92; up to 16 experts
-// the same at 16384 and 1777 tokens of 4096 in 11 and 17; more than 128 experts 4096 x 2048 29, 43, 16384 x 2048 91, 93.
+// and 32: 17 to 32 experts, 4096 x 4096 14, 18, 6000 x 6144 33, 30, 8192 x 6144 36, 31, 8192 x 4096 26, 23, 16384 x 6144 63, 53; 64 experts,
+// 2048 x 2048 11, 14, 8192 x 2048 18.9, 18.0, 16384 x 4096 58, 48; 128 experts of 2048, 8192 28, 34, 12000 39, 45, 16384 49, 47, of 6144, 16384 120, 92; up to 16 experts
+// 1777 x 4096 11, 17, 8192 x 4096 22.7, 22.7, 16384 x 4096 36, 34; more than 128 experts 4096 x 2048 29, 43, 16384 x 2048 91, 93.
 // Wavefronts: 8 where every part is whole 64-wide chunks, 4 from 128 padded experts on (their partial sums leave room for fewer
 // workgroups on a unit).
 static void launch_gate_topk_mfma(const moe_shape* s, const bf16_t* x, const bf16_t* w_gate, const float* bias, int32_t* ids, float* w,
