@@ -228,3 +228,56 @@ def test_quadrant_kernel_meets_no_barrier_twice_in_a_row(ffn_asm):
                     seen = True
                 elif i.startswith(("ds_", "global_", "v_mfma", "s_cbranch", "s_branch")):
                     seen = False
+
+
+def hand_placed_waits(lines, first, last):
+    """[(line, count)] of the vmcnt waits in between, all of which must be written in inline assembly."""
+    by_hand, waits = False, []
+    for n in range(first, last):
+        if lines[n].startswith(";;#ASM"):
+            by_hand = lines[n].startswith(";;#ASMSTART")
+        elif lines[n].startswith("s_waitcnt") and "vmcnt" in lines[n]:
+            assert by_hand, (n, lines[n])
+            waits.append((n, int(re.search(r"vmcnt\((\d+)\)", lines[n]).group(1))))
+    return waits
+
+
+def test_fp32_ring_holds_only_the_hand_placed_vmcnt_waits(ffn_asm):
+    """gg_f32_kernel: one stage of DMA (four requests) stays in flight behind a wait, each wait stands in front of the stage's barrier.  The
+    forward products compute one 32x32 block per wavefront, the others 2x2 blocks of 16x16."""
+    found = re.findall(r"^(_ZN3moe13gg_f32_kernelILi([01])ELi([01])\w+):(.*?)^\.Lfunc_end", ffn_asm, re.S | re.M)
+    assert len(found) == 7, [f[0] for f in found]
+    for name, at, bt, text in found:
+        lines = [l.strip() for l in text.split("\n")]
+        mfma = [l.split()[0] for l in lines if l.startswith("v_mfma")]
+        assert mfma == (["v_mfma_f32_32x32x2_f32"] * 16 if at + bt == "00" else ["v_mfma_f32_16x16x4_f32"] * 32), name
+        waits = hand_placed_waits(lines, *stage_loop(lines, len(mfma)))
+        assert sorted(w for _, w in waits) == [0, 4], (name, waits)
+        for w, _ in waits:
+            assert next(l for l in lines[w + 1:] if l.startswith(("s_barrier", "v_mfma", "global_load_lds", "ds_read"))).startswith("s_barrier"), name
+
+
+def test_fp32_split_rings_hold_only_the_hand_placed_waits(ffn_asm):
+    """gg_f32_split_kernel and the three products of gg_f32_split_bwd_kernel: a wavefront's ring has no barrier, so what orders it are
+    its waits.  One slab of DMA (eight requests) stays in flight behind ``vmcnt(8)``, the last slab is waited for with 0, the compiler
+    adds no vmcnt wait, and a slab is requested anew only behind an ``lgkmcnt(0)`` that follows its last LDS read."""
+    tiles = {}
+    for m in re.finditer(r"^(_ZN3moe\d+gg_f32_split(?:_bwd)?_kernel\w+):(.*?)^\.Lfunc_end", ffn_asm, re.S | re.M):
+        name, lines = m.group(1), [l.strip() for l in m.group(2).split("\n")]
+        at, tiles[name] = 0, 0
+        while any(l.startswith("global_load_lds") for l in lines[at:]):
+            first = next(n for n in range(at, len(lines)) if lines[n].startswith("global_load_lds"))
+            end = next(n for n in range(first, len(lines)) if lines[n].startswith("ds_write"))   # the four sums
+            mfma = [n for n in range(first, end) if lines[n].startswith("v_mfma")]
+            assert len(mfma) == 32, (name, len(mfma))
+            assert sorted(w for _, w in hand_placed_waits(lines, first, mfma[-1])) == [0, 8], name
+            reads = [n for n in range(first, mfma[-1]) if lines[n].startswith("ds_read")]
+            refill = [n for n in range(reads[0], mfma[-1]) if lines[n].startswith("global_load_lds")]
+            assert len(refill) == 8 and refill[0] > reads[-1], name
+            assert any(l.startswith("s_waitcnt") and "lgkmcnt(0)" in l for l in lines[reads[-1]:refill[0]]), name
+            assert not any(l.startswith("s_barrier") for l in lines[first:end]), name
+            at, tiles[name] = end, tiles[name] + 1
+        assert sum(l.startswith("s_barrier") for l in lines) == tiles[name], name
+    assert sorted(tiles.values()) == [1] * 7 + [3], tiles
+    for m in re.finditer(r"\.amdhsa_kernel (_ZN3moe\d+gg_f32_(?:split_|split_bwd_)?kernel\w+)(.*?)\.end_amdhsa_kernel", ffn_asm, re.S):
+        assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", m.group(2)), m.group(1)
