@@ -484,8 +484,11 @@ static int64_t f32_tiles(const GArgs& g, int64_t R, int bm, int groups) {
 //     0.37 to 0.63, 256 0.61 and 0.62, 264 0.59 (4 experts with 32 rows), but 320 tiles all of which have rows 53 us -> 58
 //   at most 16 rows per expert (a tile of 64 rows would be empty but for a quarter), more tiles than that, rows even and Zipf-skewed:
 //     contractions of 128 0.74 to 1.41, of 256 0.58 to 1.15, of 512 and more 0.31 to 1.0 but for 1.11 at one row for each of 256 experts
-//     and 1.10 at 16 rows for each of 4.  Where a sixteenth of 128 or 256 experts has all the rows (the host cannot know) up to 1.8: the
-//     grid is made for every expert, and finding that a tile does not exist is what the empty workgroups do.
+//     and 1.10 at 16 rows for each of 4.  Where a sixteenth of the experts has all the rows, which the host cannot know, up to 1.8: with few rows
+//     most workgroups of a grid made for every expert find no tile, with more the tiles are four times as many for nothing.  Forward passes,
+//     64x64 tiles and this: 128 experts of 512 x 1024, 1 row on average 44, 36, 4 rows 53, 54, 16 rows 99, 119; 256 of these 62, 68, 78, 105, 168,
+//     235; 128 of 1024 x 768 with 16 rows 133, 149.  (As many workgroups as the chip holds, each taking tile after tile, spares the empty ones: 256 experts
+//     35, 77, 210, but 64 experts of 2048 x 1408 with 4 rows each 505 -> 555.)
 //   gradients: up to 32 tiles 0.46 to 1.10   64 0.49 to 0.95   128 0.64 to 1.13 (the most: 4.4 us -> 4.9)   256 0.97 to 1.9   more
 //     up to 6 (many tiles, few stages each).  dW_g stays there too: 5 -> 5 to 8.
 // Its sums are in another order than those of the other fp32 kernels.  So the products over ragged rows count the experts, not the
